@@ -45,51 +45,6 @@ struct DecArgs {
   WinDesc win[kHeadsPerLaunch];    // explicit windows of heads head_base .. head_base + 31
 };
 
-// The visible keys of the decoding query (distance-0 key c = N_k - 1) as up to
-// three ascending, merged key runs [a, b] -- the union of the sink, long-range
-// and near windows of Sec. 2.1 -- computed with scalar selects only (no
-// indexed arrays, which the compiler would place in scratch memory).  Empty
-// runs have a = kNone.
-constexpr int32_t kNone = 0x3fffffff;
-struct Runs3 {
-  int32_t a0, b0, a1, b1, a2, b2;
-};
-__device__ inline void order2(int32_t& a, int32_t& b, int32_t& c, int32_t& d) {  // (a, b) before (c, d)
-  const bool sw = c < a;
-  const int32_t ta = sw ? c : a, tb = sw ? d : b, tc = sw ? a : c, td = sw ? b : d;
-  a = ta; b = tb; c = tc; d = td;
-}
-__device__ inline Runs3 key_runs3(int32_t n_k, int32_t sink, int32_t near, int32_t lo, int32_t hi) {
-  const int32_t c = n_k - 1;
-  Runs3 r;
-  // near: delta in [0, near); sink: keys below sink; long: delta in [lo, hi)
-  r.a0 = near >= 1 ? max(0, c - near + 1) : kNone;
-  r.b0 = near >= 1 ? c : kNone - 1;
-  r.a1 = sink >= 1 ? 0 : kNone;
-  r.b1 = sink >= 1 ? min(sink - 1, c) : kNone - 1;
-  const bool has_long = hi > lo && c - lo >= 0;
-  r.a2 = has_long ? max(0, c - hi + 1) : kNone;
-  r.b2 = has_long ? c - lo : kNone - 1;
-  order2(r.a0, r.b0, r.a1, r.b1);
-  order2(r.a1, r.b1, r.a2, r.b2);
-  order2(r.a0, r.b0, r.a1, r.b1);
-  // merge overlapping or touching runs (an empty run starts at kNone and never merges)
-  if (r.a1 != kNone && r.a1 <= r.b0 + 1) {
-    r.b0 = max(r.b0, r.b1);
-    r.a1 = r.a2; r.b1 = r.b2;
-    r.a2 = kNone; r.b2 = kNone - 1;
-  }
-  if (r.a1 != kNone && r.a1 <= r.b0 + 1) {
-    r.b0 = max(r.b0, r.b1);
-    r.a1 = kNone; r.b1 = kNone - 1;
-  }
-  if (r.a2 != kNone && r.a2 <= r.b1 + 1) {
-    r.b1 = max(r.b1, r.b2);
-    r.a2 = kNone; r.b2 = kNone - 1;
-  }
-  return r;
-}
-
 // Sum over the DC lanes of each lane group (DC = 8 or 16 consecutive lanes,
 // inside one 16-lane DPP row), the result in every lane of the group:
 // quad butterflies, then mirrors within 8 and within 16 lanes.

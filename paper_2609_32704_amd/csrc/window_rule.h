@@ -120,6 +120,84 @@ __host__ __device__ inline uint32_t legal_queries32(const Geo32& g, int32_t q0, 
   return k < g.n_k ? m : 0u;
 }
 
+// Up to three ascending, merged inclusive ranges in scalars, built with selects
+// only (kernels: indexed arrays would go to scratch memory).  Empty ranges
+// have a = kNone and b = kNone - 1 and come last.
+constexpr int32_t kNone = 0x3fffffff;
+struct Runs3 {
+  int32_t a0, b0, a1, b1, a2, b2;
+};
+__host__ __device__ inline void order2(int32_t& a, int32_t& b, int32_t& c, int32_t& d) {  // (a, b) before (c, d)
+  const bool sw = c < a;
+  const int32_t ta = sw ? c : a, tb = sw ? d : b, tc = sw ? a : c, td = sw ? b : d;
+  a = ta; b = tb; c = tc; d = td;
+}
+__host__ __device__ inline void runs3_merge(Runs3& r) {
+  order2(r.a0, r.b0, r.a1, r.b1);
+  order2(r.a1, r.b1, r.a2, r.b2);
+  order2(r.a0, r.b0, r.a1, r.b1);
+  // merge overlapping or touching runs (an empty run starts at kNone and never merges)
+  if (r.a1 != kNone && r.a1 <= r.b0 + 1) {
+    r.b0 = imax32(r.b0, r.b1);
+    r.a1 = r.a2; r.b1 = r.b2;
+    r.a2 = kNone; r.b2 = kNone - 1;
+  }
+  if (r.a1 != kNone && r.a1 <= r.b0 + 1) {
+    r.b0 = imax32(r.b0, r.b1);
+    r.a1 = kNone; r.b1 = kNone - 1;
+  }
+  if (r.a2 != kNone && r.a2 <= r.b1 + 1) {
+    r.b1 = imax32(r.b1, r.b2);
+    r.a2 = kNone; r.b2 = kNone - 1;
+  }
+}
+
+// The visible keys of the decoding query (distance-0 key c = N_k - 1): the
+// union of the sink, long-range and near windows of Sec. 2.1.
+__host__ __device__ inline Runs3 key_runs3(int32_t n_k, int32_t sink, int32_t near, int32_t lo, int32_t hi) {
+  const int32_t c = n_k - 1;
+  Runs3 r;
+  // near: delta in [0, near); sink: keys below sink; long: delta in [lo, hi)
+  r.a0 = near >= 1 ? imax32(0, c - near + 1) : kNone;
+  r.b0 = near >= 1 ? c : kNone - 1;
+  r.a1 = sink >= 1 ? 0 : kNone;
+  r.b1 = sink >= 1 ? imin32(sink - 1, c) : kNone - 1;
+  const bool has_long = hi > lo && c - lo >= 0;
+  r.a2 = has_long ? imax32(0, c - hi + 1) : kNone;
+  r.b2 = has_long ? c - lo : kNone - 1;
+  runs3_merge(r);
+  return r;
+}
+
+// Blocks of BK keys that hold a legal pair with some query q0 .. q1 (q1 < n_q):
+// fwd_block_ranges for any query range, in 32-bit scalars.
+template <int BK>
+__host__ __device__ inline Runs3 key_block_runs3(const Geo32& g, int32_t q0, int32_t q1) {
+  const int32_t c0 = q0 + g.off, c1 = q1 + g.off;  // keys at distance 0
+  Runs3 r;
+  r.a0 = g.w_near >= 1 ? imax32(0, c0 - g.w_near + 1) / BK : kNone;
+  r.b0 = g.w_near >= 1 ? c1 / BK : kNone - 1;
+  r.a1 = g.w_sink >= 1 ? 0 : kNone;
+  r.b1 = g.w_sink >= 1 ? imin32(g.w_sink - 1, c1) / BK : kNone - 1;
+  const bool has_long = g.hi > g.lo && c1 - g.lo >= 0;
+  r.a2 = has_long ? imax32(0, c0 - g.hi + 1) / BK : kNone;
+  r.b2 = has_long ? (c1 - g.lo) / BK : kNone - 1;
+  runs3_merge(r);
+  return r;
+}
+
+// Every pair of queries q0 .. q1 and keys k0 .. k1 lies inside the sequence and
+// is legal (tile_full for any query and key range, in 32-bit scalars; bounds
+// clamped to n_k).
+__host__ __device__ inline bool key_block_full(const Geo32& g, int32_t q0, int32_t q1, int32_t k0, int32_t k1) {
+  const int32_t c0 = q0 + g.off, c1 = q1 + g.off;
+  const bool in = (q1 < g.n_q) & (k1 < g.n_k) & (k1 <= c0);  // inside, and causal for every pair
+  // keys past the sink: every distance in [c0 - k1, c1 - max(k0, sink)] in one window
+  const int32_t a = c0 - k1, b = c1 - imax32(k0, g.w_sink);
+  const bool win = (b < g.w_near) | ((a >= g.lo) & (b < g.hi)) | ((g.lo == g.w_near) & (b < g.hi));
+  return in & ((k1 < g.w_sink) | win);
+}
+
 // Up to three inclusive ranges, merged (overlapping or adjacent ranges join).
 struct Ranges {
   int32_t n;

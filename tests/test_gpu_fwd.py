@@ -72,6 +72,22 @@ def test_fwd_odd_shapes(case):
     _full_check(w, key=inputs.key_of("fwd", name), tile_q=tq, tile_k=tk)
 
 
+@pytest.mark.parametrize("case", [
+    # name, batch, n_q, n_k, h_q, h_k, d, sink, near, tile: the float32 kernel's
+    # 16-row tiles and 16-key chunks at their edges, both wave counts (the last two
+    # have more than 256 row tiles), rows without keys, one key, every key
+    ("one", 1, 1, 1, 1, 1, 64, 0, 1, 32), ("edge16", 1, 16, 16, 2, 1, 128, 1, 3, 32),
+    ("edge17", 2, 17, 49, 4, 1, 64, 2, 16, 64), ("tail", 1, 130, 131, 3, 3, 128, 0, 33, 128),
+    ("no_near", 1, 100, 100, 2, 2, 64, 0, 0, 32), ("dense", 1, 257, 300, 2, 1, 128, 0, 300, 64),
+    ("grid_256", 1, 1024, 1024, 4, 2, 64, 16, 64, 32), ("grid_257", 1, 1025, 1025, 4, 2, 64, 16, 64, 32),
+    ("many_tiles", 2, 700, 900, 8, 2, 128, 5, 100, 64), ("rows32", 1, 2100, 2100, 32, 4, 128, 5, 100, 64)], ids=lambda c: c[0])
+def test_fwd_fp32_tiles(case):
+    name, bsz, n_q, n_k, h_q, h_k, d, ws, wn, tile = case
+    w = inputs.custom("fwd32_" + name, batch=bsz, n_q=n_q, n_k=n_k, h_q=h_q, h_k=h_k, head_dim=d, w_sink=ws,
+                      w_near=wn, tile=tile, dtype="fp32")
+    _full_check(w, key=inputs.key_of("fwd32", name))
+
+
 def test_fwd_deterministic():
     dev = need_gpu()
     w = inputs.custom("fwd_det", batch=1, n_q=2000, n_k=2000, h_q=8, h_k=2, head_dim=128, w_sink=16, w_near=256,

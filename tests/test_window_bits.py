@@ -26,3 +26,17 @@ def test_bit_masks_match_pair_rule(tmp_path):
     out = subprocess.run([exe], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout + out.stderr
     assert "mismatches 0" in out.stdout
+
+
+def test_kernel_block_lists_match_pair_rule(tmp_path):
+    """The block lists that kernels build for tiles of their own (query rows and
+    key blocks other than the schedule's) against the per-pair rule."""
+    if not os.path.exists(HIPCC) and shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / "block_runs_check")
+    src = os.path.join(ROOT, "tests", "probes", "block_runs_check.cpp")
+    subprocess.run([HIPCC, "-x", "hip", "--offload-arch=gfx950", "-O1", "-I", os.path.join(ROOT, "include"), src,
+                    "-o", exe], check=True, capture_output=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "mismatches 0" in out.stdout
