@@ -686,12 +686,17 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
     } else {
       // a column without an offset at the start (m = 0) keeps its sum only if
       // that sum is comfortably normal (otherwise it met no legal key, or its
-      // P underflowed); an overflow shows in the sum
+      // P underflowed); an overflow shows in the sum.  The line lies below
+      // 2^-kHead, the sum that a move of the offset leaves: with it above (2^-60)
+      // every such row whose offset moved was run again, which doubled the
+      // forward of short ragged batches (10 sequences of up to 6000 tokens, d =
+      // 64: 126 + 118 us, now 126 + 4).  Terms lost below 2^-126 weigh at most
+      // 2^-56 of the sum each.
 #pragma unroll
       for (int nq = 0; nq < NQT; ++nq) {
         const float l = lacc[nq][0];
         hot |= !(l <= 0x1p64f);
-        far |= m_fix[nq] == -INFINITY && q_first + nq * 32 + l32 < n_q && !(l >= 0x1p-60f);
+        far |= m_fix[nq] == -INFINITY && q_first + nq * 32 + l32 < n_q && !(l >= 0x1p-70f);
       }
     }
     if (__ballot(hot) != 0) {

@@ -131,3 +131,31 @@ def test_fwd_wide_score_range(lift, lse_min, d, tile):
     assert l_r.max() > lse_min  # the score range of the case
     compare("O", to_host(o), o_r)
     compare("LSE", to_host(lse), l_r)
+
+
+@pytest.mark.parametrize("level", [-62.0, -67.0, -73.0, 40.0])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fwd_rows_without_a_starting_offset(level, d):
+    """A near window of 20 keys: most rows meet no legal key among the first 32
+    of their first block, so the untracked launch starts them at offset 0.  Their
+    scores lie near `level` (base 2), on both sides of the sum below which such
+    rows go to the tracked launch (2^-70) and, at 40, high enough that the offset
+    moves at once."""
+    dev = need_gpu()
+    import paper_2609_32704_amd as cowa
+    n, h_q, h_k = 400, 4, 1
+    rng = np.random.default_rng(5)
+    a = (abs(level) * np.log(2.0) * d ** 0.5 / d) ** 0.5  # d a^2 / sqrt(d) = |level| ln 2
+    qf = (np.full((1, h_q, n, d), a) + 0.02 * rng.standard_normal((1, h_q, n, d))).astype(np.float32)
+    kf = (np.sign(level) * np.full((1, h_k, n, d), a) + 0.02 * rng.standard_normal((1, h_k, n, d))).astype(np.float32)
+    vf = rng.standard_normal((1, h_k, n, d)).astype(np.float32)
+    bits = [inputs.f32_to_bf16_bits(x) for x in (qf, kf, vf)]
+    vals = [inputs.bf16_bits_to_f64(b) for b in bits]
+    q, k, v = (to_dev(b, dev) for b in bits)
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((1, h_q, n), float("nan"), dtype=torch.float32, device=dev)
+    cowa.fwd(q, k, v, 0, 20, 128, 128, d ** -0.5, out=o, lse=lse)
+    torch.cuda.synchronize()
+    o_r, l_r = ref.forward(vals[0], vals[1], vals[2], 0, 20, d ** -0.5)
+    compare("O", to_host(o), o_r)
+    compare("LSE", to_host(lse), l_r)
