@@ -1,11 +1,16 @@
 // CoWA forward in bfloat16 on the CDNA4 matrix cores (Alg. 1).
 //
-// Work decomposition.  One workgroup per (QO block i, group of HPW QO heads
-// that share one KV head, sequence b): every QO head of a GQA group has the
-// same block set J_{h_k}(i), so the heads of a workgroup share each K/V block
-// staged in LDS.  Each 64-lane wave owns 64 query rows of one head (up to 256
-// rows, four waves, per workgroup).  Workgroups are grouped per XCD so that
-// rows sharing K/V blocks run together on one L2 (cluster_item).
+// Work decomposition.  One workgroup of four waves per (row tile, group of hpw
+// QO heads that share one KV head, sequence b): every QO head of a GQA group sees
+// the same keys, so the heads of a workgroup share each K/V block staged in
+// LDS.  Each 64-lane wave owns 32 or 64 query rows of one head (see launch_d),
+// so a row tile holds R = 4 x 32 (or 64) / hpw rows: the row tiles and the key
+// blocks are the kernel's own, whatever tiles the schedule has, and it computes
+// the tile's block list itself from the windows (three merged ranges) instead of
+// reading the schedule's.  Every group size gets four waves: with one or two
+// waves for groups that 256 / tile_q does not divide, multi-head attention left
+// half or three quarters of the SIMDs idle.  Workgroups are grouped per XCD so
+// that rows sharing K/V blocks run together on one L2 (cluster_item).
 //
 // Per KV block j of J_{h_k}(i), full blocks first, then partial ones:
 //   * K_j and V_j are copied global -> LDS with direct 16-byte buffer loads,
@@ -78,6 +83,7 @@ __device__ inline void mfma_settle(f32x16& a, f32x16& b) {
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(a), "+v"(b));
 }
 __device__ inline void mfma_settle(f32x16 (&r)[2]) { mfma_settle(r[0], r[1]); }
+__device__ inline void mfma_settle(f32x16 (&r)[1]) { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(r[0])); }
 
 // max(a, b, c) in one instruction (fmaxf would first quiet each operand that
 // the compiler cannot prove canonical: the products above are opaque to it)
@@ -87,79 +93,147 @@ __device__ inline float max3(float a, float b, float c) {
   return d;
 }
 
-template <int D, int BQ, int BK>
+// waves per SIMD that the registers are cut for
+constexpr int fwd_occupancy(int nqt) { return nqt == 1 ? 2 : 1; }
+
+// NQT: 32-query tiles per wave (columns of S^T); BK: keys per block
+template <int D, int NQT_, int BK>
 struct FwdCfg {
-  static constexpr int NQW = 64;          // query rows per wave
-  static constexpr int NWF = 256 / NQW;   // waves of a full workgroup (256 query rows)
-  static constexpr int NQT = NQW / 32;    // 32-query tiles per wave (columns of S^T)
+  static constexpr int NW = 4;            // waves per workgroup
+  static constexpr int NQT = NQT_;
+  static constexpr int NQW = 32 * NQT;    // query rows per wave
   static constexpr int KS = D / 16;       // k-steps over d of S^T = K Q^T
   static constexpr int MD = D / 32;       // 32-row d tiles of O^T
   static constexpr int NCH = BK / 32;     // 32-key chunks per block (2 or 4)
   static constexpr int NG = KS + 2 * MD;  // product groups per chunk (NQT products each)
-  static constexpr int WPH = BQ / NQW;    // waves per QO head
   using T = SwzTile<D, BK>;
-  static constexpr int MAIN_BYTES = 4 * T::BYTES;  // K and V of two blocks; then the row's entry lists
+  static constexpr int MAIN_BYTES = 4 * T::BYTES;  // K and V of two blocks; then the row's entry list
   static constexpr int LDS_MAX = 160 * 1024;
-  static constexpr int OUT_PITCH = 2 * D + 16;               // staged output rows (bytes)
-  static constexpr int OUT_BYTES = NWF * NQW * OUT_PITCH;    // reuses the K/V buffers and lists at the end
-  static int lds_bytes(int n_kt) {                           // + a vote word
-    return MAIN_BYTES + 4 * n_kt + 16 > OUT_BYTES ? MAIN_BYTES + 4 * n_kt + 16 : OUT_BYTES;
+  static constexpr int OUT_PITCH = 2 * D + 16;             // staged output rows (bytes)
+  static constexpr int OUT_BYTES = NW * NQW * OUT_PITCH;   // reuses the K/V buffers and list at the end
+  static int lds_bytes(int n_kb) {                         // n_kb: list capacity; + a vote word
+    return MAIN_BYTES + 4 * n_kb + 16 > OUT_BYTES ? MAIN_BYTES + 4 * n_kb + 16 : OUT_BYTES;
   }
-  static int max_kblocks() { return (LDS_MAX - MAIN_BYTES - 16) / 4; }
+  static constexpr int max_kblocks() { return (LDS_MAX - MAIN_BYTES - 16) / 4; }
   static_assert(KS == 2 * MD, "S and O groups alternate one to one");
   static_assert(NCH == 2 || NCH == 4, "64- or 128-key blocks");
 };
 
-// FULL: launched with NWF waves (the fast copy path; a compile-time choice
-// keeps the block step free of branches)
-template <int D, int BQ, int BK, bool FULL, bool TRACK>
-__global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView sv, int hpw,
-                                                       const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                                                       const __bf16* __restrict__ v, __bf16* __restrict__ o,
-                                                       float* __restrict__ lse) {
-  using C = FwdCfg<D, BQ, BK>;
+// rt: the launch's rows; R = rows per (workgroup, head)
+template <int D, int NQT, int BK, bool TRACK>
+__global__ void __launch_bounds__(256, fwd_occupancy(NQT))
+    fwd_bf16_kernel(cowa_params p, SchedView sv, RowTiles rt, int cap, const __bf16* __restrict__ q,
+                    const __bf16* __restrict__ k, const __bf16* __restrict__ v, __bf16* __restrict__ o,
+                    float* __restrict__ lse) {
+  using C = FwdCfg<D, NQT, BK>;
   using T = typename C::T;
-  constexpr int NQT = C::NQT, KS = C::KS, MD = C::MD, NCH = C::NCH, NG = C::NG;
+  constexpr int KS = C::KS, MD = C::MD, NCH = C::NCH, NG = C::NG;
   extern __shared__ __align__(1024) unsigned char smem[];
 
-  const int nw = blockDim.x >> 6;
+  const int hpw = rt.hpw, wph = C::NW / hpw;  // heads per workgroup, waves per head
   const int G = p.h_q / p.h_k;
-  // rows of 16 QO blocks x the head groups of one KV head share an XCD's L2;
-  // latest (longest) QO blocks first
-  const WorkItem wi = cluster_item(blockIdx.x, sv.n_qt, G / hpw, grid_units(p, sv),
-                                   cluster_rows(sv.n_qt, grid_units(p, sv), 16), true);
-  int hk;
-  const SeqCtx sc = seq_ctx(p, sv, wi.row, wi.unit, true, hk);
-  const int i = sc.tile;
-  const int hgi = hk * (G / hpw) + wi.group;
-  const int h0 = hgi * hpw;  // first QO head of this workgroup (all in KV group hk)
+  // rows of 16 row tiles x the head groups of one KV head share an XCD's L2;
+  // latest (longest) rows first
+  const WorkItem wi = cluster_item(blockIdx.x, rt.n_rows, G / hpw, grid_units(p, sv),
+                                   cluster_rows(rt.n_rows, grid_units(p, sv), 16), true);
+  int hk, q0;
+  const SeqCtx sc = row_ctx(p, sv, rt, wi.row, wi.unit, hk, q0);
+  const int n_q = sc.n_q, n_k = sc.n_k;
+  if (q0 >= n_q) return;
+  const int h0 = (hk * (G / hpw) + wi.group) * hpw;  // first QO head of this workgroup (all in KV group hk)
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31, hh = lane >> 5;  // MFMA column and half
-  const int hq = h0 + wave / C::WPH;
-  const int q_first = i * BQ + (wave % C::WPH) * C::NQW;
+  const int hq = h0 + wave / wph;
+  const int q_first = q0 + (wave % wph) * C::NQW;
   const Geo32 g = sc.g;
-  const int n_q = sc.n_q, n_k = sc.n_k;
   const __bf16* kbase = k + (sc.k0 + (int64_t)hk * sc.kh) * D;
   const __bf16* vbase = v + (sc.k0 + (int64_t)hk * sc.kh) * D;
   const uint32_t smem_base = lds_addr(smem);
-
-  // Q^T fragments (B operands): query column 32 nq + l32, d = 16 ks + 8 hh + 0..7;
-  // loaded first, so that their latency overlaps that of the entry lists
   const int64_t row_base = sc.q0 + (int64_t)hq * sc.qh;
   if constexpr (TRACK) {
     // only the workgroups with a row that the untracked launch left to this
     // one (LSE = NaN) run; the rest end here, uniformly
-    int* flag = reinterpret_cast<int*>(smem + C::MAIN_BYTES + 4 * sv.max_kt);
+    int* flag = reinterpret_cast<int*>(smem + C::MAIN_BYTES + 4 * cap);
     if (tid == 0) *flag = 0;
     __syncthreads();
     const int qr = q_first + lane;
-    if (__ballot(qr < n_q && __builtin_isnan(lse[row_base + qr])) != 0 && lane == 0) *flag = 1;
+    if (__ballot(lane < C::NQW && qr < n_q && __builtin_isnan(lse[row_base + qr])) != 0 && lane == 0) *flag = 1;
     __syncthreads();
     const bool mine = *flag != 0;
     __syncthreads();
     if (!mine) return;
   }
+
+  // The row tile's block list, in LDS: full blocks from the front, partial
+  // ones from the back, both by descending key (at most three merged ranges,
+  // computed rather than read: the schedule's tiles need not be this kernel's)
+  const int q_last = (q0 + rt.R < n_q ? q0 + rt.R : n_q) - 1;
+  const Runs3 runs = key_block_runs3<BK>(g, q0, q_last);
+  const int n0 = runs.b0 - runs.a0 + 1, n1 = n0 + runs.b1 - runs.a1 + 1, n_ent = n1 + runs.b2 - runs.a2 + 1;
+  uint32_t* list = reinterpret_cast<uint32_t*>(smem + C::MAIN_BYTES);
+  int n_full = 0;
+  for (int c0 = 0; c0 < n_ent; c0 += 64) {
+    const int t = n_ent - 1 - (c0 + lane);
+    const bool in = t >= 0;
+    const int j = t < n0 ? runs.a0 + t : t < n1 ? runs.a1 + (t - n0) : runs.a2 + (t - n1);
+    const bool is_full = key_block_full(g, q0, q0 + rt.R - 1, j * BK, j * BK + BK - 1);
+    const uint64_t full = __ballot(in && is_full);
+    const uint64_t part = __ballot(in && !is_full);
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    if (wave == 0 && in) list[is_full ? n_full + __popcll(full & below) : cap - 1 - (c0 - n_full + __popcll(part & below))] = j;
+    n_full += __popcll(full);
+  }
+  auto entry_at = [&](int t) -> int {
+    const int tt = t < n_ent ? t : n_ent - 1;
+    const int idx = tt < n_full ? tt : cap - 1 - (tt - n_full);
+    return __builtin_amdgcn_readfirstlane(list[idx]);
+  };
+  // zero the K/V buffers once when the row reaches the last KV block and that
+  // is partial: key rows past the end of the sequence are not copied and must
+  // hold finite values
+  if (n_k % BK != 0 && (q_last + g.off) / BK == n_k / BK)
+    for (int x = tid; x < C::MAIN_BYTES / 16; x += 256) reinterpret_cast<u32x4*>(smem)[x] = u32x4{0u, 0u, 0u, 0u};
+
+  // Global -> LDS copies of K and V blocks: each lane copies the same 16-byte
+  // column of its row in every 1 KB piece it takes, so its byte offsets within
+  // a block are fixed, and the block position goes into the (scalar) buffer
+  // resource, whose size bounds the reads to the sequence.
+  constexpr int RPL = 1024 / (D * 2);    // rows per 1 KB piece
+  constexpr int PPW = T::LOADS / C::NW;  // pieces per wave
+  static_assert(T::LOADS % C::NW == 0 && (C::NW * RPL) % 16 == 0, "piece layout");
+  uint32_t dma_off[PPW];
+  {
+    const int row0 = wave * RPL + lane / T::CH;
+    const int col = (lane % T::CH) ^ swz<T::CH>(row0);
+#pragma unroll
+    for (int n = 0; n < PPW; ++n) dma_off[n] = (uint32_t)(((n * C::NW * RPL + row0) * D + col * 8) * 2);
+  }
+  auto kbuf_off = [](int t) { return (t & 1) * 2 * T::BYTES; };
+  auto vbuf_off = [](int t) { return (t & 1) * 2 * T::BYTES + T::BYTES; };
+  // piece n of a block copy, issued on its own
+  auto stage_piece = [&](const __bf16* base, int kf, int buf_off, int n) {
+    const i32x4 rs = buffer_rsrc(base + (int64_t)kf * D, (uint32_t)(n_k - kf) * D * 2);
+    dma16_buf(dma_off[n], rs, smem_base + buf_off + wave * 1024 + n * C::NW * 1024);
+  };
+  auto stage = [&](const __bf16* base, int t, int buf_off) {
+    const int kf = entry_at(t) * BK;
+#pragma unroll
+    for (int n = 0; n < PPW; ++n) stage_piece(base, kf, buf_off, n);
+  };
+  __syncthreads();  // the list and the zeroed buffers are in LDS
+  // The first block's copies go out before the Q^T loads, so that the row
+  // start waits for memory once.  (With 128-key blocks V of block 0 is needed
+  // from its third chunk; with 64-key blocks it is copied by the first step.)
+  auto stage_first = [&]() {
+    if (n_ent > 0) {
+      stage(kbase, 0, kbuf_off(0));
+      if (NCH == 4) stage(vbase, 0, vbuf_off(0));
+    }
+  };
+  stage_first();
+
+  // Q^T fragments (B operands): query column 32 nq + l32, d = 16 ks + 8 hh + 0..7
   bf16x8 qf[NQT][KS];
 #pragma unroll
   for (int nq = 0; nq < NQT; ++nq) {
@@ -181,72 +255,6 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
   for (int nq = 0; nq < NQT; ++nq)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qf[nq][ks]));
-  // zero the K/V buffers once when the last KV block is partial: key rows past
-  // the end of the sequence are not copied and must hold finite values
-  if (n_k % BK != 0)
-    for (int x = tid; x < C::MAIN_BYTES / 16; x += blockDim.x) reinterpret_cast<u32x4*>(smem)[x] = u32x4{0u, 0u, 0u, 0u};
-
-  // the row's entries, split into full (from the front) and partial (from the back) lists
-  const int r = sc.sched;
-  const int e0 = sv.fwd_row_ptr[r], e1 = sv.fwd_row_ptr[r + 1];
-  const int n_ent = e1 - e0;
-  const int cap = sv.max_kt;
-  uint32_t* list = reinterpret_cast<uint32_t*>(smem + C::MAIN_BYTES);
-  int n_full = 0;
-  for (int c0 = 0; c0 < n_ent; c0 += 64) {
-    const bool in = c0 + lane < n_ent;
-    const uint32_t ent = in ? sv.fwd_ent[e0 + c0 + lane] : 0u;
-    const uint64_t full = __ballot(in && !(ent & 1u));
-    const uint64_t part = __ballot(in && (ent & 1u));
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (wave == 0 && in) {
-      if (ent & 1u)
-        list[cap - 1 - (c0 - n_full + __popcll(part & below))] = ent;
-      else
-        list[n_full + __popcll(full & below)] = ent;
-    }
-    n_full += __popcll(full);
-  }
-  auto entry_at = [&](int t) -> uint32_t {
-    const int tt = t < n_ent ? t : n_ent - 1;
-    const int idx = tt < n_full ? tt : cap - 1 - (tt - n_full);
-    return __builtin_amdgcn_readfirstlane(list[idx]);
-  };
-
-  // Global -> LDS copies of K and V blocks.  With four waves each lane copies
-  // the same 16-byte column of its row in every 1 KB piece it takes: its byte
-  // offsets within a block are fixed, and the block position goes into the
-  // (scalar) buffer resource, whose size bounds the reads to the sequence.
-  constexpr int RPL = 1024 / (D * 2);  // rows per 1 KB piece
-  constexpr int NWF = C::NWF;
-  constexpr int PPW = T::LOADS / NWF;  // pieces per wave
-  uint32_t dma_off[PPW];
-  {
-    const int row0 = wave * RPL + lane / T::CH;
-    const int col = (lane % T::CH) ^ swz<T::CH>(row0);
-#pragma unroll
-    for (int n = 0; n < PPW; ++n) dma_off[n] = (uint32_t)(((n * NWF * RPL + row0) * D + col * 8) * 2);
-  }
-  auto kbuf_off = [](int t) { return (t & 1) * 2 * T::BYTES; };
-  auto vbuf_off = [](int t) { return (t & 1) * 2 * T::BYTES + T::BYTES; };
-  auto stage = [&](const __bf16* base, int t, int buf_off) {
-    const int kf = (int)(entry_at(t) >> 1) * BK;
-    if constexpr (FULL) {
-      const i32x4 rs = buffer_rsrc(base + (int64_t)kf * D, (uint32_t)(n_k - kf) * D * 2);
-      const uint32_t lds0 = smem_base + buf_off + wave * 1024;
-#pragma unroll
-      for (int n = 0; n < PPW; ++n) dma16_buf(dma_off[n], rs, lds0 + n * NWF * 1024);
-    } else {
-      load_tile_asm_nw<D, BK>(base, kf, n_k, smem_base + buf_off, wave, nw, lane);
-    }
-  };
-  // piece n of a block copy (full waves only), issued on its own
-  auto stage_piece = [&](const __bf16* base, int kf, int buf_off, int n) {
-    const i32x4 rs = buffer_rsrc(base + (int64_t)kf * D, (uint32_t)(n_k - kf) * D * 2);
-    dma16_buf(dma_off[n], rs, smem_base + buf_off + wave * 1024 + n * NWF * 1024);
-  };
-  __syncthreads();  // the lists and the zeroed buffers are in LDS
-
   // LDS fragment offsets for chunk 0 of a tile (the swizzle depends on row % 16,
   // so chunks 32 rows further and k-steps 16 rows further add plain row bytes)
   //  K (A operand of S^T): row l32, columns 16 ks + 8 hh + 0..7;
@@ -308,7 +316,7 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
                                    (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f}
                           : bf16x8{};
 
-  float pv[32];  // exponentials in flight between the two halves of an element step
+  float pv[16 * NQT];  // exponentials in flight between the two halves of an element step
   uint32_t lmask[NQT];  // legal keys of the chunk being masked, per query tile
   // element step e of a chunk's softmax (query tile e / 16, slot e % 16), first half
   auto soft_a = [&](auto ec, auto rpc, bool masked, int key0) __attribute__((always_inline)) {
@@ -466,14 +474,14 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
   auto step = [&](int t, auto firstc, auto mprevc, auto mcurc) __attribute__((always_inline)) {
     constexpr bool FIRST = decltype(firstc)::value, MPREV = decltype(mprevc)::value;
     constexpr bool MCUR = decltype(mcurc)::value;
-    const int k_first = (int)(entry_at(t) >> 1) * BK;
+    const int k_first = entry_at(t) * BK;
     // K of block t + 1 goes into the K buffer of block t - 1, which is free
-    // (the last block repeats itself).  With 128-key blocks and full waves the
+    // (the last block repeats itself).  With 128-key blocks the
     // copies of K (from the block start) and of V (from the mid-block barrier)
     // go out one 1 KB piece per product group: a burst of them would hold the
     // wave at the vector memory queue.
-    constexpr bool SPREAD = FULL && NCH == 4;
-    [[maybe_unused]] const int kf_next = (int)(entry_at(t + 1) >> 1) * BK;
+    constexpr bool SPREAD = NCH == 4;
+    [[maybe_unused]] const int kf_next = entry_at(t + 1) * BK;
     if constexpr (!SPREAD) stage(kbase, t + 1, kbuf_off(t + 1));
     if constexpr (NCH == 2) stage(vbase, t, vbuf_off(t));  // V buffer of block t - 2: free
     const unsigned char* Kt = smem + kbuf_off(t);
@@ -508,12 +516,8 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
         // block t - 1 was issued: V of block t is in (its copies were issued
         // before this block's K copies), and once every wave's reads of V of
         // block t - 1 are done, the copy of block t + 1 may overwrite it
-        if constexpr (FULL)
-          __builtin_amdgcn_s_waitcnt(vmcnt_only(PPW));
-        else
-          __builtin_amdgcn_s_waitcnt(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(PPW));
         __syncthreads();
-        if constexpr (!SPREAD) stage(vbase, t + 1, vbuf_off(t + 1));
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (SPREAD && GG < PPW) stage_piece(kbase, kf_next, kbuf_off(t + 1), GG);
@@ -575,7 +579,7 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
     k_prev = k_first;
     // the next block's K has landed (with 128-key blocks the next V may still
     // be in flight)
-    if constexpr (NCH == 4 && FULL)
+    if constexpr (NCH == 4)
       __builtin_amdgcn_s_waitcnt(vmcnt_only(PPW));
     else
       __builtin_amdgcn_s_waitcnt(0);
@@ -587,7 +591,7 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
     using R1 = std::integral_constant<int, 1>;
     static_for<16 * NQT>([&](auto ec) { soft_a(ec, R1{}, true, k_prev + (NCH - 1) * 32 + 4 * hh); });
     static_for<16 * NQT>([&](auto ec) { soft_b(ec, R1{}, R1{}); });
-    if constexpr (NCH == 4 && FULL) __builtin_amdgcn_s_waitcnt(0);  // (the repeated V copy of the mid-block)
+    if constexpr (NCH == 4) __builtin_amdgcn_s_waitcnt(0);  // (the repeated V copy of the mid-block)
     const unsigned char* Vt = smem + vbuf_off(t);
     static_for<2 * 2 * MD>([&](auto gc) {
       constexpr int GG = decltype(gc)::value, jj = GG / (2 * MD), kk = (GG / MD) % 2, md = GG % MD;
@@ -633,13 +637,10 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
 #pragma unroll
       for (int md = 0; md < MD; ++md) oacc[md][nq] = f32x16{};
     }
-    if (n_ent > 0) {
-      stage(kbase, 0, kbuf_off(0));
-      if (NCH == 4) stage(vbase, 0, vbuf_off(0));  // (needed from the block's third chunk)
-    }
-    // K of the first block has landed; with 128-key blocks and full waves its V
+    if (pass > 0) stage_first();
+    // K of the first block has landed; with 128-key blocks its V
     // may still be in flight (the first block's mid-block wait covers it)
-    if constexpr (NCH == 4 && FULL)
+    if constexpr (NCH == 4)
       __builtin_amdgcn_s_waitcnt(vmcnt_only(PPW));
     else
       __builtin_amdgcn_s_waitcnt(0);
@@ -647,7 +648,7 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
     if (pass == 0 && n_ent > 0) {
       // offsets from the first 32 keys of the row's first block (in processing
       // order: a full block when the row has one)
-      const int kb = (int)(entry_at(0) >> 1) * BK + 4 * hh;
+      const int kb = entry_at(0) * BK + 4 * hh;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8 a = ld_row8(smem + offk[ks]);
@@ -756,46 +757,71 @@ __global__ void __launch_bounds__(256) fwd_bf16_kernel(cowa_params p, SchedView 
   }
 }
 
-template <int D, int BQ, int BK, bool FULL>
-hipError_t launch_waves(const cowa_params& p, const SchedView& sv, int hpw, int n_hgroups, int waves, const void* q,
-                        const void* k, const void* v, void* o, float* lse, hipStream_t stream) {
-  using C = FwdCfg<D, BQ, BK>;
-  // the untracked launch, then the tracked one for the rows it flagged
-  auto kern0 = fwd_bf16_kernel<D, BQ, BK, FULL, false>;
-  auto kern1 = fwd_bf16_kernel<D, BQ, BK, FULL, true>;
-  for (const void* kp : {reinterpret_cast<const void*>(kern0), reinterpret_cast<const void*>(kern1)}) {
-    const hipError_t err = allow_lds(kp, C::LDS_MAX);
-    if (err != hipSuccess) return err;
-  }
-  const unsigned blocks = (unsigned)sv.n_qt * n_hgroups * (sv.ragged ? 1 : p.batch);
-  hipLaunchKernelGGL(kern0, dim3(blocks), dim3(64 * waves), C::lds_bytes(sv.max_kt), stream, p, sv, hpw,
-                     static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
-                     static_cast<__bf16*>(o), lse);
-  hipLaunchKernelGGL(kern1, dim3(blocks), dim3(64 * waves), C::lds_bytes(sv.max_kt), stream, p, sv, hpw,
+template <int D, int NQT, int BK, bool TRACK>
+hipError_t launch_one(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v, void* o,
+                      float* lse, hipStream_t stream) {
+  using C = FwdCfg<D, NQT, BK>;
+  auto kern = fwd_bf16_kernel<D, NQT, BK, TRACK>;
+  const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
+  if (err != hipSuccess) return err;
+  // as many heads of the group per workgroup as it has, up to one per wave: the
+  // fewest query rows per head, and so the fewest masked or unneeded pairs
+  const int G = p.h_q / p.h_k, hpw = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+  const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw);
+  const int cap = list_capacity(p, sv, rt.R, BK);
+  if (cap > C::max_kblocks()) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)rt.n_rows * (p.h_q / hpw) * (sv.ragged ? 1 : p.batch);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), C::lds_bytes(cap), stream, p, sv, rt, cap,
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<__bf16*>(o), lse);
   return hipGetLastError();
 }
 
-template <int D, int BQ, int BK>
-hipError_t launch_cfg(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                      void* o, float* lse, hipStream_t stream) {
-  using C = FwdCfg<D, BQ, BK>;
-  if (sv.max_kt > C::max_kblocks()) return hipErrorInvalidValue;
-  const int G = p.h_q / p.h_k;
-  int hpw = 256 / BQ;  // QO heads per workgroup: up to 256 query rows
-  while (hpw > 1 && G % hpw != 0) hpw >>= 1;
-  const int n_hgroups = p.h_q / hpw;
-  const int waves = hpw * C::WPH;
-  if (waves == C::NWF) return launch_waves<D, BQ, BK, true>(p, sv, hpw, n_hgroups, waves, q, k, v, o, lse, stream);
-  return launch_waves<D, BQ, BK, false>(p, sv, hpw, n_hgroups, waves, q, k, v, o, lse, stream);
+// Which shape runs the untracked launch.  32 rows per wave leave room for two
+// waves per SIMD (at d = 128 with 64-key blocks), which hide each other's row
+// starts, copies and exponentials, and make twice as many workgroups; 64 rows
+// per wave read each K/V fragment from LDS once for two products, which wins
+// only where rows are long and many.  Measured at d = 128 (us, 32 rows and
+// 64-key blocks / 64 rows and 128-key blocks), V the visible keys of a row, W
+// the workgroups of 256 rows:
+//   1000 tokens, 32/8 heads (V 250, W 125)               23 /   37
+//   4096, 32/8 (V 1500, W 512)                           95 /  107
+//   2 x 4096, 8/8 heads (V 1000, W 256)                  55 /   68  (121 before: two waves)
+//   32768, 32/8 (V 5900, W 4096)                       2039 / 2088
+//   8192 dense (V up to 8192, W 1024)                   537 /  517
+//   2 x 32768, 32/8 (V 5900, W 8192)                   4005 / 3857
+//   131072, one KV head (V 20000, W 2048)              3091 / 2855
+// At d = 64 the exponentials weigh twice as much per product and 32 rows always
+// win (65536 tokens, 16/4 heads: 3172 / 3490); 128-key blocks from V = 1024 on
+// (3237 against 3472 us there; 27 against 25 at 2048 tokens, V 900).
+template <int D>
+hipError_t launch_d(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v, void* o,
+                    float* lse, hipStream_t stream) {
+  const int64_t V = visible_bound(p, sv);
+  const int64_t W = ((int64_t)p.h_q * p.n_q * (sv.ragged ? 1 : p.batch) + 255) / 256;
+  hipError_t err;
+  if constexpr (D == 128) {
+    if ((V >= 8192 && W >= 256) || (V >= 4096 && W >= 8192))
+      err = launch_one<128, 2, 128, false>(p, sv, q, k, v, o, lse, stream);
+    else
+      err = launch_one<128, 1, 64, false>(p, sv, q, k, v, o, lse, stream);
+    if (err == hipSuccess) err = launch_one<128, 2, 64, true>(p, sv, q, k, v, o, lse, stream);
+  } else {
+    if (V >= 1024)
+      err = launch_one<64, 1, 128, false>(p, sv, q, k, v, o, lse, stream);
+    else
+      err = launch_one<64, 1, 64, false>(p, sv, q, k, v, o, lse, stream);
+    if (err == hipSuccess) err = launch_one<64, 1, 128, true>(p, sv, q, k, v, o, lse, stream);
+  }
+  return err;
 }
 
 }  // namespace
 
+// Limits per schedule tile, as the entry point documents them.
 int fwd_bf16_max_kblocks(int d, int tk) {
-  if (d == 128) return tk == 128 ? FwdCfg<128, 128, 128>::max_kblocks() : FwdCfg<128, 128, 64>::max_kblocks();
-  return tk == 128 ? FwdCfg<64, 128, 128>::max_kblocks() : FwdCfg<64, 128, 64>::max_kblocks();
+  if (d == 128) return tk == 128 ? FwdCfg<128, 2, 128>::max_kblocks() : FwdCfg<128, 2, 64>::max_kblocks();
+  return tk == 128 ? FwdCfg<64, 1, 128>::max_kblocks() : FwdCfg<64, 1, 64>::max_kblocks();
 }
 
 bool fwd_bf16_supported(int d, int tq, int tk) {
@@ -804,18 +830,8 @@ bool fwd_bf16_supported(int d, int tq, int tk) {
 
 hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
                            void* o, float* lse, hipStream_t stream) {
-#define COWA_FWD_CASE(D_, BQ_, BK_) \
-  if (p.head_dim == D_ && p.tile_q == BQ_ && p.tile_k == BK_) return launch_cfg<D_, BQ_, BK_>(p, sv, q, k, v, o, lse, stream);
-  COWA_FWD_CASE(128, 128, 128)
-  COWA_FWD_CASE(128, 128, 64)
-  COWA_FWD_CASE(128, 64, 128)
-  COWA_FWD_CASE(128, 64, 64)
-  COWA_FWD_CASE(64, 128, 128)
-  COWA_FWD_CASE(64, 128, 64)
-  COWA_FWD_CASE(64, 64, 128)
-  COWA_FWD_CASE(64, 64, 64)
-#undef COWA_FWD_CASE
-  return hipErrorInvalidValue;
+  return p.head_dim == 128 ? launch_d<128>(p, sv, q, k, v, o, lse, stream)
+                           : launch_d<64>(p, sv, q, k, v, o, lse, stream);
 }
 
 }  // namespace cowa

@@ -88,6 +88,30 @@ def test_fwd_fp32_tiles(case):
     _full_check(w, key=inputs.key_of("fwd32", name))
 
 
+@pytest.mark.parametrize("h_q,h_k,n_q", [(16, 16, 4173), (32, 16, 2049), (16, 4, 4100)])
+def test_fwd_long_rows_by_heads_per_workgroup(h_q, h_k, n_q):
+    """Rows of more than 8192 visible keys in a grid large enough for the 64-row
+    waves, with one, two and four QO heads per workgroup (tiles of 256, 128 and 64
+    rows, a ragged last one), against the oracle on the first and last 200 rows."""
+    dev = need_gpu()
+    import paper_2609_32704_amd as cowa
+    n_k, d, win = 9001, 128, [(5, 8300, 100, 200)] * h_k
+    seq = {n: inputs.seed_sequence(inputs.key_of("long_rows", h_q, h_k), n) for n in ("q", "k", "v")}
+    qb, qv = inputs.normal_bf16((1, h_q, n_q, d), seq["q"])
+    kb, kv = inputs.normal_bf16((1, h_k, n_k, d), seq["k"])
+    vb, vv = inputs.normal_bf16((1, h_k, n_k, d), seq["v"])
+    q, k, v = (to_dev(b, dev) for b in (qb, kb, vb))
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((1, h_q, n_q), float("nan"), dtype=torch.float32, device=dev)
+    cowa.fwd(q, k, v, 0, 0, 64, 128, d ** -0.5, out=o, lse=lse, windows=win)
+    torch.cuda.synchronize()
+    assert not torch.isnan(o).any().item() and not torch.isnan(lse).any().item()
+    for rows, keys in ((slice(0, 200), n_k - n_q + 200), (slice(n_q - 200, n_q), n_k)):
+        o_r, l_r = ref.forward(qv[:, :, rows], kv[:, :, :keys], vv[:, :, :keys], 0, 0, d ** -0.5, windows=win)
+        compare("O", to_host(o[:, :, rows]), o_r)
+        compare("LSE", to_host(lse[:, :, rows]), l_r)
+
+
 def test_fwd_deterministic():
     dev = need_gpu()
     w = inputs.custom("fwd_det", batch=1, n_q=2000, n_k=2000, h_q=8, h_k=2, head_dim=128, w_sink=16, w_near=256,
