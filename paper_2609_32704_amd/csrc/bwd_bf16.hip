@@ -600,318 +600,11 @@ hipError_t launch_main(const cowa_params& p, const SchedView& sv, const void* q,
   return hipGetLastError();
 }
 
-// dQ pass: one workgroup per (QO block i, HPW QO heads of one KV group,
-// sequence b); each 64-lane wave owns 64 query rows of one head, and one wave
-// runs per SIMD.  Q^T and dO^T of the wave's rows stay in registers (as MFMA B
-// operands, pinned to AGPRs) for the whole row of KV blocks; K_j and V_j are
-// double buffered in LDS and shared by the heads.  Full blocks are taken first,
-// then partial ones (each kind a straight-line loop body).  Per chunk of 32 keys:
-//   phase A: S^T = K Q^T and dP^T = V dO^T for 16 keys (32 MFMAs),
-//   phase B: dS^T = P^T (dP^T - D) for those keys on the vector units while the
-//            matrix cores run half of dQ^T += K^T dS^T of the previous chunk,
-// twice per chunk;
-// the softmax scale is applied to dQ when it is written.
-template <int D, int BQ, int BK, int NQW_ = 64>
-struct DqCfg {
-  static constexpr int NQW = NQW_;          // query rows per wave
-  static constexpr int NTQ = NQW / 16;      // query tiles per wave
-  static constexpr int BKC = 32;            // keys per chunk (one k-step of dQ^T += K^T dS^T)
-  static constexpr int NCH = BK / BKC;      // chunks per block
-  static constexpr int KSD = D / 32;        // k-steps over d
-  static constexpr int MTD = D / 16;        // d tiles of dQ^T
-  static constexpr int WPH = BQ / NQW;      // waves per QO head
-  using T = SwzTile<D, BK>;
-  static constexpr int MAIN_BYTES = 4 * T::BYTES;  // K, V of two blocks; then the row's entry lists
-  static constexpr int LDS_MAX = 160 * 1024;
-  static int lds_bytes(int n_kt) { return MAIN_BYTES + 4 * n_kt; }
-  static int max_kblocks() { return (LDS_MAX - MAIN_BYTES) / 4; }
-};
-
-// W4: the workgroup has exactly four waves (then the next block's copies are
-// spread over the block's product groups).
-template <int D, int BQ, int BK, int NQW, bool W4>
-__global__ void __launch_bounds__(256 * 64 / NQW) bwd_dq_kernel(cowa_params p, SchedView sv, int hpw,
-                                                     const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                                                     const __bf16* __restrict__ v, const __bf16* __restrict__ d_o,
-                                                     const float* __restrict__ nl, const float* __restrict__ nd,
-                                                     __bf16* __restrict__ dq) {
-  using C = DqCfg<D, BQ, BK, NQW>;
-  using T = typename C::T;
-  constexpr int NTQ = C::NTQ, KSD = C::KSD, MTD = C::MTD;
-  extern __shared__ __align__(1024) unsigned char smem[];
-
-  const int nw = blockDim.x >> 6;
-  const int G = p.h_q / p.h_k;
-  // rows of 16 QO blocks x the head groups of one KV head share an XCD's L2;
-  // latest (longest) QO blocks first
-  const WorkItem wi = cluster_item(blockIdx.x, sv.n_qt, G / hpw, grid_units(p, sv),
-                                   cluster_rows(sv.n_qt, grid_units(p, sv), 16), true);
-  int hk;
-  const SeqCtx sc = seq_ctx(p, sv, wi.row, wi.unit, true, hk);
-  const int i = sc.tile;
-  const int hgi = hk * (G / hpw) + wi.group;
-  const int h0 = hgi * hpw;
-
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int h = h0 + wave / C::WPH;
-  const int q_first = i * BQ + (wave % C::WPH) * C::NQW;
-  const Geo32 g = sc.g;
-  const int n_q = sc.n_q, n_k = sc.n_k;
-
-  const __bf16* kbase = k + (sc.k0 + (int64_t)hk * sc.kh) * D;
-  const __bf16* vbase = v + (sc.k0 + (int64_t)hk * sc.kh) * D;
-  const uint32_t smem_base = lds_addr(smem);
-
-  // the row's entries, split into full (from the front) and partial (from the back) lists
-  const int r = sc.sched;
-  const int e0 = sv.fwd_row_ptr[r], e1 = sv.fwd_row_ptr[r + 1];
-  const int n_ent = e1 - e0;
-  const int cap = sv.max_kt;
-  uint32_t* list = reinterpret_cast<uint32_t*>(smem + C::MAIN_BYTES);
-  int n_full = 0;
-  for (int c0 = 0; c0 < n_ent; c0 += 64) {
-    const bool in = c0 + lane < n_ent;
-    const uint32_t ent = in ? sv.fwd_ent[e0 + c0 + lane] : 0u;
-    const uint64_t full = __ballot(in && !(ent & 1u));
-    const uint64_t part = __ballot(in && (ent & 1u));
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (wave == 0 && in) {
-      if (ent & 1u)
-        list[cap - 1 - (c0 - n_full + __popcll(part & below))] = ent;
-      else
-        list[n_full + __popcll(full & below)] = ent;
-    }
-    n_full += __popcll(full);
-  }
-  // list position of the t-th block in processing order (full ones, then partial ones)
-  auto entry_at = [&](int t) -> uint32_t {
-    const int tt = t < n_ent ? t : n_ent - 1;
-    const int idx = tt < n_full ? tt : cap - 1 - (tt - n_full);
-    return __builtin_amdgcn_readfirstlane(list[idx]);
-  };
-  auto stage = [&](uint32_t ent, int buf) {
-    const int kf = (int)(ent >> 1) * BK;
-    load_tile_asm_nw<D, BK>(kbase, kf, n_k, smem_base + buf * 2 * T::BYTES, wave, nw, lane);
-    load_tile_asm_nw<D, BK>(vbase, kf, n_k, smem_base + buf * 2 * T::BYTES + T::BYTES, wave, nw, lane);
-  };
-  __syncthreads();  // the lists are in LDS
-  if (n_ent > 0) stage(entry_at(0), 0);
-  // With four waves, the next block's K and V copies go out one 1 KB piece per
-  // product group (K piece n, then V piece n) instead of a burst that would
-  // hold the wave at the vector memory queue; past the last block the last
-  // block is copied again (into the free buffer, never read).
-  constexpr int RPL = 1024 / (D * 2), PPW4 = T::LOADS / 4;
-  static_assert(!W4 || (T::LOADS % 4 == 0 && (4 * RPL) % 16 == 0), "piece layout");
-  const int row0 = wave * RPL + lane / T::CH;
-  const int col0 = ((lane % T::CH) ^ swz<T::CH>(row0)) << 3;
-  auto stage_piece = [&](const __bf16* base, int kf, int buf, int n, int isv) {
-    int r = kf + n * 4 * RPL + row0;
-    r = r < n_k ? r : n_k - 1;
-    dma16(base + (int64_t)r * D + col0,
-          __builtin_amdgcn_readfirstlane(smem_base + buf * 2 * T::BYTES + isv * T::BYTES + (n * 4 + wave) * 1024));
-  };
-
-  // Q^T and dO^T fragments (B operands): query column nt*16 + lr, d = ks*32 + 8*lg + 0..7;
-  // per-query LSE (base 2; a row without keys or past n_q gets +inf, so P = 0) and D
-  const int64_t row_base = sc.q0 + (int64_t)h * sc.qh;
-  bf16x8 qf[NTQ][KSD], gf[NTQ][KSD];
-  float l2[NTQ], dd[NTQ];
-#pragma unroll
-  for (int nt = 0; nt < NTQ; ++nt) {
-    const int qp = q_first + nt * 16 + lr;
-    const bool ok = qp < n_q;
-    const int64_t row = row_base + (ok ? qp : 0);
-#pragma unroll
-    for (int ks = 0; ks < KSD; ++ks) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(q + row * D + ks * 32 + 8 * lg);
-      const bf16x8 c2 = *reinterpret_cast<const bf16x8*>(d_o + row * D + ks * 32 + 8 * lg);
-      qf[nt][ks] = ok ? a : bf16x8{};
-      gf[nt][ks] = ok ? c2 : bf16x8{};
-    }
-    // nl = -LSE log2(e); a row without keys (LSE = -inf) or past n_q gets +inf, so P = 0
-    const float nlv = ok ? nl[row] : INFINITY;
-    l2[nt] = nlv == INFINITY ? INFINITY : -nlv;
-    dd[nt] = ok ? -nd[row] : 0.f;
-  }
-
-  f32x4 qacc[MTD][NTQ];  // dQ^T / scale: rows d, columns queries
-#pragma unroll
-  for (int md = 0; md < MTD; ++md)
-#pragma unroll
-    for (int nt = 0; nt < NTQ; ++nt) qacc[md][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float c = p.softmax_scale * kLog2e;
-  // per-lane offsets: K/V row fragments (row lr of a 16-row tile, chunk 4 ks + lg)
-  // and the transposing K^T reads (rows 4 lg + lr / 4, column 16 md + 4 (lr % 4))
-  int offr[KSD], offt[MTD];
-#pragma unroll
-  for (int ks = 0; ks < KSD; ++ks) offr[ks] = row8_off<D>(lr, lg, ks);
-#pragma unroll
-  for (int md = 0; md < MTD; ++md) offt[md] = tr8_off<D>(lr, lg, md);
-
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-
-  f32x4 sacc[NTQ], pacc[NTQ];  // S^T, dP^T of 16 keys: rows keys 4 lg + rr, column query 16 nt + lr
-  bf16x8 sb[2][NTQ];           // dS^T of the current and the previous chunk as B operands
-
-  // dS^T of key tile kt, query tile nt into sb[sl], k-slots 4 (kt % 2) + rr
-  // (key 16 kt + 4 lg + rr of the block); the chunk's k-slot order is the one
-  // the transposing K^T read produces
-  auto ds_tile = [&](int sl, int kt, int nt, bool masked, int k_first) {
-    const int qp = q_first + nt * 16 + lr;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      float x = fmaf(sacc[nt][rr], c, -l2[nt]);
-      if (masked) x = legal32(g, qp, k_first + kt * 16 + 4 * lg + rr) ? x : -INFINITY;
-      const float pv = __builtin_amdgcn_exp2f(x);
-      sb[sl][nt][4 * (kt & 1) + rr] = (__bf16)(pv * (pacc[nt][rr] - dd[nt]));
-    }
-  };
-  // A block is a fixed sequence of groups, each an LDS read (issued PD groups
-  // ahead) and the MFMAs that consume it:
-  //   per key tile kt (16 keys): KSD groups of S^T/dP^T, then MTD/2 groups of
-  //   dQ^T for the previous 32-key chunk interleaved with dS^T of tile kt;
-  //   finally MTD groups of dQ^T for the last chunk.
-  constexpr int GPS = KSD + MTD / 2, NKT = 2 * C::NCH, NGB = NKT * GPS + MTD, PD = 1;
-  static_assert(!W4 || 2 * PPW4 <= NGB, "copy pieces per block");
-  auto load_g = [&](const unsigned char* Kt, const unsigned char* Vt, int gg, bf16x8& fa, bf16x8& fb) {
-    if (gg < NKT * GPS) {
-      const int kt = gg / GPS, r = gg % GPS;
-      if (r < KSD) {
-        fa = ld_row8(Kt + offr[r] + kt * 16 * D * 2);
-        fb = ld_row8(Vt + offr[r] + kt * 16 * D * 2);
-      } else if (kt >= 2) {
-        const int md = (kt & 1) * (MTD / 2) + (r - KSD);
-        fa = ld_tr8(Kt + offt[md] + (kt / 2 - 1) * C::BKC * D * 2, D * 2);
-      }
-    } else {
-      const int md = gg - NKT * GPS;
-      fa = ld_tr8(Kt + offt[md] + (C::NCH - 1) * C::BKC * D * 2, D * 2);
-    }
-  };
-  auto exec_g = [&](int gg, const bf16x8& fa, const bf16x8& fb, bool masked, int k_first) {
-    if (gg < NKT * GPS) {
-      const int kt = gg / GPS, r = gg % GPS;
-      if (r < KSD) {
-#pragma unroll
-        for (int nt = 0; nt < NTQ; ++nt) {
-          sacc[nt] = mfma16(fa, qf[nt][r], r == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sacc[nt]);
-          pacc[nt] = mfma16(fb, gf[nt][r], r == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : pacc[nt]);
-        }
-      } else {
-        const int x = r - KSD;
-        if (kt >= 2) {
-          const int md = (kt & 1) * (MTD / 2) + x, sl = (kt / 2 - 1) & 1;
-#pragma unroll
-          for (int nt = 0; nt < NTQ; ++nt) qacc[md][nt] = mfma16(fa, sb[sl][nt], qacc[md][nt]);
-        }
-#pragma unroll
-        for (int nt = x * NTQ / (MTD / 2); nt < (x + 1) * NTQ / (MTD / 2); ++nt)
-          ds_tile((kt / 2) & 1, kt, nt, masked, k_first);
-      }
-    } else {
-      const int md = gg - NKT * GPS, sl = (C::NCH - 1) & 1;
-#pragma unroll
-      for (int nt = 0; nt < NTQ; ++nt) qacc[md][nt] = mfma16(fa, sb[sl][nt], qacc[md][nt]);
-    }
-  };
-
-  auto block = [&](int t, bool masked) {
-    const int buf = t & 1;
-    const uint32_t ent = entry_at(t);
-    const int k_first = (int)(ent >> 1) * BK;
-    [[maybe_unused]] const int kf_next = (int)(entry_at(t + 1) >> 1) * BK;
-    if constexpr (!W4) {
-      if (t + 1 < n_ent) stage(entry_at(t + 1), buf ^ 1);  // prefetch the next block
-    }
-    const unsigned char* Kt = smem + buf * 2 * T::BYTES;
-    const unsigned char* Vt = Kt + T::BYTES;
-    bf16x8 fa[PD + 1], fb[PD + 1];
-    static_for<PD>([&](auto ic) { load_g(Kt, Vt, ic.value, fa[ic.value], fb[ic.value]); });
-    __builtin_amdgcn_sched_barrier(0);
-    static_for<NGB>([&](auto ic) {
-      constexpr int gg = decltype(ic)::value;
-      if constexpr (W4 && gg < 2 * PPW4) stage_piece((gg & 1) ? vbase : kbase, kf_next, buf ^ 1, gg >> 1, gg & 1);
-      if constexpr (gg + PD < NGB) load_g(Kt, Vt, gg + PD, fa[(gg + PD) % (PD + 1)], fb[(gg + PD) % (PD + 1)]);
-      exec_g(gg, fa[gg % (PD + 1)], fb[gg % (PD + 1)], masked, k_first);
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    // register placement: dQ^T accumulators in VGPRs, Q^T / dO^T fragments in
-    // AGPRs (read directly as B operands); these statements emit nothing
-#pragma unroll
-    for (int md = 0; md < MTD; ++md)
-#pragma unroll
-      for (int nt = 0; nt < NTQ; ++nt) asm volatile("" : "+v"(qacc[md][nt]));
-#pragma unroll
-    for (int nt = 0; nt < NTQ; ++nt)
-#pragma unroll
-      for (int ks = 0; ks < KSD; ++ks) asm volatile("" : "+a"(qf[nt][ks]), "+a"(gf[nt][ks]));
-    __builtin_amdgcn_s_waitcnt(0);  // the next block has landed
-    __syncthreads();                 // ... for every wave, and this block is no longer read
-  };
-  int t = 0;
-  for (; t < n_full; ++t) block(t, false);
-  for (; t < n_ent; ++t) block(t, true);
-
-  const float scale = p.softmax_scale;
-#pragma unroll
-  for (int nt = 0; nt < NTQ; ++nt) {
-    const int qp = q_first + nt * 16 + lr;
-    if (qp >= n_q) continue;
-    __bf16* drow = dq + (row_base + qp) * D;
-#pragma unroll
-    for (int md = 0; md < MTD; ++md) {
-      bf16x4 w4;
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) w4[rr] = (__bf16)(scale * qacc[md][nt][rr]);
-      *reinterpret_cast<bf16x4*>(drow + md * 16 + 4 * lg) = w4;
-    }
-  }
-}
-
-template <int D, int BQ, int BK, int NQW, bool W4>
-hipError_t launch_dq_w(const cowa_params& p, const SchedView& sv, int hpw, int waves, const void* q, const void* k,
-                       const void* v, const void* d_o, const float* nl, const float* nd, void* dq,
-                       hipStream_t stream) {
-  using C = DqCfg<D, BQ, BK, NQW>;
-  auto kern = bwd_dq_kernel<D, BQ, BK, NQW, W4>;
-  {
-    const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
-    if (err != hipSuccess) return err;
-  }
-  const int n_hgroups = p.h_q / hpw;
-  const unsigned blocks = (unsigned)sv.n_qt * n_hgroups * (sv.ragged ? 1 : p.batch);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * waves), C::lds_bytes(sv.max_kt), stream, p, sv, hpw,
-                     static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
-                     static_cast<const __bf16*>(d_o), nl, nd, static_cast<__bf16*>(dq));
-  return hipGetLastError();
-}
-
-template <int D, int BQ, int BK, int NQW = 64>
-hipError_t launch_dq(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                     const void* d_o, const float* nl, const float* nd, void* dq, hipStream_t stream) {
-  using C = DqCfg<D, BQ, BK, NQW>;
-  if (sv.max_kt > C::max_kblocks()) return hipErrorInvalidValue;
-  const int G = p.h_q / p.h_k;
-  int hpw = 256 / BQ;  // up to 256 query rows per workgroup
-  while (hpw > 1 && G % hpw != 0) hpw >>= 1;
-  const int waves = hpw * C::WPH;
-  if (waves == 4) return launch_dq_w<D, BQ, BK, NQW, true>(p, sv, hpw, waves, q, k, v, d_o, nl, nd, dq, stream);
-  return launch_dq_w<D, BQ, BK, NQW, false>(p, sv, hpw, waves, q, k, v, d_o, nl, nd, dq, stream);
-}
-
 }  // namespace
 
 int bwd_main_max_qblocks(int d, int tk) {
   if (d == 128) return tk == 128 ? BwdCfg<128, 128>::max_qblocks() : BwdCfg<128, 64>::max_qblocks();
   return tk == 128 ? BwdCfg<64, 128>::max_qblocks() : BwdCfg<64, 64>::max_qblocks();
-}
-
-int bwd_dq_max_kblocks(int d, int tk) {
-  // the LDS of the dQ pass: two K/V blocks, then one row's block list
-  if (d == 128) return tk == 128 ? DqCfg<128, 128, 128>::max_kblocks() : DqCfg<128, 128, 64>::max_kblocks();
-  return tk == 128 ? DqCfg<64, 128, 128>::max_kblocks() : DqCfg<64, 128, 64>::max_kblocks();
 }
 
 bool bwd_bf16_supported(int d, int tq, int tk) {
@@ -938,23 +631,6 @@ hipError_t launch_bwd_main(const cowa_params& p, const SchedView& sv, const void
   if (p.head_dim == 128 && p.tile_k == 64) return launch_main<128, 64>(p, sv, q, k, v, d_o, w, dk, dv, stream);
   if (p.head_dim == 64 && p.tile_k == 128) return launch_main<64, 128>(p, sv, q, k, v, d_o, w, dk, dv, stream);
   if (p.head_dim == 64 && p.tile_k == 64) return launch_main<64, 64>(p, sv, q, k, v, d_o, w, dk, dv, stream);
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                         const void* d_o, void* dq, const BwdWork& w, hipStream_t stream) {
-  if (bwd_dq32_supported(p)) return launch_bwd_dq32(p, sv, q, k, v, d_o, dq, w, stream);
-#define COWA_DQ_CASE(D_, BQ_, BK_) \
-  if (p.head_dim == D_ && p.tile_q == BQ_ && p.tile_k == BK_) return launch_dq<D_, BQ_, BK_>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-  COWA_DQ_CASE(128, 128, 128)
-  COWA_DQ_CASE(128, 128, 64)
-  COWA_DQ_CASE(128, 64, 128)
-  COWA_DQ_CASE(128, 64, 64)
-  COWA_DQ_CASE(64, 128, 128)
-  COWA_DQ_CASE(64, 128, 64)
-  COWA_DQ_CASE(64, 64, 128)
-  COWA_DQ_CASE(64, 64, 64)
-#undef COWA_DQ_CASE
   return hipErrorInvalidValue;
 }
 

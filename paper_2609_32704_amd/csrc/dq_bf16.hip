@@ -1,10 +1,13 @@
 // CoWA backward, dQ pass, in bfloat16 on the CDNA4 matrix cores (Alg. 2, the
-// dQ = scale dS K term), for 128-key blocks and four-wave workgroups.
+// dQ = scale dS K term).
 //
-// One workgroup per (QO block i, QO heads of one KV group, sequence b): four
-// waves of 64 query rows (two heads of a 128-row block, or four of a 64-row
-// block).  Every QO head of a group has the same block set J_{h_k}(i), so the
-// heads share each K/V block staged in LDS.  Per KV block, full blocks first:
+// One workgroup of four waves per (row tile, hpw QO heads of one KV group,
+// sequence b): each wave owns 32 or 64 query rows of one head, so a row tile
+// holds 4 x 32 (or 64) / hpw rows.  Every QO head of a group sees the same keys, so
+// the heads share each K/V block staged in LDS; the row tiles and key blocks
+// are the kernel's own and it computes the tile's block list itself.  Per KV
+// block, full blocks
+// first:
 //   S^T = K Q^T and dP^T = V dO^T on v_mfma_f32_32x32x16_bf16, with Q^T and dO^T
 //     in registers for the whole row;
 //   P^T = exp2(S^T c - LSE log2 e) (LSE from the forward: P is exact, no
@@ -12,12 +15,26 @@
 //   dQ^T += K^T dS^T, K^T from the transposing LDS read of the row-major K
 //     block.  The S^T accumulator layout is the B-operand layout of dS^T, so dS
 //     never leaves registers.
-// The 32-key chunks of a row form a software pipeline: in chunk step n the
-// matrix cores compute S^T and dP^T of chunk n and dQ^T of chunk n - 2 while
-// the vector ALUs turn chunk n - 1 into dS^T.  Alg. 2 adds the dQ terms of
-// different KV blocks with atomics; here each row's dQ is complete in
-// registers and written once.  The pass recomputes S and dP (the dK/dV pass
-// computed them too).
+// The 32-key chunks of a row form a software pipeline: chunk step n computes S^T
+// and dP^T of chunk n beside the exponentials of chunk n - 1, then dQ^T of
+// chunk n - 1.  Alg. 2 adds the dQ terms of different KV blocks with atomics;
+// here each row's dQ is complete in registers and written once.  The pass
+// recomputes S and dP (the dK/dV pass computed them too).
+//
+// Shapes.  32 rows per wave and 64-key blocks: 250 registers and 64 KB of LDS
+// let two workgroups share a compute unit, and the two waves of a SIMD hide
+// each other's row starts, copies, barriers and exponentials.  64 rows per wave
+// read each fragment from LDS once for two products, which wins where rows are
+// long and many.  Measured at d = 128 (us; 32 rows / 64 rows, 64-key blocks / 64
+// rows, 128-key blocks / the pass before, which had 64 rows, 128-key blocks and
+// dQ^T two steps behind S^T, and two or one waves for groups that do not divide):
+//   1000 tokens, 32/8 heads         22 /    31 /     - /    40
+//   8192, 32/8 heads               273 /   277 /     - /   317
+//   2 x 4096, 8/8 heads             63 /    80 /     - /   170
+//   16384, near 4096 (V 5700)     1386 /  1358 /     - /  1435
+//   2 x 32768 (V 5900)            5183 /  5069 /  5144 /  5293
+//   131072 (V 20000)             30187 / 29110 / 28655 / 29522
+// At d = 64: 8192 tokens, 16/4 heads 93 / 106 / - / 125; 65536 3913 / 4099 / - / 4358.
 #include "internal.h"
 #include "window_rule.h"
 #include "mfma_tiles.h"
@@ -49,114 +66,83 @@ __device__ inline f32x16 mfma32_v(const bf16x8& a, const bf16x8& b, const f32x16
 __device__ inline f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
+__device__ inline void settle(f32x16 (&s)[1], f32x16 (&d)[1]) {
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(s[0]), "+v"(d[0]));
+}
 __device__ inline void settle(f32x16 (&s)[2], f32x16 (&d)[2]) {
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(s[0]), "+v"(s[1]), "+v"(d[0]), "+v"(d[1]));
 }
 
-template <int D, int BQ>
+// waves per SIMD that the registers are cut for
+constexpr int dq_occupancy(int nqt) { return nqt == 1 ? 2 : 1; }
+
+// NQT: 32-query tiles per wave (columns of S^T); BK: keys per block
+template <int D, int NQT_, int BK>
 struct Dq32Cfg {
-  static constexpr int BK = 128;          // keys per block
-  static constexpr int NQW = 64;          // query rows per wave
-  static constexpr int NQT = NQW / 32;    // 32-query tiles per wave (columns of S^T)
+  static constexpr int NW = 4;            // waves per workgroup
+  static constexpr int NQT = NQT_;
+  static constexpr int NQW = 32 * NQT;    // query rows per wave
   static constexpr int KS = D / 16;       // k-steps over d of S^T and dP^T
   static constexpr int MD = D / 32;       // 32-row d tiles of dQ^T
   static constexpr int NCH = BK / 32;     // 32-key chunks per block
   static constexpr int NG = 3 * KS;       // groups per chunk step: S^T, dP^T and dQ^T per slot x < KS
-  static constexpr int WPH = BQ / NQW;    // waves per QO head
-  static constexpr int HPW = 4 / WPH;     // QO heads per workgroup
   using T = SwzTile<D, BK>;
-  static constexpr int MAIN_BYTES = 4 * T::BYTES;  // K and V of two blocks; then the row's entry lists
+  static constexpr int MAIN_BYTES = 4 * T::BYTES;  // K and V of two blocks; then the row's entry list
   static constexpr int LDS_MAX = 160 * 1024;
-  static int lds_bytes(int n_kt) { return MAIN_BYTES + 4 * n_kt; }
-  static constexpr int OUT_PITCH = 2 * D + 16;  // staged dQ rows (bytes), in the K/V buffers at the end
+  static constexpr int OUT_PITCH = 2 * D + 16;  // staged dQ rows (bytes), in the K/V buffers and list at the end
+  static constexpr int OUT_BYTES = NW * NQW * OUT_PITCH;
+  static int lds_bytes(int n_kb) {
+    return MAIN_BYTES + 4 * n_kb > OUT_BYTES ? MAIN_BYTES + 4 * n_kb : OUT_BYTES;
+  }
+  static constexpr int max_kblocks() { return (LDS_MAX - MAIN_BYTES) / 4; }
   static_assert(KS == 2 * MD, "one dQ^T product group per k-step slot");
-  static_assert(4 * NQW * OUT_PITCH <= MAIN_BYTES, "staged rows fit the K/V buffers");
+  static_assert(NCH >= 2, "the K buffer of block t - 1 is free within block t");
 };
 
-template <int D, int BQ>
-__global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, const __bf16* __restrict__ q,
-                                                const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-                                                const __bf16* __restrict__ d_o, const float* __restrict__ nl,
-                                                const float* __restrict__ nd, __bf16* __restrict__ dq) {
-  using C = Dq32Cfg<D, BQ>;
+template <int D, int NQT, int BK>
+__global__ void __launch_bounds__(256, dq_occupancy(NQT))
+    bwd_dq32(cowa_params p, SchedView sv, RowTiles rt, int cap, const __bf16* __restrict__ q,
+             const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ d_o,
+             const float* __restrict__ nl, const float* __restrict__ nd, __bf16* __restrict__ dq) {
+  using C = Dq32Cfg<D, NQT, BK>;
   using T = typename C::T;
-  constexpr int NQT = C::NQT, KS = C::KS, MD = C::MD, NCH = C::NCH, NG = C::NG, BK = C::BK;
+  constexpr int KS = C::KS, MD = C::MD, NCH = C::NCH, NG = C::NG;
   extern __shared__ __align__(1024) unsigned char smem[];
 
+  const int hpw = rt.hpw, wph = C::NW / hpw;  // heads per workgroup, waves per head
   const int G = p.h_q / p.h_k;
-  // rows of 16 QO blocks x the head groups of one KV head share an XCD's L2;
-  // latest (longest) QO blocks first
-  const WorkItem wi = cluster_item(blockIdx.x, sv.n_qt, G / C::HPW, grid_units(p, sv),
-                                   cluster_rows(sv.n_qt, grid_units(p, sv), 16), true);
-  int hk;
-  const SeqCtx sc = seq_ctx(p, sv, wi.row, wi.unit, true, hk);
-  const int i = sc.tile;
-  const int h0 = (hk * (G / C::HPW) + wi.group) * C::HPW;  // first QO head (all in KV group hk)
+  int row, unit, group, hk, q0;
+  if (!row_item(rt, grid_units(p, sv), G / hpw, blockIdx.x, row, unit, group)) return;
+  const SeqCtx sc = row_ctx(p, sv, rt, row, unit, hk, q0);
+  const int n_q = sc.n_q, n_k = sc.n_k;
+  if (q0 >= n_q) return;
+  const int h0 = (hk * (G / hpw) + group) * hpw;  // first QO head (all in KV group hk)
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31, hh = lane >> 5;  // MFMA column and half
-  const int hq = h0 + wave / C::WPH;
-  const int q_first = i * BQ + (wave % C::WPH) * C::NQW;
+  const int hq = h0 + wave / wph;
+  const int q_first = q0 + (wave % wph) * C::NQW;
   const Geo32 g = sc.g;
-  const int n_q = sc.n_q, n_k = sc.n_k;
   const __bf16* kbase = k + (sc.k0 + (int64_t)hk * sc.kh) * D;
   const __bf16* vbase = v + (sc.k0 + (int64_t)hk * sc.kh) * D;
   const uint32_t smem_base = lds_addr(smem);
 
-  // Q^T and dO^T fragments (B operands): query column 32 nq + l32, d = 16 ks + 8 hh + 0..7;
-  // the row values of that query: the exponent offset -LSE log2 e (-inf for a
-  // row past n_q or without keys, so P = 0 there) and -D.  Loaded first, so
-  // that their latency overlaps that of the entry lists.
-  const int64_t row_base = sc.q0 + (int64_t)hq * sc.qh;
-  bf16x8 qf[NQT][KS], gf[NQT][KS];
-  float mlse[NQT], dn[NQT];
-#pragma unroll
-  for (int nq = 0; nq < NQT; ++nq) {
-    const int qp = q_first + nq * 32 + l32;
-    const bool ok = qp < n_q;
-    const int64_t row = row_base + (ok ? qp : 0);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(q + row * D + ks * 16 + 8 * hh);
-      const bf16x8 b = *reinterpret_cast<const bf16x8*>(d_o + row * D + ks * 16 + 8 * hh);
-      qf[nq][ks] = ok ? a : bf16x8{};
-      gf[nq][ks] = ok ? b : bf16x8{};
-    }
-    const float nlv = ok ? nl[row] : -INFINITY;
-    mlse[nq] = nlv == INFINITY ? -INFINITY : nlv;
-    dn[nq] = ok ? nd[row] : 0.f;
-  }
-  // zero the K/V buffers once when the last KV block is partial: key rows past
-  // the end of the sequence are not copied and must hold finite values
-  if (n_k % BK != 0)
-    for (int x = tid; x < C::MAIN_BYTES / 16; x += blockDim.x) reinterpret_cast<u32x4*>(smem)[x] = u32x4{0u, 0u, 0u, 0u};
-
-  // the row's entries, split into full (from the front) and partial (from the back) lists
-  const int r = sc.sched;
-  const int e0 = sv.fwd_row_ptr[r], e1 = sv.fwd_row_ptr[r + 1];
-  const int n_ent = e1 - e0;
-  const int cap = sv.max_kt;
+  // The row tile's block list, in LDS: full blocks from the front, partial
+  // ones from the back, both by descending key (at most three merged ranges)
+  const int q_last = (q0 + rt.R < n_q ? q0 + rt.R : n_q) - 1;
   uint32_t* list = reinterpret_cast<uint32_t*>(smem + C::MAIN_BYTES);
-  int n_full = 0;
-  for (int c0 = 0; c0 < n_ent; c0 += 64) {
-    const bool in = c0 + lane < n_ent;
-    const uint32_t ent = in ? sv.fwd_ent[e0 + c0 + lane] : 0u;
-    const uint64_t full = __ballot(in && !(ent & 1u));
-    const uint64_t part = __ballot(in && (ent & 1u));
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (wave == 0 && in) {
-      if (ent & 1u)
-        list[cap - 1 - (c0 - n_full + __popcll(part & below))] = ent;
-      else
-        list[n_full + __popcll(full & below)] = ent;
-    }
-    n_full += __popcll(full);
-  }
-  auto entry_at = [&](int t) -> uint32_t {
+  int n_ent;
+  const int n_full = build_row_list<BK>(g, q0, q_last, rt.R, list, cap, wave, lane, n_ent);
+  auto entry_at = [&](int t) -> int {
     const int tt = t < n_ent ? t : n_ent - 1;
     const int idx = tt < n_full ? tt : cap - 1 - (tt - n_full);
     return __builtin_amdgcn_readfirstlane(list[idx]);
   };
+  // zero the K/V buffers once when the row reaches the last KV block and that
+  // is partial: key rows past the end of the sequence are not copied and must
+  // hold finite values
+  if (n_k % BK != 0 && (q_last + g.off) / BK == n_k / BK)
+    for (int x = tid; x < C::MAIN_BYTES / 16; x += 256) reinterpret_cast<u32x4*>(smem)[x] = u32x4{0u, 0u, 0u, 0u};
 
   // Global -> LDS copies of K and V blocks: each lane copies the same 16-byte
   // column of its row in every 1 KB piece it takes (fixed byte offsets within a
@@ -179,12 +165,39 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
     dma16_buf(dma_off[n], rs, smem_base + buf_off + wave * 1024 + n * 4 * 1024);
   };
   auto stage = [&](const __bf16* base, int t, int buf_off) {
-    const int kf = (int)(entry_at(t) >> 1) * BK;
+    const int kf = entry_at(t) * BK;
 #pragma unroll
     for (int n = 0; n < PPW; ++n) stage_piece(base, kf, buf_off, n);
   };
-  __syncthreads();  // the lists and the zeroed buffers are in LDS
+  __syncthreads();  // the list and the zeroed buffers are in LDS
+  // (issued before the Q and dO loads: the row start waits for memory once)
+  if (n_ent > 0) {
+    stage(kbase, 0, kbuf_off(0));
+    stage(vbase, 0, vbuf_off(0));
+  }
 
+  // Q^T and dO^T fragments (B operands): query column 32 nq + l32, d = 16 ks + 8 hh + 0..7;
+  // the row values of that query: the exponent offset -LSE log2 e (-inf for a
+  // row past n_q or without keys, so P = 0 there) and -D.
+  const int64_t row_base = sc.q0 + (int64_t)hq * sc.qh;
+  bf16x8 qf[NQT][KS], gf[NQT][KS];
+  float mlse[NQT], dn[NQT];
+#pragma unroll
+  for (int nq = 0; nq < NQT; ++nq) {
+    const int qp = q_first + nq * 32 + l32;
+    const bool ok = qp < n_q;
+    const int64_t row = row_base + (ok ? qp : 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(q + row * D + ks * 16 + 8 * hh);
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(d_o + row * D + ks * 16 + 8 * hh);
+      qf[nq][ks] = ok ? a : bf16x8{};
+      gf[nq][ks] = ok ? b : bf16x8{};
+    }
+    const float nlv = ok ? nl[row] : -INFINITY;
+    mlse[nq] = nlv == INFINITY ? -INFINITY : nlv;
+    dn[nq] = ok ? nd[row] : 0.f;
+  }
   // dQ^T accumulators: element (lane, e) is d = 32 md + 8 (e / 4) + 4 hh + e % 4, query 32 nq + l32
   f32x16 qacc[MD][NQT];
 #pragma unroll
@@ -208,17 +221,19 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
   //  K and V rows (A operands of S^T, dP^T): row l32, columns 16 ks + 8 hh + 0..7;
   //  K^T (A operand of dQ^T): transposing reads of rows 4 hh + (lane % 16) / 4
   //  (+ 8 for slots 4..7), columns 32 md + 16 ((lane / 16) % 2) + 4 (lane % 4).
-  int offk[KS], offt[MD][2];
+  // The chunk index of a read is XORed with the row's swizzle, so the offset of
+  // k-step ks (chunk 2 ks + hh) is that of k-step 0 with bits 2 ks << 4 flipped,
+  // and that of d tile md the one of tile 0 with bits 4 md << 4 flipped: one XOR
+  // per read instead of a register per offset.
+  const int offk0 = T::off(l32, hh);
+  int offt0[2];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) offk[ks] = T::off(l32, 2 * ks + hh);
-#pragma unroll
-  for (int md = 0; md < MD; ++md)
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-      offt[md][hf] = T::off_col(4 * hh + ((lane & 15) >> 2) + 8 * hf, 32 * md + 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+  for (int hf = 0; hf < 2; ++hf) offt0[hf] = T::off_col(4 * hh + ((lane & 15) >> 2) + 8 * hf, 16 * ((lane >> 4) & 1) + 4 * (lane & 3));
+  auto offk = [&](int ks) { return offk0 ^ (ks << 5); };
+  auto offt = [&](int md, int hf) { return offt0[hf] ^ (md << 6); };
   auto ld_kt = [&](const unsigned char* tile, int md, int row_bytes) -> bf16x8 {
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + offt[md][0] + row_bytes));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + offt[md][1] + row_bytes));
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + offt(md, 0) + row_bytes));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + offt(md, 1) + row_bytes));
     const bf16x4 a = __builtin_bit_cast(bf16x4, lo), c2 = __builtin_bit_cast(bf16x4, hi);
     return bf16x8{a[0], a[1], a[2], a[3], c2[0], c2[1], c2[2], c2[3]};
   };
@@ -227,10 +242,10 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
   // the chunk, query 32 nq + l32.  Slots e = 8 kk .. 8 kk + 7 are exactly the keys
   // that lane holds in k-step kk of dQ^T += K^T dS^T (16 keys each).
   f32x16 sacc[2][NQT], pacc[2][NQT];
-  u32x4 dsw[2][2][NQT];  // dS^T of two chunks: bf16 pairs, [chunk % 2][k-step][query tile]
+  u32x4 dsw[2][NQT];  // dS^T of a chunk: bf16 pairs, [k-step][query tile]
   const float c = p.softmax_scale * kLog2e;
 
-  float pv[16 * NQT];  // exponentials in flight between the two halves of an element step
+  float pv[16 * NQT];   // exponentials in flight between the two halves of an element step
   uint32_t lmask[NQT];  // legal keys of the chunk being masked, per query tile
   // element step e of a chunk (query tile e / 16, slot e % 16), first half: P
   auto soft_a = [&](auto ec, auto rpc, bool masked, int key0) __attribute__((always_inline)) {
@@ -247,36 +262,37 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
     pv[e] = __builtin_amdgcn_exp2f(fmaf(sacc[rp][nq][s], c, mlse[nq]));
   };
   // second half (odd e): dS = P (dP - D) of the pair, rounded to bf16
-  auto soft_b = [&](auto ec, auto rpc, auto psc) __attribute__((always_inline)) {
-    constexpr int e = decltype(ec)::value, rp = decltype(rpc)::value, ps = decltype(psc)::value;
+  auto soft_b = [&](auto ec, auto rpc) __attribute__((always_inline)) {
+    constexpr int e = decltype(ec)::value, rp = decltype(rpc)::value;
     constexpr int nq = e / 16, s = e % 16;
     if constexpr (s & 1) {
       const float d0 = pv[e - 1] * (pacc[rp][nq][s - 1] + dn[nq]);
       const float d1 = pv[e] * (pacc[rp][nq][s] + dn[nq]);
       const bf16x2 pk = {(__bf16)d0, (__bf16)d1};
-      dsw[ps][s / 8][nq][(s & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
+      dsw[s / 8][nq][(s & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
     }
   };
   // the element steps that belong to slot `slot` of NS
-  auto soft_slot = [&](auto slotc, auto nsc, auto rpc, auto psc, bool masked, int key0) __attribute__((always_inline)) {
+  auto soft_slot = [&](auto slotc, auto nsc, auto rpc, bool masked, int key0) __attribute__((always_inline)) {
     constexpr int slot = decltype(slotc)::value, NS = decltype(nsc)::value;
     static_for<16 * NQT>([&](auto ec) {
       constexpr int e = decltype(ec)::value;
       constexpr int sa = e * NS / (16 * NQT);
       constexpr int sb = sa + 1 < NS ? sa + 1 : sa;
       if constexpr (sa == slot) soft_a(ec, rpc, masked, key0);
-      if constexpr (sb == slot) soft_b(ec, rpc, psc);
+      if constexpr (sb == slot) soft_b(ec, rpc);
     });
   };
 
   // LDS: K of block t in K buffer t % 2, V of block t in V buffer t % 2.  The
-  // dQ^T products of block t's first two chunk steps read K of block t - 1
-  // (chunks two back), so K of block t + 1 is copied from the middle of block
-  // t, once every wave has read K of block t - 1 for the last time; V of block
-  // t + 1 is copied from the start of block t.  Both copies go out one 1 KB
-  // piece per product group (a burst would hold the wave at the vector memory
-  // queue) and land by the end of block t.
-  constexpr int PF = 2, RING = PF + 2;
+  // dQ^T products of block t's first chunk step read K of block t - 1, so K of
+  // block t + 1 is copied from the end of that step on, once every wave has read
+  // K of block t - 1 for the last time; V of block t + 1 is copied from the
+  // start of block t.  Both copies go out one 1 KB piece per product group (a
+  // burst would hold the wave at the vector memory queue) and land by the end
+  // of block t.
+  constexpr int PF = 2, RING = PF + 1;
+  constexpr int NSG = 2 * KS;  // groups that the exponentials spread over
   int k_prev = 0;  // first key of the previous block
   // One block.  FIRST: the row's first block (nothing before its first chunk).
   // MPREV / MCUR: the chunks turned into dS here from the previous / this block
@@ -284,24 +300,28 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
   auto step = [&](int t, auto firstc, auto mprevc, auto mcurc) __attribute__((always_inline)) {
     constexpr bool FIRST = decltype(firstc)::value, MPREV = decltype(mprevc)::value;
     constexpr bool MCUR = decltype(mcurc)::value;
-    const int k_first = (int)(entry_at(t) >> 1) * BK;
-    const int kf_next = (int)(entry_at(t + 1) >> 1) * BK;  // (the last block repeats itself)
+    const int k_first = entry_at(t) * BK;
+    const int kf_next = entry_at(t + 1) * BK;  // (the last block repeats itself)
     const unsigned char* Kt = smem + kbuf_off(t);
     const unsigned char* Vt = smem + vbuf_off(t);
     const unsigned char* Kp = smem + kbuf_off(t + 1);  // K of block t - 1
     constexpr int NGS = NCH * NG;
-    constexpr int MID = 2 * NG - PF;  // group of the mid-block barrier
+    constexpr int MID = NG - PF;  // group of the mid-block barrier
+    static_assert(MID + PPW <= NGS && PPW <= NGS, "copy pieces per block");
     bf16x8 fa[RING];
     // group GG of the block: chunk step j, slot x, product 0 S^T / 1 dP^T / 2 dQ^T
+    constexpr auto gkind = [](int gi) { return gi < 2 * KS ? gi % 2 : 2; };
+    constexpr auto gslot = [](int gi) { return gi < 2 * KS ? gi / 2 : gi - 2 * KS; };
     auto load = [&](auto gc, bf16x8& dst) __attribute__((always_inline)) {
-      constexpr int GG = decltype(gc)::value, j = GG / NG, gi = GG % NG, x = gi / 3, kind = gi % 3;
-      constexpr int jo = (j + NCH - 2) % NCH;  // chunk of the dQ^T products within its block
-      constexpr bool OLD = j < 2;              // ... of the previous block
+      constexpr int GG = decltype(gc)::value, j = GG / NG, gi = GG % NG;
+      constexpr int x = gslot(gi), kind = gkind(gi);
+      constexpr int jo = (j + NCH - 1) % NCH;  // chunk of the dQ^T products within its block
+      constexpr bool OLD = j < 1;             // ... of the previous block
       if constexpr (kind == 0) {
-        dst = ld_row8(Kt + offk[x] + j * 32 * D * 2);
+        dst = ld_row8(Kt + offk(x) + j * 32 * D * 2);
       } else if constexpr (kind == 1) {
-        dst = ld_row8(Vt + offk[x] + j * 32 * D * 2);
-      } else if constexpr (!(FIRST && OLD)) {
+        dst = ld_row8(Vt + offk(x) + j * 32 * D * 2);
+      } else if constexpr (!(FIRST && j == 0)) {
         constexpr int kk = x / MD, md = x % MD;
         dst = ld_kt(OLD ? Kp : Kt, md, (jo * 32 + kk * 16) * D * 2);
       }
@@ -309,8 +329,9 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
     static_for<PF>([&](auto ic) { load(ic, fa[decltype(ic)::value]); });
     __builtin_amdgcn_sched_barrier(0);
     static_for<NGS>([&](auto gc) {
-      constexpr int GG = decltype(gc)::value, j = GG / NG, gi = GG % NG, x = gi / 3, kind = gi % 3;
-      constexpr bool OLD = j < 2;
+      constexpr int GG = decltype(gc)::value, j = GG / NG, gi = GG % NG;
+      constexpr int x = gslot(gi), kind = gkind(gi);
+      constexpr bool OLD = j < 1;
       if constexpr (GG == MID) {
         // every read of K of block t - 1 has been issued (fragments run PF
         // groups ahead): once all waves are past them, K of block t + 1 may
@@ -334,21 +355,20 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
             pacc[j & 1][m] = mfma32_v0(a, gf[m][0]);
           else
             pacc[j & 1][m] = mfma32_v(a, gf[m][x], pacc[j & 1][m]);
-        } else if constexpr (!(FIRST && OLD)) {
+        } else if constexpr (!(FIRST && j == 0)) {
           constexpr int kk = x / MD, md = x % MD;
-          qacc[md][m] = mfma32(a, __builtin_bit_cast(bf16x8, dsw[j & 1][kk][m]), qacc[md][m]);
+          qacc[md][m] = mfma32(a, __builtin_bit_cast(bf16x8, dsw[kk][m]), qacc[md][m]);
         }
         // dS^T of the chunk before chunk j (chunk j - 1 of this block, or the
-        // last chunk of the previous block), spread over the products
-        constexpr int slot = gi * NQT + m;
-        if constexpr (!(FIRST && j == 0)) {
-          using SL = std::integral_constant<int, slot>;
-          using NSC = std::integral_constant<int, NQT * NG>;
+        // last chunk of the previous block), beside the S^T and dP^T products
+        if constexpr (!(FIRST && j == 0) && gi < NSG) {
+          using SL = std::integral_constant<int, gi * NQT + m>;
+          using NSC = std::integral_constant<int, NQT * NSG>;
           using RP = std::integral_constant<int, (j + 1) & 1>;
           if constexpr (j == 0)
-            soft_slot(SL{}, NSC{}, RP{}, RP{}, MPREV, k_prev + (NCH - 1) * 32 + 4 * hh);
+            soft_slot(SL{}, NSC{}, RP{}, MPREV, k_prev + (NCH - 1) * 32 + 4 * hh);
           else
-            soft_slot(SL{}, NSC{}, RP{}, RP{}, MCUR, k_first + (j - 1) * 32 + 4 * hh);
+            soft_slot(SL{}, NSC{}, RP{}, MCUR, k_first + (j - 1) * 32 + 4 * hh);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -379,29 +399,23 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
     __syncthreads();                // ... for every wave
   };
   // after the last block: dS^T of its last chunk, then the dQ^T products of its
-  // last two chunks
+  // last chunk
   auto drain = [&](int t) __attribute__((always_inline)) {
     using R1 = std::integral_constant<int, 1>;
     static_for<16 * NQT>([&](auto ec) { soft_a(ec, R1{}, true, k_prev + (NCH - 1) * 32 + 4 * hh); });
-    static_for<16 * NQT>([&](auto ec) { soft_b(ec, R1{}, R1{}); });
+    static_for<16 * NQT>([&](auto ec) { soft_b(ec, R1{}); });
     const unsigned char* Kt = smem + kbuf_off(t);
-    static_for<2 * 2 * MD>([&](auto gc) {
-      constexpr int GG = decltype(gc)::value, jj = GG / (2 * MD), kk = (GG / MD) % 2, md = GG % MD;
-      constexpr int jo = NCH - 2 + jj;  // chunk within the block
-      const bf16x8 a = ld_kt(Kt, md, (jo * 32 + kk * 16) * D * 2);
+    static_for<2 * MD>([&](auto gc) {
+      constexpr int kk = decltype(gc)::value / MD, md = decltype(gc)::value % MD;
+      const bf16x8 a = ld_kt(Kt, md, ((NCH - 1) * 32 + kk * 16) * D * 2);
 #pragma unroll
-      for (int nq = 0; nq < NQT; ++nq)
-        qacc[md][nq] = mfma32(a, __builtin_bit_cast(bf16x8, dsw[jo & 1][kk][nq]), qacc[md][nq]);
+      for (int nq = 0; nq < NQT; ++nq) qacc[md][nq] = mfma32(a, __builtin_bit_cast(bf16x8, dsw[kk][nq]), qacc[md][nq]);
     });
   };
   using TT = std::true_type;
   using FF = std::false_type;
 
-  if (n_ent > 0) {
-    stage(kbase, 0, kbuf_off(0));
-    stage(vbase, 0, vbuf_off(0));
-  }
-  __builtin_amdgcn_s_waitcnt(0);
+  __builtin_amdgcn_s_waitcnt(0);  // K and V of the first block
   __syncthreads();
   {
     int t = 0;
@@ -448,17 +462,19 @@ __global__ void __launch_bounds__(256) bwd_dq32(cowa_params p, SchedView sv, con
   }
 }
 
-template <int D, int BQ>
+template <int D, int NQT, int BK>
 hipError_t launch(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
                   const void* d_o, const float* nl, const float* nd, void* dq, hipStream_t stream) {
-  using C = Dq32Cfg<D, BQ>;
-  auto kern = bwd_dq32<D, BQ>;
-  {
-    const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
-    if (err != hipSuccess) return err;
-  }
-  const unsigned blocks = (unsigned)sv.n_qt * (p.h_q / C::HPW) * (sv.ragged ? 1 : p.batch);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), C::lds_bytes(sv.max_kt), stream, p, sv,
+  using C = Dq32Cfg<D, NQT, BK>;
+  auto kern = bwd_dq32<D, NQT, BK>;
+  const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
+  if (err != hipSuccess) return err;
+  // as many heads of the group per workgroup as it has, up to one per wave
+  const int G = p.h_q / p.h_k, hpw = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+  const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw);
+  const int cap = list_capacity(p, sv, rt.R, BK);
+  if (cap > C::max_kblocks()) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3((unsigned)rt.blocks), dim3(256), C::lds_bytes(cap), stream, p, sv, rt, cap,
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<const __bf16*>(d_o), nl, nd, static_cast<__bf16*>(dq));
   return hipGetLastError();
@@ -466,21 +482,27 @@ hipError_t launch(const cowa_params& p, const SchedView& sv, const void* q, cons
 
 }  // namespace
 
-bool bwd_dq32_supported(const cowa_params& p) {
-  const int G = p.h_q / p.h_k;
-  if (p.tile_k != 128 || (p.head_dim != 128 && p.head_dim != 64)) return false;
-  if (p.tile_q == 128) return G % 2 == 0;
-  if (p.tile_q == 64) return G % 4 == 0;
-  return false;
-}
+// LDS of the dQ pass: two K/V blocks, then one row's block list.  Limits per
+// schedule tile, as the entry point documents them.
+int bwd_dq_max_kblocks(int d, int tk) { return (160 * 1024 - 4 * tk * d * 2) / 4; }
 
-hipError_t launch_bwd_dq32(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                           const void* d_o, void* dq, const BwdWork& w, hipStream_t stream) {
-  if (p.head_dim == 128 && p.tile_q == 128) return launch<128, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-  if (p.head_dim == 128 && p.tile_q == 64) return launch<128, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-  if (p.head_dim == 64 && p.tile_q == 128) return launch<64, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-  if (p.head_dim == 64 && p.tile_q == 64) return launch<64, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-  return hipErrorInvalidValue;
+hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
+                         const void* d_o, void* dq, const BwdWork& w, hipStream_t stream) {
+  // Which shape: V the visible keys of a row, W the workgroups of 256 rows (see
+  // the measurements at the top of this file).  The 64-row shape with 128-key
+  // blocks needs its row's list beside 128 KB of buffers (up to 1M keys).
+  if (p.head_dim == 128) {
+    const int64_t V = visible_bound(p, sv);
+    const int64_t W = ((int64_t)p.h_q * p.n_q * (sv.ragged ? 1 : p.batch) + 255) / 256;
+    if (V >= 8192 && W >= 256 && list_capacity(p, sv, 256, 128) <= Dq32Cfg<128, 2, 128>::max_kblocks())
+      return launch<128, 2, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+    if (V >= 4096 && V < 8192 && W >= 2048) return launch<128, 2, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+    return launch<128, 1, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+  }
+  // (128-key blocks halve the list where a row of more than 2M keys needs it)
+  if (list_capacity(p, sv, 128, 64) > Dq32Cfg<64, 1, 64>::max_kblocks())
+    return launch<64, 1, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+  return launch<64, 1, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
 }
 
 }  // namespace cowa

@@ -132,15 +132,12 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
 
   const int hpw = rt.hpw, wph = C::NW / hpw;  // heads per workgroup, waves per head
   const int G = p.h_q / p.h_k;
-  // rows of 16 row tiles x the head groups of one KV head share an XCD's L2;
-  // latest (longest) rows first
-  const WorkItem wi = cluster_item(blockIdx.x, rt.n_rows, G / hpw, grid_units(p, sv),
-                                   cluster_rows(rt.n_rows, grid_units(p, sv), 16), true);
-  int hk, q0;
-  const SeqCtx sc = row_ctx(p, sv, rt, wi.row, wi.unit, hk, q0);
+  int row, unit, group, hk, q0;
+  if (!row_item(rt, grid_units(p, sv), G / hpw, blockIdx.x, row, unit, group)) return;
+  const SeqCtx sc = row_ctx(p, sv, rt, row, unit, hk, q0);
   const int n_q = sc.n_q, n_k = sc.n_k;
   if (q0 >= n_q) return;
-  const int h0 = (hk * (G / hpw) + wi.group) * hpw;  // first QO head of this workgroup (all in KV group hk)
+  const int h0 = (hk * (G / hpw) + group) * hpw;  // first QO head of this workgroup (all in KV group hk)
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31, hh = lane >> 5;  // MFMA column and half
@@ -169,21 +166,9 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
   // ones from the back, both by descending key (at most three merged ranges,
   // computed rather than read: the schedule's tiles need not be this kernel's)
   const int q_last = (q0 + rt.R < n_q ? q0 + rt.R : n_q) - 1;
-  const Runs3 runs = key_block_runs3<BK>(g, q0, q_last);
-  const int n0 = runs.b0 - runs.a0 + 1, n1 = n0 + runs.b1 - runs.a1 + 1, n_ent = n1 + runs.b2 - runs.a2 + 1;
   uint32_t* list = reinterpret_cast<uint32_t*>(smem + C::MAIN_BYTES);
-  int n_full = 0;
-  for (int c0 = 0; c0 < n_ent; c0 += 64) {
-    const int t = n_ent - 1 - (c0 + lane);
-    const bool in = t >= 0;
-    const int j = t < n0 ? runs.a0 + t : t < n1 ? runs.a1 + (t - n0) : runs.a2 + (t - n1);
-    const bool is_full = key_block_full(g, q0, q0 + rt.R - 1, j * BK, j * BK + BK - 1);
-    const uint64_t full = __ballot(in && is_full);
-    const uint64_t part = __ballot(in && !is_full);
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (wave == 0 && in) list[is_full ? n_full + __popcll(full & below) : cap - 1 - (c0 - n_full + __popcll(part & below))] = j;
-    n_full += __popcll(full);
-  }
+  int n_ent;
+  const int n_full = build_row_list<BK>(g, q0, q_last, rt.R, list, cap, wave, lane, n_ent);
   auto entry_at = [&](int t) -> int {
     const int tt = t < n_ent ? t : n_ent - 1;
     const int idx = tt < n_full ? tt : cap - 1 - (tt - n_full);
@@ -770,8 +755,7 @@ hipError_t launch_one(const cowa_params& p, const SchedView& sv, const void* q, 
   const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw);
   const int cap = list_capacity(p, sv, rt.R, BK);
   if (cap > C::max_kblocks()) return hipErrorInvalidValue;
-  const unsigned blocks = (unsigned)rt.n_rows * (p.h_q / hpw) * (sv.ragged ? 1 : p.batch);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), C::lds_bytes(cap), stream, p, sv, rt, cap,
+  hipLaunchKernelGGL(kern, dim3((unsigned)rt.blocks), dim3(256), C::lds_bytes(cap), stream, p, sv, rt, cap,
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<__bf16*>(o), lse);
   return hipGetLastError();
@@ -794,6 +778,7 @@ hipError_t launch_one(const cowa_params& p, const SchedView& sv, const void* q, 
 // At d = 64 the exponentials weigh twice as much per product and 32 rows always
 // win (65536 tokens, 16/4 heads: 3172 / 3490); 128-key blocks from V = 1024 on
 // (3237 against 3472 us there; 27 against 25 at 2048 tokens, V 900).
+// (Past 1M keys in a row the list of 128-key blocks does not fit beside its buffers.)
 template <int D>
 hipError_t launch_d(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v, void* o,
                     float* lse, hipStream_t stream) {
@@ -801,7 +786,8 @@ hipError_t launch_d(const cowa_params& p, const SchedView& sv, const void* q, co
   const int64_t W = ((int64_t)p.h_q * p.n_q * (sv.ragged ? 1 : p.batch) + 255) / 256;
   hipError_t err;
   if constexpr (D == 128) {
-    if ((V >= 8192 && W >= 256) || (V >= 4096 && W >= 8192))
+    if (((V >= 8192 && W >= 256) || (V >= 4096 && W >= 8192)) &&
+        list_capacity(p, sv, 256, 128) <= FwdCfg<128, 2, 128>::max_kblocks())
       err = launch_one<128, 2, 128, false>(p, sv, q, k, v, o, lse, stream);
     else
       err = launch_one<128, 1, 64, false>(p, sv, q, k, v, o, lse, stream);

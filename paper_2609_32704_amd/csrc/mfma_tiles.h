@@ -83,7 +83,7 @@ __device__ inline WorkItem cluster_item(int id, int n_rows, int groups, int unit
 // unequal length (at one end of a sequence only some rows reach a long-range
 // window or the sink) must spread over many clusters to load every XCD alike
 // when there are few units (one KV head on a device, one short sequence).
-__device__ inline int cluster_rows(int n_rows, int units, int cq_max) {
+__host__ __device__ inline int cluster_rows(int n_rows, int units, int cq_max) {
   int cq = cq_max;
   while (cq > 4 && (int64_t)units * (n_rows / cq) < 8 * 16) cq >>= 1;
   return cq;

@@ -9,6 +9,7 @@
 #pragma once
 
 #include "internal.h"
+#include "mfma_tiles.h"
 #include "window_rule.h"
 
 namespace cowa {
@@ -75,8 +76,18 @@ __device__ inline SeqCtx seq_ctx(const cowa_params& p, const SchedView& sv, int 
 // schedule's block-to-sequence map: tile_q / R rows per schedule tile, or, when
 // R exceeds tile_q, one row per schedule tile of which every (R / tile_q)-th
 // of a sequence starts R rows and the others hold nothing.
+// The grid is cut into clusters of cq consecutive rows x the head groups of one
+// KV head; cluster c runs on XCD c % 8 (workgroups are dealt to the XCDs
+// round-robin by id), so that its workgroups, which stream nearly the same K/V
+// blocks, share that XCD's L2.  A cluster spans about 2048 queries: 32 or 64
+// workgroups, what an XCD's 32 compute units run at once, for groups of four
+// heads; fewer rows when there are less than 16 clusters per XCD (rows of
+// unequal length must spread over many clusters to load every XCD alike).
+// Rows go out last (longest) to first, whole cluster rows at a time; the unit
+// (KV head) of an XCD's cluster rotates from one row range to the next.
+// Rows and clusters are rounded up; the padding's workgroups end at once.
 struct RowTiles {
-  int32_t n_rows, R, hpw;
+  int32_t n_rows, R, hpw, cq, blocks;
 };
 inline RowTiles row_tiles(const cowa_params& p, const SchedView& sv, int hpw, int R) {
   RowTiles t;
@@ -86,7 +97,21 @@ inline RowTiles row_tiles(const cowa_params& p, const SchedView& sv, int hpw, in
     t.n_rows = (p.n_q + R - 1) / R;
   else
     t.n_rows = R <= p.tile_q ? sv.n_qt * (p.tile_q / R) : sv.n_qt;
+  const int units = grid_units(p, sv), groups = p.h_q / p.h_k / hpw;
+  t.cq = cluster_rows(t.n_rows, units, 2048 / R);
+  const int64_t clusters = ((int64_t)units * ((t.n_rows + t.cq - 1) / t.cq) + 7) / 8 * 8;
+  t.blocks = (int32_t)(clusters * t.cq * groups);
   return t;
+}
+// Workgroup id -> (row, unit, group); false: padding.
+__device__ inline bool row_item(const RowTiles& t, int units, int groups, int id, int& row, int& unit, int& group) {
+  const int cs = t.cq * groups;  // workgroups per cluster
+  const int n = id >> 3, c = (n / cs) * 8 + (id & 7), item = n % cs;
+  const int r = c / units;
+  unit = (c % units + r) % units;
+  group = item % groups;
+  row = t.n_rows - 1 - (r * t.cq + item / groups);
+  return row >= 0;
 }
 // Widest near, sink and long-range windows of any KV head (keys), for the
 // longest sequence.
@@ -135,6 +160,32 @@ __device__ inline SeqCtx row_ctx(const cowa_params& p, const SchedView& sv, cons
   const SeqCtx sc = seq_ctx(p, sv, row / n, unit, true, hk);
   q0 = sc.tile % m != 0 ? sc.n_q : sc.tile * p.tile_q + (row % n) * rt.R;
   return sc;
+}
+
+// The block list of the row tile of queries q0 .. q_last (of at most R), into
+// LDS: full blocks from the front, partial ones from the back, both by
+// descending key.  Every wave computes the same counts; wave 0 writes.  Returns
+// the number of full blocks.
+template <int BK>
+__device__ inline int build_row_list(const Geo32& g, int q0, int q_last, int R, uint32_t* list, int cap, int wave, int lane,
+                                     int& n_ent) {
+  const Runs3 runs = key_block_runs3<BK>(g, q0, q_last);
+  const int n0 = runs.b0 - runs.a0 + 1, n1 = n0 + runs.b1 - runs.a1 + 1;
+  n_ent = n1 + runs.b2 - runs.a2 + 1;
+  int n_full = 0;
+  for (int c0 = 0; c0 < n_ent; c0 += 64) {
+    const int t = n_ent - 1 - (c0 + lane);
+    const bool in = t >= 0;
+    const int j = t < n0 ? runs.a0 + t : t < n1 ? runs.a1 + (t - n0) : runs.a2 + (t - n1);
+    const bool is_full = key_block_full(g, q0, q0 + R - 1, j * BK, j * BK + BK - 1);
+    const uint64_t full = __ballot(in && is_full);
+    const uint64_t part = __ballot(in && !is_full);
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    if (wave == 0 && in)
+      list[is_full ? n_full + __popcll(full & below) : cap - 1 - (c0 - n_full + __popcll(part & below))] = (uint32_t)j;
+    n_full += __popcll(full);
+  }
+  return n_full;
 }
 
 }  // namespace cowa

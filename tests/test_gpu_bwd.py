@@ -96,6 +96,31 @@ def test_bwd_odd_shapes(case):
     _full_check(w, key=inputs.key_of("bwd", name), tile_q=tq, tile_k=tk)
 
 
+@pytest.mark.parametrize("h_q,h_k,n_q,near", [(16, 16, 4173, 8300), (32, 16, 2049, 8300), (16, 4, 4100, 8300),
+                                              (64, 16, 8200, 4200)])
+def test_bwd_dq_long_rows_by_heads_per_workgroup(h_q, h_k, n_q, near):
+    """dQ of rows long and many enough for the 64-row waves (128-key blocks from
+    8192 visible keys on, 64-key blocks from 4096), with one, two and four QO heads
+    per workgroup and a ragged last row tile, against the oracle on the first
+    and last 100 rows (dQ of a row depends on that row's dO and O alone)."""
+    dev = need_gpu()
+    import paper_2609_32704_amd as cowa
+    n_k, d, win = max(9001, n_q), 128, [(5, near, 100, 200)] * h_k
+    key = inputs.key_of("long_dq", h_q, h_k)
+    t = {n: inputs.normal_bf16((1, h, m, d), inputs.seed_sequence(key, n))
+         for n, h, m in (("q", h_q, n_q), ("k", h_k, n_k), ("v", h_k, n_k), ("do", h_q, n_q))}
+    q, k, v, do = (to_dev(t[n][0], dev) for n in ("q", "k", "v", "do"))
+    o, lse = cowa.fwd(q, k, v, 0, 0, 128, 64, d ** -0.5, windows=win)
+    dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, k, v))
+    cowa.bwd(q, k, v, o, lse, do, 0, 0, 128, 64, d ** -0.5, dq=dq, dk=dk, dv=dv, windows=win)
+    torch.cuda.synchronize()
+    assert not any(torch.isnan(x).any().item() for x in (dq, dk, dv))
+    for rows, keys in ((slice(0, 100), n_k - n_q + 100), (slice(n_q - 100, n_q), n_k)):
+        dq_r = ref.backward(t["q"][1][:, :, rows], t["k"][1][:, :, :keys], t["v"][1][:, :, :keys],
+                            t["do"][1][:, :, rows], 0, 0, d ** -0.5, windows=win)[0]
+        compare("dQ", to_host(dq[:, :, rows]), dq_r)
+
+
 def test_autograd_function_and_determinism():
     """cowa.attention (torch.autograd.Function over cowa_fwd / cowa_bwd):
     gradients of sum(O * dO) match the oracle, and a second forward and
