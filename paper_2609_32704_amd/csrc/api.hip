@@ -185,48 +185,114 @@ cowa::HeadGeo geo_of(const cowa_params* p, const Layout& L, int b, int h) {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Split plan of the dK/dV pass (cowa::BwdSplit): the leading KV blocks that hold
-// sink keys of some head are split into P parts, P = ceil(2 x longest such
-// column / longest other column) (at most 16, and at most 256 MB of partials):
-// parts of about half an ordinary column, which fill the ends of the other
-// workgroups' queues when the grid is a few rounds of the device.  A
-// column past the sink holds at most the query blocks of its near run
-// (B_k + w_near - 1 distance-0 keys) and of its long-range run
-// (B_k + hi - lo - 1), each spanning up to one block more than its length.
+// Split plan of the dK/dV pass (cowa::BwdSplit).  Lengths are in steps of 64
+// query rows of one QO head.
+//
+// Sink columns: parts of about half an ordinary column, and not longer than an
+// ordinary column's parts; at most 16 and 256 MB of partials (with whole other
+// columns and 64-key schedule tiles half as many, so that a schedule's tiles, not
+// the pass's 128-key columns, set the partials' bytes).
+//
+// Other columns, where there are at most two per workgroup slot of the device:
+// the pass takes about
+//   max(mean steps per slot, what the k + 1 longest of k * slots + 1 parts need
+//       on one slot) x time per step
+// plus the start of each workgroup and the partials' way through HBM, which is
+// evaluated for each number of parts from a few length classes per (sequence,
+// KV head): columns with near and whole long-range run, with some of the latter,
+// and with the whole or part of the near run alone.  With more columns than that the partials cost
+// about what the balance gains, and longest-first order does most of it.
+// Measured (us, d = 128, one part / the chosen number): 1000 tokens 32/8 heads
+// 95 / 50 (3), 2048 142 / 101 (2), 65536 of one KV head 2020 / 1910 (2); 8192
+// tokens 32/8 heads stay at one part (469, two would take 534); d = 64, 8192
+// tokens 16/4 heads 214 / 159 (3).
 cowa::BwdSplit bwd_split_plan(const cowa_params* p, const Layout& L) {
   cowa::BwdSplit sp;
-  if (p->tile_q < 1 || p->tile_k < 1 || L.max_kt == 0) return sp;
+  if (L.max_kt == 0 || L.max_qt == 0) return sp;
+  const int CK = cowa::kColKeys, G = p->h_q / p->h_k;
+  const int64_t copies = L.ragged ? 1 : p->batch;
+  const int64_t max_cols = ((int64_t)L.max_kt * p->tile_k + CK - 1) / CK;
   int64_t S = 0;
-  for (const cowa::WinDesc& w : L.win) S = std::max<int64_t>(S, ((int64_t)w.sink + p->tile_k - 1) / p->tile_k);
-  S = std::min<int64_t>(S, L.max_kt);
-  if (S == 0) return sp;
-  int64_t l_sink = 0, l_other = 1;
+  for (const cowa::WinDesc& w : L.win) S = std::max<int64_t>(S, ((int64_t)w.sink + CK - 1) / CK);
+  S = std::min<int64_t>(S, max_cols);
+  struct Level {
+    double len, cnt;
+  };
+  std::vector<Level> lv;
+  double l_sink = 0, l_other = 1, total = 0;
   for (size_t b = 0; b < L.seq.size(); ++b) {
-    const int64_t bq = ((int64_t)L.seq[b].n_q + p->tile_q - 1) / p->tile_q;
-    const int64_t bk = ((int64_t)L.seq[b].n_k + p->tile_k - 1) / p->tile_k;
+    const int64_t nq = L.seq[b].n_q, nk = L.seq[b].n_k, off = nk - nq;
+    if (nq == 0) continue;
+    const double bq = (double)((nq + 63) / 64);
+    const double cols = (double)((nk + CK - 1) / CK);
     for (int h = 0; h < p->h_k; ++h) {
-      const cowa::HeadGeo g = geo_of(p, L, (int)b, h);
-      for (int64_t j = 0; j < std::min(S, bk); ++j)
-        l_sink = std::max<int64_t>(l_sink, cowa::ranges_count(cowa::bwd_block_ranges(g, (int32_t)j)));
-      const int64_t near = std::min<int64_t>(g.w_near, g.n_k), width = std::min<int64_t>(g.hi, g.n_k) -
-                                                                         std::min<int64_t>(g.lo, g.n_k);
-      int64_t other = 0;
-      if (near > 0) other += (p->tile_k + near - 2) / p->tile_q + 2;
-      if (width > 0) other += (p->tile_k + width - 2) / p->tile_q + 2;
-      l_other = std::max(l_other, std::min(bq, other));
+      const cowa::Geo32 g = cowa::geo32(geo_of(p, L, (int)b, h));
+      if (S > 0 && g.w_sink > 0) {
+        const double s = G * (double)cowa::runs3_count(cowa::query_block_runs3<64>(g, 0, (int32_t)std::min<int64_t>(CK, nk) - 1));
+        l_sink = std::max(l_sink, s);
+        total += s * (double)std::min<int64_t>(S, (int64_t)cols) * copies;
+      }
+      const int64_t width = g.hi > g.lo ? g.hi - g.lo : 0;
+      const double ln = g.w_near > 0 ? std::min(bq, (double)((CK + g.w_near - 2) / 64 + 2)) : 0;
+      const double ll = width > 0 ? std::min(bq, (double)((CK + width - 2) / 64 + 2)) : 0;
+      const double with = std::max<double>(0, (double)(nk - g.lo) - std::max<int64_t>(0, off - g.hi)) / CK;
+      const double full = width > 0 ? std::max<double>(0, (double)(nk - g.hi) - std::max<int64_t>(0, off - g.lo)) / CK : 0;
+      const double ramp = width > 0 ? std::max(0.0, with - full) : 0;
+      const double near = std::max(0.0, std::min(cols, (double)(nk - std::max<int64_t>(0, off - g.w_near)) / CK) - full - ramp);
+      const double tail = std::min(near, (double)std::min<int64_t>(g.w_near, nk) / CK);  // the last columns' near runs end early
+      const Level add[5] = {{G * std::min(bq, ln + ll), full}, {G * std::min(bq, ln + 0.75 * ll), ramp / 2},
+                            {G * std::min(bq, ln + 0.25 * ll), ramp / 2}, {G * ln, near - tail}, {G * ln / 2, tail}};
+      for (const Level& a : add)
+        if (a.cnt > 0 && a.len > 0) {
+          lv.push_back({a.len, a.cnt * copies});
+          total += a.len * a.cnt * copies;
+          l_other = std::max(l_other, a.len);
+        }
     }
   }
+  const int64_t rows = (int64_t)p->h_k * copies * (L.ragged ? (int64_t)L.n_kt : max_cols);
+  const size_t part_bytes = cowa::bwd_part_floats(*p) * sizeof(float);
+  const double slots = p->head_dim == 128 ? 256 : 512, step_us = p->head_dim == 128 ? 2.0 : 2.6;
+  double n_cols = 0;
+  for (const Level& a : lv) n_cols += a.cnt;
   const int64_t seqs = L.ragged ? (int64_t)L.seq.size() : p->batch;
-  int64_t P = std::min<int64_t>((2 * l_sink + l_other - 1) / l_other, 16);
-  const size_t col_bytes = cowa::bwd_part_floats(*p) * sizeof(float);
-  while (P > 1 && (size_t)(seqs * p->h_k * S * P) * col_bytes > (size_t(256) << 20)) --P;
-  if (P <= 1) return sp;
-  sp.S = (int32_t)S;
-  sp.P = (int32_t)P;
-  sp.n_cols = seqs * p->h_k * S;
+  auto sink_parts = [&](int PO) -> int64_t {
+    if (S == 0) return 1;
+    int64_t P = std::min<int64_t>((int64_t)std::ceil(std::max(2, PO) * l_sink / l_other), 16) ;
+    if (PO == 1) P = P * p->tile_k / CK;
+    while (P > 1 && (size_t)(seqs * p->h_k * S * P) * part_bytes > (size_t(256) << 20)) --P;
+    return std::max<int64_t>(P, 1);
+  };
+  double best = 0;
+  for (int P : {1, 2, 3, 4, 6, 8}) {
+    if (P > 1 && (n_cols > 2 * slots || (size_t)rows * P * part_bytes > (size_t(256) << 20))) break;
+    std::vector<Level> parts;
+    for (const Level& a : lv) parts.push_back({a.len / P, a.cnt * P});
+    if (S > 0) parts.push_back({l_sink / sink_parts(P), (double)(seqs * p->h_k * S * sink_parts(P))});
+    if (parts.empty()) break;
+    std::sort(parts.begin(), parts.end(), [](const Level& a, const Level& b) { return a.len > b.len; });
+    double bound = total / slots, seen = 0;
+    for (const Level& a : parts) {
+      seen += a.cnt;
+      bound = std::max(bound, std::floor((seen - 1) / slots + 1) * a.len);
+    }
+    const double est = bound * step_us + 6.0 * std::ceil(seen / slots) +
+                       (P > 1 ? 5.0 + n_cols * P * 2.0 * part_bytes / 4.5e6 : 0.0);
+    if (P == 1 || est < 0.97 * best) {
+      best = est;
+      sp.PO = P;
+    }
+  }
+  sp.target = (int32_t)std::ceil(l_other / sp.PO);
+  sp.n_all = rows;
+  const int64_t P = sink_parts(sp.PO);
+  if (P > 1) {
+    sp.S = (int32_t)S;
+    sp.P = (int32_t)P;
+    sp.n_cols = seqs * p->h_k * S;
+  }
   return sp;
 }
-
 
 // Every schedule-relevant field must match (the digest covers windows and lengths).
 bool same_schedule(const cowa_params* a, const cowa_params* b) {
@@ -389,7 +455,7 @@ cowa_status cowa_schedule_size(const cowa_params* p, cowa_schedule_t* out) {
   } else {
     out->off_qt_seq = out->off_kt_seq = off;
   }
-  out->bytes = off;
+  out->bytes = off + cowa::column_order_bytes(*p);  // (off is where column_order_offset puts it)
   out->buf = nullptr;
   return COWA_OK;
 }
@@ -534,9 +600,9 @@ static cowa_status check_bwd(const cowa_params* p, const Layout& L, size_t ws_by
     return fail(COWA_ERR_UNSUPPORTED, "bf16 backward is built for tile_q, tile_k in {64, 128} (got %d x %d)",
                 p->tile_q, p->tile_k);
   // the dK/dV pass keeps a column's block list, the dQ pass a row's, in LDS
-  if (L.max_qt > cowa::bwd_main_max_qblocks(p->head_dim, p->tile_k))
+  if (L.max_qt > cowa::bwd_main_max_qblocks(p->head_dim))
     return fail(COWA_ERR_UNSUPPORTED, "backward supports at most %d query blocks per sequence (got %d)",
-                cowa::bwd_main_max_qblocks(p->head_dim, p->tile_k), L.max_qt);
+                cowa::bwd_main_max_qblocks(p->head_dim), L.max_qt);
   if (L.max_kt > cowa::bwd_dq_max_kblocks(p->head_dim, p->tile_k))
     return fail(COWA_ERR_UNSUPPORTED, "backward supports at most %d key blocks per sequence (got %d)",
                 cowa::bwd_dq_max_kblocks(p->head_dim, p->tile_k), L.max_kt);
@@ -547,7 +613,7 @@ static cowa_status check_bwd(const cowa_params* p, const Layout& L, size_t ws_by
   if ((int64_t)L.n_qt * p->h_q * seq_factor(p) >= (int64_t(1) << 31))
     return fail(COWA_ERR_UNSUPPORTED, "too many query blocks for one launch");
   const cowa::BwdSplit sp = bwd_split_plan(p, L);
-  if ((int64_t)L.n_kt * p->h_k * seq_factor(p) + sp.n_cols * sp.P + 8 >= (int64_t(1) << 31))
+  if (sp.n_all * sp.PO + sp.n_cols * sp.P + 64 >= (int64_t(1) << 31))
     return fail(COWA_ERR_UNSUPPORTED, "too many key blocks for one launch");
   const size_t need = cowa::bwd_workspace_bytes(*p, sp);
   if (!no_work(p) && (!workspace || ws_bytes < need || !aligned(workspace, 256)))

@@ -3,27 +3,25 @@
 // Three launches on the caller's stream:
 //
 //  1. bwd_pre: D = rowsum(O * dO) per query row (fp32).
-//  2. bwd_main (dK, dV): one workgroup of four waves per (KV block j, local KV
-//     head h_k, sequence b).  K_j and V_j stay in registers for the whole
-//     workgroup (wave w owns keys [w BK/4, (w+1) BK/4)).  The workgroup walks
-//     every QO head of the group and, for each, the QO blocks of I_{h_k}(j)
-//     in ascending order, 64 query rows per step; Q and dO of the next step are
-//     copied global -> LDS while the current step computes
+//  2. bwd_main (dK, dV): one workgroup of four waves per (column of 128 keys,
+//     local KV head h_k, sequence b), or per part of a column (BwdSplit).  K and V
+//     of the column stay in registers for the whole workgroup (wave w owns keys
+//     [32 w, 32 w + 32)).  The workgroup walks every QO head of the group and,
+//     for each, the blocks of 64 queries that see the column (its own list,
+//     computed from the windows), one per step; Q and dO of the step after next
+//     are copied global -> LDS while the current step computes
 //       S = Q K^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - D),
 //       dV^T += dO^T P, dK^T += scale Q^T dS.
-//     dK and dV of the block are summed over every QO head of the group
+//     dK and dV of the column are summed over every QO head of the group
 //     inside the workgroup and written once, without atomics; keys that no
-//     query sees get zeros.
-//  3. bwd_dq (dQ): one workgroup per (QO block i, QO heads of one KV group,
-//     sequence b), like the forward: K_j and V_j of J_{h_k}(i) are staged in
-//     double-buffered LDS and shared by the heads, Q^T and dO^T stay in
-//     registers, and per KV block
-//       S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - D), dQ^T += scale K^T dS^T.
-//     Alg. 2 adds dQ contributions of different KV blocks with atomics; at the
-//     paper's 128K scale that is ~5e10 fp32 atomic adds, more than the L2
-//     atomic units sustain, so dQ is instead computed in its own pass that
-//     recomputes S and dP (4d extra FLOPs per legal pair) and writes each dQ
-//     row once.
+//     query sees get zeros.  64-key columns (what 64-key schedule tiles got
+//     before) need every wave to read all of Q and dO for 16 keys: 2.5 us per
+//     step and CU for half the products of a 2.0 us step here.
+//  3. the dQ pass (dq_bf16.hip).  Alg. 2 adds dQ contributions of different KV
+//     blocks with atomics; at the paper's 128K scale that is ~5e10 fp32 atomic
+//     adds, more than the L2 atomic units sustain, so dQ is instead computed in
+//     its own pass that recomputes S and dP (4d extra FLOPs per legal pair) and
+//     writes each dQ row once.
 #include "internal.h"
 #include "window_rule.h"
 #include "mfma_tiles.h"
@@ -65,9 +63,10 @@ __global__ void __launch_bounds__(256) bwd_pre(const __bf16* __restrict__ o, con
   }
 }
 
-template <int D, int BK, int NW_ = 4>
+template <int D>
 struct BwdCfg {
-  static constexpr int NW = NW_;          // waves per workgroup
+  static constexpr int NW = 4;            // waves per workgroup
+  static constexpr int BK = kColKeys;     // keys per column
   static constexpr int BQ = 64;           // query rows per step
   static constexpr int NKW = BK / NW;     // keys per wave
   static constexpr int NTK = NKW / 16;    // key tiles per wave
@@ -86,135 +85,165 @@ struct BwdCfg {
   static constexpr int LOADS_PER_STEP = 2 * QT::LOADS / NW + 1;  // direct loads each wave issues per step
   static constexpr int OUT_BYTES = 2 * BK * (D + 8) * 2;        // dK, dV staging at the end
   static constexpr int LDS_MAX = 160 * 1024;
-  // LDS for a schedule with n_qt query blocks
-  static int lds_bytes(int n_qt) {
-    const int main = MAIN_BYTES + 4 * n_qt;
+  // LDS with a list of up to n_qb blocks of BQ queries (16 bits each)
+  static int lds_bytes(int n_qb) {
+    const int main = MAIN_BYTES + 2 * n_qb;
     return main > OUT_BYTES ? main : OUT_BYTES;
   }
-  static int max_qblocks() { return (LDS_MAX - MAIN_BYTES) / 4; }
+  static int max_qblocks() { return (LDS_MAX - MAIN_BYTES) / 2; }
 };
 
-// Parts of the split columns (BwdSplit): the first n_extra workgroups (a
-// multiple of 8, so the XCD order of the others is unchanged) take parts
-// 1 .. P-1 of the first S KV blocks of every (sequence, KV head); the other
-// workgroups take one column each (part 0 of a split column).
+// Workgroups of the pass (BwdSplit): the first n_extra (a multiple of 8, so the
+// XCD order of the others is unchanged) take parts 1 .. P-1 of the sink columns;
+// the others take n_items columns x PO parts (part 0 of a sink column).  With an
+// order table the items are its columns, longest first, each with the batch
+// entries and parts side by side (past two workgroups per compute unit in
+// chunks of 8 per XCD, so that neighbours share its L2); without one they are
+// clusters of 32 consecutive columns of one KV head that share an XCD's L2.
+// Measured (us, clusters / longest first): 8192 tokens, 32/8 heads 516 / 469; 4 x
+// 2048 288 / 231; 16384 1199 / 1142; 131072 of one KV head 6930 / 6887; 32768
+// (2048 columns) 3977 / 4056.
 struct SplitArgs {
-  float* part;       // [split column][P][2][BK * D] float32 partials
-  int32_t S, P;      // split blocks per (sequence, KV head); parts (1: no split)
+  float* part;       // sinks [n_cols][P][2][BK * D] float32 partials (P > 1), then [n_all][PO][...] (PO > 1)
+  int32_t S, P, PO, target;
   int32_t n_extra;   // workgroups of parts 1 .. P-1, rounded up to a multiple of 8
+  int32_t rows;      // column rows (column_rows)
+  int32_t n_items;   // columns of the grid
+  int64_t other;     // first partial of the other columns
+  int32_t cap;       // list capacity
 };
 
-template <int D, int BK, int NW>
-__global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv, SplitArgs sa,
+// The column of (unit, row): its context and first key; false: none starts there.
+__device__ inline bool column_ctx(const cowa_params& p, const SchedView& sv, int row, int unit, int& hk, SeqCtx& sc, int& k_first) {
+  sc = seq_ctx(p, sv, row, unit, false, hk);
+  k_first = sv.ragged ? sc.tile * p.tile_k : row * kColKeys;
+  return k_first % kColKeys == 0 && k_first < sc.n_k;
+}
+// Parts of a column of n_steps steps.
+__device__ inline int column_parts(const SplitArgs& sa, int col, int n_steps) {
+  if (sa.P > 1 && col < sa.S) return sa.P;
+  const int n = (n_steps + sa.target - 1) / sa.target;
+  return n < 1 ? 1 : (n < sa.PO ? n : sa.PO);
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, SplitArgs sa,
                                                 const __bf16* __restrict__ q,
                                                 const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                                                 const __bf16* __restrict__ d_o, const float* __restrict__ nl,
                                                 const float* __restrict__ nd, __bf16* __restrict__ dk,
                                                 __bf16* __restrict__ dv) {
-  using C = BwdCfg<D, BK, NW>;
+  using C = BwdCfg<D>;
+  constexpr int NW = C::NW, BK = C::BK;
   extern __shared__ __align__(1024) unsigned char smem[];
 
-  // clusters of 32 consecutive KV blocks of one KV head share an XCD's L2;
-  // first blocks (the sink, with the longest query lists) first
-  int part = 0;
-  WorkItem wi;
-  if ((int)blockIdx.x < sa.n_extra) {
+  int part = 0, row, unit;
+  const bool extra = (int)blockIdx.x < sa.n_extra;
+  if (extra) {
     const int e = blockIdx.x;
     part = 1 + e % (sa.P - 1);
     const int rest = e / (sa.P - 1);
     const int tile = rest % sa.S, us = rest / sa.S;  // us = sequence * h_k + KV head
     if (us >= p.batch * p.h_k) return;               // padding
-    wi.group = 0;
     if (!sv.ragged) {
-      wi.row = tile;
-      wi.unit = us;
+      row = tile;
+      unit = us;
     } else {
       const SeqDesc sd = sv.seq[us / p.h_k];
-      if (tile * BK >= sd.n_k) return;  // a sequence with fewer blocks
-      wi.row = sd.kt_off + tile;
-      wi.unit = us % p.h_k;
+      if (tile * BK >= sd.n_k) return;  // a sequence with fewer columns
+      row = sd.kt_off + tile * (BK / p.tile_k);
+      unit = us % p.h_k;
     }
+  } else if (sv.order != nullptr) {
+    const int total = sa.n_items * sa.PO, id = blockIdx.x - sa.n_extra, copies = sv.ragged ? 1 : p.batch;
+    const int e = total > 512 ? xcd_remap(id, total) : id;
+    part = e % sa.PO;
+    const int item = e / sa.PO;
+    const int c = (int)sv.order[item / copies];
+    row = c % sa.rows;
+    unit = c / sa.rows + (item % copies) * p.h_k;
   } else {
-    wi = cluster_item(blockIdx.x - sa.n_extra, sv.n_kt, 1, grid_units(p, sv),
-                      cluster_rows(sv.n_kt, grid_units(p, sv), 32), false);
+    const int e = blockIdx.x - sa.n_extra;
+    part = e / sa.n_items;
+    const WorkItem wi = cluster_item(e % sa.n_items, sa.rows, 1, grid_units(p, sv),
+                                     cluster_rows(sa.rows, grid_units(p, sv), 32), false);
+    row = wi.row;
+    unit = wi.unit;
   }
-  int hk;
-  const SeqCtx sc = seq_ctx(p, sv, wi.row, wi.unit, false, hk);
-  const int j = sc.tile;
-  const bool split = sa.P > 1 && j < sa.S;
-  const int n_parts = split ? sa.P : 1;
+  int hk, k_first_;
+  SeqCtx sc;
+  if (row >= sa.rows || !column_ctx(p, sv, row, unit, hk, sc, k_first_)) return;
+  const int j = k_first_ / BK;  // column within the sequence
+  if (!extra && part > 0 && sa.P > 1 && j < sa.S) return;  // a sink column's parts are the extra workgroups
   const int G = p.h_q / p.h_k;
   const Geo32 g = sc.g;
   const int n_q = sc.n_q, n_k = sc.n_k;
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int lr = lane & 15, lg = lane >> 4;
-  const int64_t k_first = (int64_t)j * BK;
+  const int64_t k_first = k_first_;
   const int64_t kv_row0 = sc.k0 + (int64_t)hk * sc.kh;
   const __bf16* kbase = k + kv_row0 * D;
   const __bf16* vbase = v + kv_row0 * D;
 
-  // The steps: every QO head of the group x every QO block of I(j) x 64-row
-  // sub-blocks.  Full blocks are taken first, then partial ones, so that each
+  // The steps: every QO head of the group x every block of 64 queries that sees
+  // the column.  Full blocks are taken first, then partial ones, so that each
   // of the two step loops below is straight-line code (the partial loop adds
-  // the element mask).  The column's entries are split once into two lists in
-  // LDS: full entries from the front, partial entries from the back.
-  const int col = sc.sched;
-  const int e0 = sv.bwd_col_ptr[col], e1 = sv.bwd_col_ptr[col + 1];
-  const int n_ent = e1 - e0;
-  const int cap = sv.max_qt;  // list capacity (entries of one column)
-  uint32_t* list = reinterpret_cast<uint32_t*>(smem + C::MAIN_BYTES);
+  // the element mask).  The blocks (up to three merged ranges, computed from the
+  // windows) go into two lists in LDS: full ones from the front, partial ones
+  // from the back, ascending.
+  const int k_last = (int)k_first + BK < n_k ? (int)k_first + BK - 1 : n_k - 1;
+  const Runs3 runs = query_block_runs3<C::BQ>(g, (int)k_first, k_last);
+  const int r0 = runs.b0 - runs.a0 + 1, r1 = r0 + runs.b1 - runs.a1 + 1, n_ent = r1 + runs.b2 - runs.a2 + 1;
+  const int n_steps = G * n_ent;
+  const int n_parts = column_parts(sa, j, n_steps);
+  if (part >= n_parts) return;
+  const bool split = n_parts > 1;
+  const int cap = sa.cap;
+  uint16_t* list = reinterpret_cast<uint16_t*>(smem + C::MAIN_BYTES);
   int n_full = 0;
   for (int c0 = 0; c0 < n_ent; c0 += 64) {  // every wave builds the same counts; wave 0 writes
-    const bool in = c0 + lane < n_ent;
-    const uint32_t ent = in ? sv.bwd_ent[e0 + c0 + lane] : 0u;
-    const uint64_t full = __ballot(in && !(ent & 1u));
-    const uint64_t part = __ballot(in && (ent & 1u));
+    const int t = c0 + lane;
+    const bool in = t < n_ent;
+    const int i = t < r0 ? runs.a0 + t : t < r1 ? runs.a1 + (t - r0) : runs.a2 + (t - r1);
+    const bool is_full = key_block_full(g, i * C::BQ, i * C::BQ + C::BQ - 1, (int)k_first, (int)k_first + BK - 1);
+    const uint64_t full = __ballot(in && is_full);
+    const uint64_t prt = __ballot(in && !is_full);
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int n_part_before = c0 - n_full;
-    if (wave == 0 && in) {
-      if (ent & 1u)
-        list[cap - 1 - (n_part_before + __popcll(part & below))] = ent;
-      else
-        list[n_full + __popcll(full & below)] = ent;
-    }
+    if (wave == 0 && in)
+      list[is_full ? n_full + __popcll(full & below) : cap - 1 - (c0 - n_full + __popcll(prt & below))] = (uint16_t)i;
     n_full += __popcll(full);
   }
   const int n_part = n_ent - n_full;
-  const int subs = p.tile_q / C::BQ;
-  const int steps_full = G * n_full * subs, n_steps = G * n_ent * subs;
+  const int steps_full = G * n_full;
   // this workgroup's steps: all of them, or part `part` of n_parts contiguous shares
   const int s_begin = (int)((int64_t)n_steps * part / n_parts);
   const int s_end = (int)((int64_t)n_steps * (part + 1) / n_parts);
-  // cursor (phase: 0 full / 1 partial, QO head, list index, sub-block) of step s_begin
-  int c_ph, c_k, c_sub, c_hh;
+  // cursor (phase: 0 full / 1 partial, QO head, list index) of step s_begin
+  int c_ph, c_k, c_hh;
   {
     c_ph = s_begin < steps_full ? 0 : 1;
     const int r = c_ph ? s_begin - steps_full : s_begin;
     const int nl_ = c_ph ? n_part : n_full;
-    c_hh = nl_ > 0 ? r / (nl_ * subs) : 0;
-    c_k = nl_ > 0 ? (r / subs) % nl_ : 0;
-    c_sub = r % subs;
+    c_hh = nl_ > 0 ? r / nl_ : 0;
+    c_k = nl_ > 0 ? r % nl_ : 0;
   }
-  int n1_ph = c_ph, n1_hh = c_hh, n1_k = c_k, n1_sub = c_sub;  // the next step (staged)
-  int n2_ph = c_ph, n2_hh = c_hh, n2_k = c_k, n2_sub = c_sub;  // the step after (being staged)
-  auto advance = [&](int& ph, int& hh, int& kk, int& sub) {
-    if (++sub == subs) {
-      sub = 0;
-      if (++kk == (ph == 0 ? n_full : n_part)) {
-        kk = 0;
-        if (++hh == G) {
-          hh = 0;
-          ++ph;
-          if (ph == 1 && n_part == 0) ph = 2;  // past the end
-        }
+  int n1_ph = c_ph, n1_hh = c_hh, n1_k = c_k;  // the next step (staged)
+  int n2_ph = c_ph, n2_hh = c_hh, n2_k = c_k;  // the step after (being staged)
+  auto advance = [&](int& ph, int& hh, int& kk) {
+    if (++kk == (ph == 0 ? n_full : n_part)) {
+      kk = 0;
+      if (++hh == G) {
+        hh = 0;
+        ++ph;
+        if (ph == 1 && n_part == 0) ph = 2;  // past the end
       }
     }
   };
   // list entry of a cursor; a cursor past the end names the first entry
-  auto entry_of = [&](int ph, int kk) -> uint32_t {
+  auto entry_of = [&](int ph, int kk) -> int {
     const int idx = ph == 0 ? kk : (ph == 1 ? cap - 1 - kk : (n_full > 0 ? 0 : cap - 1));
-    return __builtin_amdgcn_readfirstlane(list[idx]);
+    return __builtin_amdgcn_readfirstlane((int)list[idx]);
   };
 
   // Every operand of a step goes global -> LDS directly, through copies the
@@ -248,12 +277,11 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
     uint32_t bytes;    // bytes from there to the end of the sequence
     const float* rv;   // this lane's LSE or D value
   };
-  auto stage_src = [&](uint32_t ent, int hh, int sub) -> StageSrc {
+  auto stage_src = [&](int ent, int hh) -> StageSrc {
     hh = hh < G ? hh : G - 1;
-    const int q0 = (int)(ent >> 1) * p.tile_q + sub * C::BQ;
+    const int q0 = ent * C::BQ;
     const int64_t row_base = sc.q0 + (int64_t)(hk * G + hh) * sc.qh;
-    // a sub-block wholly past n_q (the last QO block's second half) reads nothing
-    const uint32_t bytes = q0 < n_q ? (uint32_t)(n_q - q0) * D * 2 : 0u;
+    const uint32_t bytes = (uint32_t)(n_q - q0) * D * 2;
     const int r = q0 + lane;
     const int rc = r < n_q ? r : n_q - 1;
     return StageSrc{(row_base + q0) * D * 2, bytes, ((wave & 1) ? nd : nl) + row_base + rc};
@@ -267,8 +295,8 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
   auto stage_rows = [&](const StageSrc& src, int slot) {
     dma4(src.rv, __builtin_amdgcn_readfirstlane(smem_base + C::rv_off(slot) + (wave & 1) * C::BQ * 4));
   };
-  auto stage = [&](uint32_t ent, int hh, int sub, int slot) {
-    const StageSrc src = stage_src(ent, hh, sub);
+  auto stage = [&](int ent, int hh, int slot) {
+    const StageSrc src = stage_src(ent, hh);
 #pragma unroll
     for (int n = 0; n < PPW; ++n) stage_piece(src, n, slot);
     stage_rows(src, slot);
@@ -280,11 +308,11 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
   __syncthreads();  // the entry lists and the zeroed stages are in LDS
   // prologue: the first two steps in flight
   if (s_end > s_begin) {
-    stage(entry_of(n2_ph, n2_k), n2_hh, n2_sub, 0);  // step s_begin
-    advance(n2_ph, n2_hh, n2_k, n2_sub);
-    n1_ph = n2_ph, n1_hh = n2_hh, n1_k = n2_k, n1_sub = n2_sub;
-    stage(entry_of(n2_ph, n2_k), n2_hh, n2_sub, 1);  // step 1
-    advance(n2_ph, n2_hh, n2_k, n2_sub);
+    stage(entry_of(n2_ph, n2_k), n2_hh, 0);  // step s_begin
+    advance(n2_ph, n2_hh, n2_k);
+    n1_ph = n2_ph, n1_hh = n2_hh, n1_k = n2_k;
+    stage(entry_of(n2_ph, n2_k), n2_hh, 1);  // step 1
+    advance(n2_ph, n2_hh, n2_k);
   }
 
   // K and V rows of this wave's keys as B fragments: key nt*16 + lr, d = ks*32 + 8*lg + 0..7
@@ -402,8 +430,8 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
     const unsigned char* qs = smem + C::q_off(slot);
     const unsigned char* dos = smem + C::do_off(slot);
     const float* rowv = reinterpret_cast<const float*>(smem + C::rv_off(slot));
-    const int q0 = (int)(entry_of(c_ph, c_k) >> 1) * p.tile_q + c_sub * C::BQ;
-    const StageSrc src2 = stage_src(entry_of(n2_ph, n2_k), n2_hh, n2_sub);
+    const int q0 = entry_of(c_ph, c_k) * C::BQ;
+    const StageSrc src2 = stage_src(entry_of(n2_ph, n2_k), n2_hh);
 
     // groups 0 .. 4 NG - 1: S/dP(half 0), S/dP(half 1), dV/dK(half 0), dV/dK(half 1);
     // operand fragments are read PD groups ahead of their MFMAs
@@ -473,9 +501,9 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
     // flight), for every wave; and this step's slot is no longer read
     __builtin_amdgcn_s_waitcnt(vmcnt_only(C::LOADS_PER_STEP));
     __syncthreads();
-    c_ph = n1_ph, c_k = n1_k, c_sub = n1_sub;
-    n1_ph = n2_ph, n1_hh = n2_hh, n1_k = n2_k, n1_sub = n2_sub;
-    advance(n2_ph, n2_hh, n2_k, n2_sub);
+    c_ph = n1_ph, c_k = n1_k;
+    n1_ph = n2_ph, n1_hh = n2_hh, n1_k = n2_k;
+    advance(n2_ph, n2_hh, n2_k);
     slot = slot == 2 ? 0 : slot + 1;
   };
   int t = s_begin;
@@ -489,7 +517,8 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
   if (split) {
     // float32 partials in register order: element ((md NTK + nt) NW + wave) 64 + lane
     // holds rows d = 16 md + 4 (lane / 16) + 0..3, key wave NKW + 16 nt + lane % 16
-    const int64_t col = ((int64_t)(sc.b * p.h_k + hk) * sa.S + j) * sa.P + part;
+    const int64_t col = sa.P > 1 && j < sa.S ? ((int64_t)(sc.b * p.h_k + hk) * sa.S + j) * sa.P + part
+                                             : sa.other + ((int64_t)unit * sa.rows + row) * sa.PO + part;
     f32x4* pk = reinterpret_cast<f32x4*>(sa.part + col * 2 * BK * D);
     f32x4* pv = pk + BK * D / 4;
 #pragma unroll
@@ -528,38 +557,60 @@ __global__ void __launch_bounds__(64 * NW) bwd_main(cowa_params p, SchedView sv,
   }
 }
 
-// Sum of the P partials of each split column (in part order) -> bf16 dK, dV;
-// one workgroup per (split column, 16-row d tile), each thread the
-// register-order elements a lane of bwd_main held for that d tile.
-template <int D, int BK, int NW>
-__global__ void __launch_bounds__(64 * NW) bwd_split_sum(cowa_params p, SchedView sv, SplitArgs sa,
+// Sum of the partials of each split column (in part order) -> bf16 dK, dV; one
+// workgroup per (column, 16-row d tile), each thread the register-order elements
+// a lane of bwd_main held for that d tile.  Sink columns first, then, where
+// others have parts, every other one (of which those of one part end at once).
+template <int D>
+__global__ void __launch_bounds__(256) bwd_split_sum(cowa_params p, SchedView sv, SplitArgs sa, int n_sink,
                                                      __bf16* __restrict__ dk, __bf16* __restrict__ dv) {
-  using C = BwdCfg<D, BK, NW>;
-  const int c = blockIdx.x;  // (sequence * h_k + KV head) * S + block
-  const int j = c % sa.S, us = c / sa.S, b = us / p.h_k, hk = us % p.h_k;
-  int n_k;
-  int64_t row0;  // row of key 0 of this (sequence, KV head) in K, V, dK, dV
-  if (!sv.ragged) {
-    n_k = p.n_k;
-    row0 = ((int64_t)b * p.h_k + hk) * p.n_k;
+  using C = BwdCfg<D>;
+  constexpr int NW = C::NW, BK = C::BK;
+  int row, unit, j;
+  int64_t first;  // first partial of the column
+  if ((int)blockIdx.x < n_sink) {
+    const int c = blockIdx.x, us = c / sa.S;  // (sequence * h_k + KV head) * S + column
+    j = c % sa.S;
+    first = (int64_t)c * sa.P;
+    row = j;
+    unit = us;
+    if (sv.ragged) {
+      const SeqDesc sd = sv.seq[us / p.h_k];
+      if (j * BK >= sd.n_k) return;
+      row = sd.kt_off + j * (BK / p.tile_k);
+      unit = us % p.h_k;
+    }
   } else {
-    const SeqDesc sd = sv.seq[b];
-    n_k = sd.n_k;
-    row0 = (int64_t)hk * p.n_k + sd.k_start;
+    const int c = blockIdx.x - n_sink;
+    row = c % sa.rows;
+    unit = c / sa.rows;
+    first = sa.other + (int64_t)c * sa.PO;
   }
-  if (j * BK >= n_k) return;
+  int hk, k_first;
+  SeqCtx sc;
+  if (!column_ctx(p, sv, row, unit, hk, sc, k_first)) return;
+  j = k_first / BK;
+  const int n_k = sc.n_k;
+  int n_parts = sa.P;
+  if ((int)blockIdx.x >= n_sink) {
+    if (sa.P > 1 && j < sa.S) return;
+    const int k_last = k_first + BK < n_k ? k_first + BK - 1 : n_k - 1;
+    n_parts = column_parts(sa, j, p.h_q / p.h_k * runs3_count(query_block_runs3<C::BQ>(sc.g, k_first, k_last)));
+    if (n_parts == 1) return;
+  }
+  const int64_t row0 = sc.k0 + (int64_t)hk * sc.kh;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-  const f32x4* src = reinterpret_cast<const f32x4*>(sa.part + (int64_t)c * sa.P * 2 * BK * D);
+  const f32x4* src = reinterpret_cast<const f32x4*>(sa.part + first * 2 * BK * D);
   const int md = blockIdx.y;
 #pragma unroll
   for (int nt = 0; nt < C::NTK; ++nt) {
     const int x = ((md * C::NTK + nt) * NW + wave) * 64 + lane;
     f32x4 a = src[x], g = src[BK * D / 4 + x];
-    for (int pt = 1; pt < sa.P; ++pt) {
-      a += src[pt * (2 * BK * D / 4) + x];
-      g += src[pt * (2 * BK * D / 4) + BK * D / 4 + x];
+    for (int pt = 1; pt < n_parts; ++pt) {
+      a += src[(int64_t)pt * (2 * BK * D / 4) + x];
+      g += src[(int64_t)pt * (2 * BK * D / 4) + BK * D / 4 + x];
     }
-    const int64_t kp = (int64_t)j * BK + wave * C::NKW + nt * 16 + lr;
+    const int64_t kp = (int64_t)k_first + wave * C::NKW + nt * 16 + lr;
     if (kp >= n_k) continue;
     bf16x4 ka, va;
 #pragma unroll
@@ -573,39 +624,50 @@ __global__ void __launch_bounds__(64 * NW) bwd_split_sum(cowa_params p, SchedVie
   }
 }
 
-template <int D, int BK, int NW = 4>
-hipError_t launch_main(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
+template <int D>
+hipError_t launch_main(const cowa_params& p, SchedView sv, const void* q, const void* k, const void* v,
                        const void* d_o, const BwdWork& w, void* dk, void* dv, hipStream_t stream) {
-  using C = BwdCfg<D, BK, NW>;
+  using C = BwdCfg<D>;
   static_assert(C::OUT_BYTES <= C::LDS_MAX && C::MAIN_BYTES < C::LDS_MAX, "LDS budget");
-  if (sv.max_qt > C::max_qblocks()) return hipErrorInvalidValue;
-  auto kern = bwd_main<D, BK, NW>;
+  auto kern = bwd_main<D>;
   {
     const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
     if (err != hipSuccess) return err;
   }
+  const BwdSplit& sp = w.split;
+  const int copies = sv.ragged ? 1 : p.batch;
+  if (column_count(p) * copies > kMaxOrdered) sv.order = nullptr;  // (many rounds: the L2 matters more)
   SplitArgs sa;
   sa.part = w.part;
-  sa.S = w.split.S;
-  sa.P = w.split.P;
-  sa.n_extra = sa.P > 1 ? (int32_t)(((int64_t)p.batch * p.h_k * sa.S * (sa.P - 1) + 7) / 8 * 8) : 0;
-  const unsigned blocks = (unsigned)sv.n_kt * p.h_k * (sv.ragged ? 1 : p.batch) + (unsigned)sa.n_extra;
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * NW), C::lds_bytes(sv.max_qt), stream, p, sv, sa,
+  sa.S = sp.S;
+  sa.P = sp.P;
+  sa.PO = sp.PO;
+  sa.target = sp.target > 0 ? sp.target : 1;
+  sa.n_extra = sp.P > 1 ? (int32_t)(((int64_t)p.batch * p.h_k * sp.S * (sp.P - 1) + 7) / 8 * 8) : 0;
+  sa.rows = column_rows(p, sv.n_kt);
+  sa.n_items = sv.order ? (int32_t)column_count(p) * copies : sa.rows * p.h_k * copies;
+  sa.other = sp.P > 1 ? sp.n_cols * sp.P : 0;
+  // 64-row blocks of the longest sequence
+  const int64_t nq = sv.ragged ? (int64_t)sv.max_qt * p.tile_q : p.n_q;
+  sa.cap = (int32_t)((nq + C::BQ - 1) / C::BQ);
+  if (sa.cap > C::max_qblocks()) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)sa.n_items * sa.PO + (unsigned)sa.n_extra;
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), C::lds_bytes(sa.cap), stream, p, sv, sa,
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<const __bf16*>(d_o), w.nl, w.nd, static_cast<__bf16*>(dk),
                      static_cast<__bf16*>(dv));
-  if (sa.P > 1)
-    hipLaunchKernelGGL((bwd_split_sum<D, BK, NW>), dim3((unsigned)w.split.n_cols, C::MD), dim3(64 * NW), 0, stream, p, sv,
-                       sa, static_cast<__bf16*>(dk), static_cast<__bf16*>(dv));
+  const int n_sink = sp.P > 1 ? (int)sp.n_cols : 0;
+  const unsigned sums = (unsigned)n_sink + (sp.PO > 1 ? (unsigned)sp.n_all : 0u);
+  if (sums > 0)
+    hipLaunchKernelGGL((bwd_split_sum<D>), dim3(sums, C::MD), dim3(256), 0, stream, p, sv, sa, n_sink,
+                       static_cast<__bf16*>(dk), static_cast<__bf16*>(dv));
   return hipGetLastError();
 }
 
 }  // namespace
 
-int bwd_main_max_qblocks(int d, int tk) {
-  if (d == 128) return tk == 128 ? BwdCfg<128, 128>::max_qblocks() : BwdCfg<128, 64>::max_qblocks();
-  return tk == 128 ? BwdCfg<64, 128>::max_qblocks() : BwdCfg<64, 64>::max_qblocks();
-}
+// Query blocks of the schedule (up to 128 rows each) that a column's list can hold.
+int bwd_main_max_qblocks(int d) { return (d == 128 ? BwdCfg<128>::max_qblocks() : BwdCfg<64>::max_qblocks()) / 2; }
 
 bool bwd_bf16_supported(int d, int tq, int tk) {
   return (d == 64 || d == 128) && (tq == 64 || tq == 128) && (tk == 64 || tk == 128);
@@ -627,11 +689,8 @@ hipError_t launch_bwd_prepare(const cowa_params& p, const void* o, const void* d
 
 hipError_t launch_bwd_main(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
                            const void* d_o, void* dk, void* dv, const BwdWork& w, hipStream_t stream) {
-  if (p.head_dim == 128 && p.tile_k == 128) return launch_main<128, 128>(p, sv, q, k, v, d_o, w, dk, dv, stream);
-  if (p.head_dim == 128 && p.tile_k == 64) return launch_main<128, 64>(p, sv, q, k, v, d_o, w, dk, dv, stream);
-  if (p.head_dim == 64 && p.tile_k == 128) return launch_main<64, 128>(p, sv, q, k, v, d_o, w, dk, dv, stream);
-  if (p.head_dim == 64 && p.tile_k == 64) return launch_main<64, 64>(p, sv, q, k, v, d_o, w, dk, dv, stream);
-  return hipErrorInvalidValue;
+  return p.head_dim == 128 ? launch_main<128>(p, sv, q, k, v, d_o, w, dk, dv, stream)
+                           : launch_main<64>(p, sv, q, k, v, d_o, w, dk, dv, stream);
 }
 
 }  // namespace cowa

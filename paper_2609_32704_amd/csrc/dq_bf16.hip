@@ -488,15 +488,17 @@ int bwd_dq_max_kblocks(int d, int tk) { return (160 * 1024 - 4 * tk * d * 2) / 4
 
 hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
                          const void* d_o, void* dq, const BwdWork& w, hipStream_t stream) {
-  // Which shape: V the visible keys of a row, W the workgroups of 256 rows (see
-  // the measurements at the top of this file).  The 64-row shape with 128-key
+  // Which shape: V the visible keys of a row, W the 256-row tiles of one KV head's
+  // group in one sequence (see the measurements at the top of this file; neither
+  // batch nor the other heads enter, so a sequence's or a rank's result does not
+  // depend on them).  The 64-row shape with 128-key
   // blocks needs its row's list beside 128 KB of buffers (up to 1M keys).
   if (p.head_dim == 128) {
     const int64_t V = visible_bound(p, sv);
-    const int64_t W = ((int64_t)p.h_q * p.n_q * (sv.ragged ? 1 : p.batch) + 255) / 256;
-    if (V >= 8192 && W >= 256 && list_capacity(p, sv, 256, 128) <= Dq32Cfg<128, 2, 128>::max_kblocks())
+    const int64_t W = (int64_t)(p.h_q / p.h_k) * p.n_q / 256;
+    if (V >= 8192 && W >= 32 && list_capacity(p, sv, 256, 128) <= Dq32Cfg<128, 2, 128>::max_kblocks())
       return launch<128, 2, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-    if (V >= 4096 && V < 8192 && W >= 2048) return launch<128, 2, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+    if (V >= 4096 && V < 8192 && W >= 256) return launch<128, 2, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
     return launch<128, 1, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
   }
   // (128-key blocks halve the list where a row of more than 2M keys needs it)

@@ -765,15 +765,18 @@ hipError_t launch_one(const cowa_params& p, const SchedView& sv, const void* q, 
 // waves per SIMD (at d = 128 with 64-key blocks), which hide each other's row
 // starts, copies and exponentials, and make twice as many workgroups; 64 rows
 // per wave read each K/V fragment from LDS once for two products, which wins
-// only where rows are long and many.  Measured at d = 128 (us, 32 rows and
-// 64-key blocks / 64 rows and 128-key blocks), V the visible keys of a row, W
-// the workgroups of 256 rows:
-//   1000 tokens, 32/8 heads (V 250, W 125)               23 /   37
-//   4096, 32/8 (V 1500, W 512)                           95 /  107
-//   2 x 4096, 8/8 heads (V 1000, W 256)                  55 /   68  (121 before: two waves)
-//   32768, 32/8 (V 5900, W 4096)                       2039 / 2088
-//   8192 dense (V up to 8192, W 1024)                   537 /  517
-//   2 x 32768, 32/8 (V 5900, W 8192)                   4005 / 3857
+// only where rows are long and many.  The rule looks at one KV head of one
+// sequence (so that a sequence's result does not depend on its batch, nor a
+// rank's on the heads of the others): V the visible keys of a row, W the
+// 256-row tiles of the head's group.  Measured at d = 128 (us, 32 rows and 64-key
+// blocks / 64 rows and 128-key blocks):
+//   1000 tokens, 32/8 heads (V 250, W 15)                23 /   37
+//   4096, 32/8 (V 1500, W 64)                            95 /  107
+//   2 x 4096, 8/8 heads (V 1000, W 16)                   55 /   68  (121 before: two waves)
+//   16384, 32/8, near 4096 (V 5700, W 256)             1111 / 1111
+//   8192 dense (V up to 8192, W 128)                    537 /  517
+//   32768, 32/8 (V 5900, W 512)                        2039 / 2088
+//   2 x 32768, 32/8 (V 5900, W 512)                    4005 / 3857
 //   131072, one KV head (V 20000, W 2048)              3091 / 2855
 // At d = 64 the exponentials weigh twice as much per product and 32 rows always
 // win (65536 tokens, 16/4 heads: 3172 / 3490); 128-key blocks from V = 1024 on
@@ -783,10 +786,10 @@ template <int D>
 hipError_t launch_d(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v, void* o,
                     float* lse, hipStream_t stream) {
   const int64_t V = visible_bound(p, sv);
-  const int64_t W = ((int64_t)p.h_q * p.n_q * (sv.ragged ? 1 : p.batch) + 255) / 256;
+  const int64_t W = (int64_t)(p.h_q / p.h_k) * p.n_q / 256;
   hipError_t err;
   if constexpr (D == 128) {
-    if (((V >= 8192 && W >= 256) || (V >= 4096 && W >= 8192)) &&
+    if (((V >= 8192 && W >= 32) || (V >= 4096 && W >= 512)) &&
         list_capacity(p, sv, 256, 128) <= FwdCfg<128, 2, 128>::max_kblocks())
       err = launch_one<128, 2, 128, false>(p, sv, q, k, v, o, lse, stream);
     else

@@ -36,7 +36,39 @@ struct SchedView {
   int32_t n_qt, n_kt;     // QO / KV blocks: of one sequence (fixed lengths) or of the whole batch (ragged)
   int32_t max_qt, max_kt; // QO / KV blocks of the longest sequence
   int32_t ragged, per_seq_win;
+  const uint32_t* order;  // dK/dV columns, longest first (column_order_bytes), or null
 };
+
+// The dK/dV pass has columns of its own: kColKeys keys of one KV head and sequence.
+// Column rows: ceil(N_k / kColKeys) for fixed lengths; in a ragged batch the
+// schedule's KV blocks, of which every (kColKeys / tile_k)-th of a sequence
+// starts a column and the others hold none.
+constexpr int kColKeys = 128;
+inline int32_t column_rows(const cowa_params& p, int32_t n_kt) {
+  return p.cu_seqlens_k ? n_kt : (p.n_k + kColKeys - 1) / kColKeys;
+}
+// Columns of one batch entry (fixed lengths) or of the whole ragged batch.
+inline int64_t column_count(const cowa_params& p) {
+  int64_t rows = 0;
+  if (p.cu_seqlens_k)
+    for (int b = 0; b < p.batch; ++b) rows += (p.cu_seqlens_k[b + 1] - p.cu_seqlens_k[b] + kColKeys - 1) / kColKeys;
+  else
+    rows = (p.n_k + kColKeys - 1) / kColKeys;
+  return rows * p.h_k;
+}
+// Up to kMaxOrdered columns are also listed longest first at the end of the
+// schedule buffer: few workgroups of unequal length leave the device idle at
+// the end unless the long ones start first.  Larger grids have enough rounds
+// (and take their columns in clusters that share an L2).
+constexpr int64_t kMaxOrdered = 1024;
+inline size_t column_order_bytes(const cowa_params& p) {
+  if (p.dtype != COWA_BF16) return 0;  // (no backward)
+  const int64_t n = column_count(p);
+  return n <= kMaxOrdered ? 4 * (size_t)n : 0;
+}
+inline size_t column_order_offset(const cowa_schedule_t* s) {
+  return (s->off_kt_seq + (s->p.cu_seqlens_k ? 4 * (size_t)s->n_kt : 0) + 255) & ~size_t(255);
+}
 
 inline SchedView sched_view(const cowa_schedule_t* s) {
   const char* b = static_cast<const char*>(s->buf);
@@ -56,6 +88,8 @@ inline SchedView sched_view(const cowa_schedule_t* s) {
   v.max_kt = s->max_kt;
   v.ragged = ragged ? 1 : 0;
   v.per_seq_win = (ragged && s->p.windows == nullptr) ? 1 : 0;
+  const size_t off = column_order_offset(s);
+  v.order = off < s->bytes ? reinterpret_cast<const uint32_t*>(b + off) : nullptr;
   return v;
 }
 
@@ -82,29 +116,32 @@ int fwd_bf16_max_kblocks(int head_dim, int tile_k);
 bool fwd_bf16_supported(int head_dim, int tile_q, int tile_k);
 bool bwd_bf16_supported(int head_dim, int tile_q, int tile_k);
 // the dK/dV pass keeps one column's block list in LDS: at most this many query blocks
-int bwd_main_max_qblocks(int head_dim, int tile_k);
+int bwd_main_max_qblocks(int head_dim);
 // the dQ pass keeps one row's block list in LDS: at most this many key blocks
 int bwd_dq_max_kblocks(int head_dim, int tile_k);
 
 hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const void* q, const void* k,
                            const void* v, void* o, float* lse, hipStream_t stream);
 
-// Split of the dK/dV pass's heaviest columns.  Every query that reaches a sink
-// key sees it, so the sink KV blocks have query lists as long as the sequence
-// while every other column holds only its near and long-range runs; walked by
-// one workgroup, a sink column would set the pass's length whenever the other
-// columns do not fill the device for longer (one KV head per device, short or
-// few sequences).  The first S KV blocks of every (sequence, KV head) are
-// therefore walked by P workgroups, each taking a contiguous share of the
-// column's steps and writing float32 partial dK and dV; a reduction kernel
-// sums the P partials of a column in a fixed order (deterministic) and writes
-// bf16.  P = 1: no split.
+// Split of the dK/dV pass's columns into parts.  Every query that reaches a sink
+// key sees it, so the sink columns have query lists as long as the sequence
+// while every other column holds only its near and long-range runs; and where
+// there are few columns, even those leave compute units idle or finish far
+// apart.  A column of several parts is walked by as many workgroups, each
+// taking a contiguous share of its steps and writing float32 partial dK and dV;
+// a second kernel sums the partials in a fixed order (deterministic) and writes
+// bf16.  The first S columns of every (sequence, KV head) have P parts; the
+// others up to PO, of about `target` steps each.  The plan depends on the
+// parameters alone.
 struct BwdSplit {
-  int32_t S = 0, P = 1;  // leading KV blocks split per (sequence, KV head); parts per column
-  int64_t n_cols = 0;    // split columns: sequences x KV heads x S
+  int32_t S = 0, P = 1;   // leading (sink) columns per (sequence, KV head), and their parts
+  int32_t PO = 1;         // most parts of any other column
+  int32_t target = 0;     // steps per part of the others
+  int64_t n_cols = 0;     // sink columns: sequences x KV heads x S
+  int64_t n_all = 0;      // column slots: sequences x KV heads x column rows
 };
-// float32 partial bytes of a column part: dK and dV of one KV block
-inline size_t bwd_part_floats(const cowa_params& p) { return (size_t)2 * p.tile_k * p.head_dim; }
+// floats of a column part: dK and dV of one column
+inline size_t bwd_part_floats(const cowa_params& p) { return (size_t)2 * kColKeys * p.head_dim; }
 
 // Backward workspace: per query row (layout of LSE), nd = -D with
 // D = rowsum(O * dO) (the term of Alg. 2), then nl = -LSE log2(e); then the
@@ -112,12 +149,13 @@ inline size_t bwd_part_floats(const cowa_params& p) { return (size_t)2 * p.tile_
 struct BwdWork {
   float* nd;
   float* nl;
-  float* part;  // [n_cols][P][2][tile_k * head_dim], or null when P = 1
+  float* part;  // sinks [n_cols][P][2][kColKeys * head_dim] if P > 1, then [n_all][PO][...] if PO > 1
   BwdSplit split;
 };
 inline size_t bwd_array_bytes(const cowa_params& p) { return ((size_t)q_rows(p) * sizeof(float) + 255) & ~size_t(255); }
 inline size_t bwd_split_bytes(const cowa_params& p, const BwdSplit& s) {
-  return s.P > 1 ? (((size_t)s.n_cols * s.P * bwd_part_floats(p) * sizeof(float) + 255) & ~size_t(255)) : 0;
+  const size_t parts = (s.P > 1 ? (size_t)s.n_cols * s.P : 0) + (s.PO > 1 ? (size_t)s.n_all * s.PO : 0);
+  return (parts * bwd_part_floats(p) * sizeof(float) + 255) & ~size_t(255);
 }
 inline size_t bwd_workspace_bytes(const cowa_params& p, const BwdSplit& s) {
   return 2 * bwd_array_bytes(p) + bwd_split_bytes(p, s);
@@ -126,7 +164,7 @@ inline BwdWork bwd_work(const cowa_params& p, const BwdSplit& s, void* ws) {
   BwdWork w;
   w.nd = static_cast<float*>(ws);
   w.nl = reinterpret_cast<float*>(static_cast<char*>(ws) + bwd_array_bytes(p));
-  w.part = s.P > 1 ? reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * bwd_array_bytes(p)) : nullptr;
+  w.part = bwd_split_bytes(p, s) > 0 ? reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * bwd_array_bytes(p)) : nullptr;
   w.split = s;
   return w;
 }

@@ -164,6 +164,60 @@ __global__ void sched_fill(SchedArgs a) {
   }
 }
 
+// The dK/dV pass's columns by descending length (query blocks of 64; equal
+// lengths in about ascending order): a counting sort in one workgroup.
+__global__ void __launch_bounds__(1024) sched_order(SchedArgs a, uint32_t* order, int rows) {
+  __shared__ int32_t bin[1024];
+  __shared__ int32_t wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int total = a.p.h_k * rows;
+  const SchedView& sv = a.sv;
+  // bin of column t, longest first; -1: no column starts there
+  auto bin_of = [&](int t) -> int {
+    const int h = t / rows, row = t % rows;
+    int32_t n_q = a.p.n_q, n_k = a.p.n_k, b = 0, k0 = row * kColKeys;
+    if (sv.ragged) {
+      b = sv.kt_seq[row];
+      const SeqDesc sd = sv.seq[b];
+      n_q = sd.n_q;
+      n_k = sd.n_k;
+      k0 = (row - sd.kt_off) * a.p.tile_k;
+      if (k0 % kColKeys != 0) return -1;
+    }
+    const WinDesc w = sv.win[(sv.per_seq_win ? b * a.p.h_k : 0) + h];
+    const Geo32 g = geo32(make_geo_bounds(n_q, n_k, w.sink, w.near, w.lo, w.hi, 64, kColKeys));
+    const int k1 = (k0 + kColKeys < n_k ? k0 + kColKeys : n_k) - 1;
+    const int len = runs3_count(query_block_runs3<64>(g, k0, k1));
+    const int longest = sv.max_qt * (a.p.tile_q / 64 > 0 ? a.p.tile_q / 64 : 1) + 1;
+    const int x = (int)((int64_t)len * 1023 / longest);
+    return 1023 - (x < 1023 ? x : 1023);
+  };
+  bin[tid] = 0;
+  __syncthreads();
+  for (int t = tid; t < total; t += 1024) {
+    const int x = bin_of(t);
+    if (x >= 0) atomicAdd(&bin[x], 1);
+  }
+  __syncthreads();
+  const int mine = bin[tid];
+  int incl = mine;  // inclusive scan over the wave, then over the waves
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int up = __shfl_up(incl, off);
+    if (lane >= off) incl += up;
+  }
+  if (lane == 63) wsum[tid >> 6] = incl;
+  __syncthreads();
+  int before = 0;
+  for (int w = 0; w < (tid >> 6); ++w) before += wsum[w];
+  bin[tid] = before + incl - mine;
+  __syncthreads();
+  for (int t = tid; t < total; t += 1024) {
+    const int x = bin_of(t);
+    if (x >= 0) order[atomicAdd(&bin[x], 1)] = (uint32_t)t;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_schedule(const cowa_schedule_t* s, const void* tables, size_t table_bytes, hipStream_t stream) {
@@ -194,6 +248,9 @@ hipError_t launch_schedule(const cowa_schedule_t* s, const void* tables, size_t 
       hipLaunchKernelGGL(sched_tile_map, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, stream, a);
   }
   const int64_t rows = (int64_t)s->p.h_k * (s->n_qt + s->n_kt);
+  if (a.sv.order != nullptr && s->n_kt > 0)
+    hipLaunchKernelGGL(sched_order, dim3(1), dim3(1024), 0, stream, a, const_cast<uint32_t*>(a.sv.order),
+                       (int)column_rows(s->p, s->n_kt));
   if (rows > 0) {
     hipLaunchKernelGGL(sched_count, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sched_scan, dim3(2), dim3(1024), 0, stream, a);

@@ -186,6 +186,29 @@ __host__ __device__ inline Runs3 key_block_runs3(const Geo32& g, int32_t q0, int
   return r;
 }
 
+// Blocks of BQ queries that hold a legal pair with some key k0 .. k1 (k1 < n_k):
+// bwd_block_ranges for any key range, in 32-bit scalars.
+template <int BQ>
+__host__ __device__ inline Runs3 query_block_runs3(const Geo32& g, int32_t k0, int32_t k1) {
+  const int32_t cmin = g.off, cmax = g.n_k - 1;  // keys at distance 0 of the first / last query
+  auto clip = [&](bool any, int32_t a, int32_t b, int32_t& ra, int32_t& rb) {
+    a = imax32(a, cmin);
+    b = imin32(b, cmax);
+    any = any && a <= b;
+    ra = any ? (a - cmin) / BQ : kNone;
+    rb = any ? (b - cmin) / BQ : kNone - 1;
+  };
+  Runs3 r;
+  clip(g.w_near >= 1, k0, k1 + g.w_near - 1, r.a0, r.b0);
+  clip(g.w_sink >= 1 && k0 < g.w_sink, k0, cmax, r.a1, r.b1);
+  clip(g.hi > g.lo, k0 + g.lo, k1 + g.hi - 1, r.a2, r.b2);
+  runs3_merge(r);
+  return r;
+}
+__host__ __device__ inline int32_t runs3_count(const Runs3& r) {
+  return (r.b0 - r.a0 + 1) + (r.b1 - r.a1 + 1) + (r.b2 - r.a2 + 1);
+}
+
 // Every pair of queries q0 .. q1 and keys k0 .. k1 lies inside the sequence and
 // is legal (tile_full for any query and key range, in 32-bit scalars; bounds
 // clamped to n_k).

@@ -1,4 +1,5 @@
-// Host check of the kernels' own block lists (key_block_runs3, key_block_full)
+// Host check of the kernels' own block lists (key_block_runs3, query_block_runs3,
+// key_block_full)
 // against the element rule: random windows (clamped as the kernels clamp
 // them), every tile of query rows and key blocks; a block is listed iff it
 // holds a legal pair, its ranges ascend without touching, and it is called full
@@ -51,6 +52,37 @@ void check(HeadGeo hg, int R) {
   }
 }
 
+// the query blocks of a key block, likewise
+template <int BQ>
+void check_q(const HeadGeo& hg, int BK) {
+  const Geo32 g = geo32(hg);
+  const int n_qb = (hg.n_q + BQ - 1) / BQ;
+  for (int k0 = 0; k0 < hg.n_k; k0 += BK) {
+    const int k1 = (k0 + BK < hg.n_k ? k0 + BK : hg.n_k) - 1;
+    const Runs3 r = query_block_runs3<BQ>(g, k0, k1);
+    const int a[3] = {r.a0, r.a1, r.a2}, b[3] = {r.b0, r.b1, r.b2};
+    std::vector<char> listed(n_qb, 0);
+    int last = -2, count = 0;
+    for (int x = 0; x < 3; ++x) {
+      if (a[x] == kNone) {
+        bad += b[x] != kNone - 1;
+        continue;
+      }
+      bad += a[x] <= last + 1 || a[x] > b[x] || b[x] >= n_qb;
+      for (int i = a[x]; i <= b[x] && i < n_qb; ++i, ++count) listed[i] = 1;
+      last = b[x];
+    }
+    bad += count != runs3_count(r);
+    for (int i = 0; i < n_qb; ++i) {
+      bool any = false;
+      for (int q = i * BQ; q < i * BQ + BQ; ++q)
+        for (int k = k0; k <= k1; ++k) any |= legal_pair(hg, q, k);
+      bad += any != (bool)listed[i];
+      ++checked;
+    }
+  }
+}
+
 int main() {
   std::mt19937 rng(609);
   auto pick = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
@@ -70,6 +102,8 @@ int main() {
     check<16>(hg, R);
     check<64>(hg, R);
     check<128>(hg, R);
+    check_q<64>(hg, 128);
+    check_q<16>(hg, 64);
   }
   printf("checked %ld mismatches %ld\n", checked, bad);
   return bad == 0 ? 0 : 1;

@@ -193,3 +193,50 @@ def test_bwd_reads_no_rows_past_the_sequence():
     compare("dK", to_host(dk), dk_r)
     compare("dV", to_host(dv), dv_r)
     del qbuf, dobuf
+
+
+@pytest.mark.parametrize("case", [
+    # name, batch, n, h_q, h_k, d, sink, near, tile: the dK/dV pass with ordinary columns in
+    # parts (few columns), its 128-key columns at their edges, and 64-key schedule tiles
+    ("one_column", 1, 128, 4, 1, 128, 4, 64, 128), ("column_edge", 2, 129, 2, 2, 128, 0, 50, 64),
+    ("parts", 1, 1000, 16, 4, 128, 16, 128, 64), ("parts_d64", 1, 1111, 8, 2, 64, 130, 200, 128),
+    ("no_sink", 1, 900, 8, 1, 128, 0, 300, 128), ("no_near", 1, 500, 2, 1, 64, 20, 0, 64),
+    ("many_columns", 3, 2300, 6, 6, 64, 3, 64, 128)], ids=lambda c: c[0])
+def test_bwd_column_parts(case):
+    name, bsz, n, h_q, h_k, d, ws, wn, tile = case
+    w = inputs.custom("bwd_parts_" + name, batch=bsz, n_q=n, n_k=n, h_q=h_q, h_k=h_k, head_dim=d, w_sink=ws,
+                      w_near=wn, tile=tile)
+    _full_check(w, key=inputs.key_of("bwd_parts", name))
+
+
+@pytest.mark.parametrize("ragged", [False, True])
+def test_bwd_columns_past_the_order_table(ragged):
+    """More columns than the order table lists (1024): the dK/dV pass takes them
+    in clusters.  Values against torch's float64 autograd of the masked softmax on
+    the first sequence (the pass has no state across sequences)."""
+    dev = need_gpu()
+    import paper_2609_32704_amd as cowa
+    h, n, d, win = 64, 2113 if not ragged else 700, 64, [(5, 70, 30, 100)] * 64
+    seqs = [n] if not ragged else [n, 1500]
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    q, k, v, do = (torch.randn((h, sum(seqs), d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(4))
+    if ragged:
+        cu = [0, n, sum(seqs)]
+        o, lse = cowa.fwd_varlen(q, k, v, cu, cu, 0, 0, 64, 64, windows=win)
+        dq, dk, dv = cowa.bwd_varlen(q, k, v, o, lse, do, cu, cu, 0, 0, 64, 64, windows=win)
+    else:
+        a = [x[None] for x in (q, k, v, do)]
+        o, lse = cowa.fwd(*a[:3], 0, 0, 64, 64, windows=win)
+        dq, dk, dv = (x[0] for x in cowa.bwd(*a[:3], o, lse, a[3], 0, 0, 64, 64, windows=win))
+    torch.cuda.synchronize()
+    pos = torch.arange(n, device=dev)
+    delta = pos[:, None] - pos[None, :]
+    seen = (delta >= 0) & ((delta < 70) | (pos[None, :] < 5) | ((delta >= 100) & (delta < 200)))
+    for hh in (0, 17, 63):
+        qf, kf, vf = (x[hh, :n].double().requires_grad_(True) for x in (q, k, v))
+        s = (qf @ kf.t()) * d ** -0.5
+        p = torch.softmax(s.masked_fill(~seen, float("-inf")), -1)
+        ref_g = torch.autograd.grad(p @ vf, (qf, kf, vf), do[hh, :n].double())
+        for name, got, want in zip(("dQ", "dK", "dV"), (dq, dk, dv), ref_g):
+            compare(name, to_host(got[hh, :n]), want.cpu().numpy())
