@@ -173,6 +173,14 @@ cowa_status cowa_windows(const cowa_params* p, cowa_window* out_host);
  * Validates the windows and sequence lengths (COWA_ERR_INVALID_ARG). */
 cowa_status cowa_schedule_size(const cowa_params* p, cowa_schedule_t* out);
 
+/* Size a schedule of tables only: what cowa_fwd and cowa_bwd read (windows,
+ * sequences, and, if backward is nonzero, the order in which cowa_bwd takes its
+ * columns), without the block lists of Sec. 2.3, for callers that do not read
+ * those.  Built by cowa_schedule and used like a full schedule; nnz is -1 and the
+ * offsets of the lists mean nothing.  (With backward = 0 the backward runs
+ * too, only in another order.)  Host only, O(h_k + batch). */
+cowa_status cowa_schedule_size_tables(const cowa_params* p, int32_t backward, cowa_schedule_t* out);
+
 /* Work accounting (host only): the number of legal (query, key) pairs of
  * Eq. fwa_support summed over the batch and every QO head.  Attention FLOPs
  * follow from it (App. A.2 and A.3: 4d per pair forward, 10d backward). */

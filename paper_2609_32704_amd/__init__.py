@@ -142,6 +142,19 @@ class Schedule:
         if build:
             _abi.cowa_schedule(self.s, _stream(stream))
 
+    @classmethod
+    def _tables(cls, params, device, stream, backward):
+        """A schedule of the kernels' tables only (no block lists), for calls
+        that build their own and hand it to nobody."""
+        torch = _torch()
+        self = cls.__new__(cls)
+        self.params = params
+        self.s = _abi.cowa_schedule_size_tables(params, backward)
+        self.buf = torch.empty(max(int(self.s.bytes), 256), dtype=torch.uint8, device=device)
+        self.s.buf = self.buf.data_ptr()
+        _abi.cowa_schedule(self.s, _stream(stream))
+        return self
+
     @property
     def nnz(self):
         return int(self.s.nnz)
@@ -221,7 +234,7 @@ def _fwd(p, q, k, v, qs, ks, ls, schedule, out, lse, stream):
     _validate([(q, "q", q.dtype, qs), (k, "k", q.dtype, ks), (v, "v", q.dtype, ks), (out, "out", q.dtype, qs),
                (lse, "lse", torch.float32, ls)])
     if schedule is None:
-        schedule = Schedule(p, q.device, stream)
+        schedule = Schedule._tables(p, q.device, stream, False)
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
@@ -261,7 +274,7 @@ def _bwd(p, q, k, v, o, lse, do, qs, ks, ls, schedule, workspace, dq, dk, dv, st
     if workspace is not None and workspace.numel() < need:
         raise ValueError(f"workspace has {workspace.numel()} bytes, the backward needs {need}")
     if schedule is None:
-        schedule = Schedule(p, q.device, stream)
+        schedule = Schedule._tables(p, q.device, stream, True)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     dq = torch.empty_like(q) if dq is None else dq
@@ -347,14 +360,14 @@ class _Attention:
                     if cq is None:
                         sched_p = make_params(q.shape[0], q.shape[2], k.shape[2], q.shape[1], k.shape[1], q.shape[3],
                                               w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype), h_tot, h_off, wins)
-                        sched = Schedule(sched_p, q.device)
+                        sched = Schedule._tables(sched_p, q.device, None, True)
                         o, lse = fwd(q, k, v, w_sink, w_near, tq, tk, scale, h_tot, h_off, schedule=sched,
                                      windows=wins)
                     else:
                         sched_p = make_params(len(cq) - 1, q.shape[1], k.shape[1], q.shape[0], k.shape[0],
                                               q.shape[2], w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype), h_tot,
                                               h_off, wins, cq, ck)
-                        sched = Schedule(sched_p, q.device)
+                        sched = Schedule._tables(sched_p, q.device, None, True)
                         o, lse = fwd_varlen(q, k, v, cq, ck, w_sink, w_near, tq, tk, scale, h_tot, h_off,
                                             schedule=sched, windows=wins)
                     ctx.save_for_backward(q, k, v, o, lse)

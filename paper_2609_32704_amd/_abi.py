@@ -80,6 +80,7 @@ _SIGNATURES = {
     "cowa_last_error": (ctypes.c_char_p, []),
     "cowa_windows": (ctypes.c_int, [_P(cowa_params), _P(cowa_window)]),
     "cowa_schedule_size": (ctypes.c_int, [_P(cowa_params), _P(cowa_schedule_t)]),
+    "cowa_schedule_size_tables": (ctypes.c_int, [_P(cowa_params), ctypes.c_int32, _P(cowa_schedule_t)]),
     "cowa_schedule": (ctypes.c_int, [_P(cowa_schedule_t), _vp]),
     "cowa_legal_pairs": (ctypes.c_int, [_P(cowa_params), _P(ctypes.c_int64)]),
     "cowa_decode_visible_keys": (ctypes.c_int, [_P(cowa_decode_params), _P(ctypes.c_int32), _P(ctypes.c_int64)]),
@@ -150,8 +151,14 @@ def cowa_schedule_size(params):
     return s
 
 
+def cowa_schedule_size_tables(params, backward):
+    s = cowa_schedule_t()
+    check(lib().cowa_schedule_size_tables(ctypes.byref(params), 1 if backward else 0, ctypes.byref(s)))
+    return s
+
+
 def cowa_schedule(sched, stream):
-    check(lib().cowa_schedule(ctypes.byref(sched), _vp(stream)))
+    check(lib().cowa_schedule(ctypes.byref(sched), stream))
 
 
 def cowa_legal_pairs(params):
@@ -168,8 +175,8 @@ def cowa_decode_visible_keys(dparams, seqlens_host):
 
 
 def cowa_fwd(params, sched, q, k, v, o, lse, stream):
-    check(lib().cowa_fwd(ctypes.byref(params), ctypes.byref(sched), _vp(q), _vp(k), _vp(v), _vp(o), _vp(lse),
-                         _vp(stream)))
+    check(lib().cowa_fwd(ctypes.byref(params), ctypes.byref(sched), q, k, v, o, lse,
+                         stream))
 
 
 def cowa_bwd_workspace_size(params):
@@ -179,23 +186,23 @@ def cowa_bwd_workspace_size(params):
 
 
 def cowa_bwd(params, sched, q, k, v, o, lse, d_o, dq, dk, dv, workspace, ws_bytes, stream):
-    check(lib().cowa_bwd(ctypes.byref(params), ctypes.byref(sched), _vp(q), _vp(k), _vp(v), _vp(o), _vp(lse),
-                         _vp(d_o), _vp(dq), _vp(dk), _vp(dv), _vp(workspace), ws_bytes, _vp(stream)))
+    check(lib().cowa_bwd(ctypes.byref(params), ctypes.byref(sched), q, k, v, o, lse,
+                         d_o, dq, dk, dv, workspace, ws_bytes, stream))
 
 
 def cowa_bwd_prepare(params, o, d_o, lse, workspace, ws_bytes, stream):
-    check(lib().cowa_bwd_prepare(ctypes.byref(params), _vp(o), _vp(d_o), _vp(lse), _vp(workspace), ws_bytes,
-                                 _vp(stream)))
+    check(lib().cowa_bwd_prepare(ctypes.byref(params), o, d_o, lse, workspace, ws_bytes,
+                                 stream))
 
 
 def cowa_bwd_main(params, sched, q, k, v, d_o, dk, dv, workspace, ws_bytes, stream):
-    check(lib().cowa_bwd_main(ctypes.byref(params), ctypes.byref(sched), _vp(q), _vp(k), _vp(v), _vp(d_o),
-                              _vp(dk), _vp(dv), _vp(workspace), ws_bytes, _vp(stream)))
+    check(lib().cowa_bwd_main(ctypes.byref(params), ctypes.byref(sched), q, k, v, d_o,
+                              dk, dv, workspace, ws_bytes, stream))
 
 
 def cowa_bwd_dq(params, sched, q, k, v, d_o, dq, workspace, ws_bytes, stream):
-    check(lib().cowa_bwd_dq(ctypes.byref(params), ctypes.byref(sched), _vp(q), _vp(k), _vp(v), _vp(d_o), _vp(dq),
-                            _vp(workspace), ws_bytes, _vp(stream)))
+    check(lib().cowa_bwd_dq(ctypes.byref(params), ctypes.byref(sched), q, k, v, d_o, dq,
+                            workspace, ws_bytes, stream))
 
 
 def cowa_decode_workspace_size(dparams):
@@ -205,10 +212,10 @@ def cowa_decode_workspace_size(dparams):
 
 
 def cowa_decode(dparams, q, k_cache, v_cache, seqlens_k, o, lse, workspace, ws_bytes, stream):
-    check(lib().cowa_decode(ctypes.byref(dparams), _vp(q), _vp(k_cache), _vp(v_cache), _vp(seqlens_k), _vp(o),
-                            _vp(lse), _vp(workspace), ws_bytes, _vp(stream)))
+    check(lib().cowa_decode(ctypes.byref(dparams), q, k_cache, v_cache, seqlens_k, o,
+                            lse, workspace, ws_bytes, stream))
 
 
 def cowa_decode_noalloc(dparams, q, k_cache, v_cache, seqlens_k, o, lse, stream):
-    check(lib().cowa_decode_noalloc(ctypes.byref(dparams), _vp(q), _vp(k_cache), _vp(v_cache), _vp(seqlens_k),
-                                    _vp(o), _vp(lse), _vp(stream)))
+    check(lib().cowa_decode_noalloc(ctypes.byref(dparams), q, k_cache, v_cache, seqlens_k,
+                                    o, lse, stream))

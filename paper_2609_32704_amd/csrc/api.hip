@@ -395,6 +395,30 @@ cowa_status cowa_windows(const cowa_params* p, cowa_window* out_host) {
   return COWA_OK;
 }
 
+// The tables behind the block lists, from byte offset `off` on.
+static void size_tables(const cowa_params* p, const Layout& L, bool backward, size_t off, cowa_schedule_t* out) {
+  out->p = *p;
+  out->n_qt = L.n_qt;
+  out->n_kt = L.n_kt;
+  out->max_qt = L.max_qt;
+  out->max_kt = L.max_kt;
+  out->digest = L.digest;
+  out->off_windows = off;
+  off = align256(off + sizeof(cowa::WinDesc) * L.win.size());
+  out->off_seqs = off;
+  if (L.ragged) {
+    off = align256(off + sizeof(cowa::SeqDesc) * L.seq.size());
+    out->off_qt_seq = off;
+    off = align256(off + 4 * (size_t)L.n_qt);
+    out->off_kt_seq = off;
+    off = align256(off + 4 * (size_t)L.n_kt);
+  } else {
+    out->off_qt_seq = out->off_kt_seq = off;
+  }
+  out->bytes = off + (backward ? cowa::column_order_bytes(*p) : 0);  // (off is where column_order_offset puts it)
+  out->buf = nullptr;
+}
+
 cowa_status cowa_schedule_size(const cowa_params* p, cowa_schedule_t* out) {
   COWA_TRY(check_params(p));
   if (!out) return fail(COWA_ERR_INVALID_ARG, "out is NULL");
@@ -425,15 +449,9 @@ cowa_status cowa_schedule_size(const cowa_params* p, cowa_schedule_t* out) {
   if ((int64_t)p->h_k * L.n_qt >= (int64_t(1) << 31) || (int64_t)p->h_k * L.n_kt >= (int64_t(1) << 31))
     return fail(COWA_ERR_UNSUPPORTED, "schedule has more than 2^31 rows");
   std::memset(out, 0, sizeof(*out));
-  out->p = *p;
-  out->n_qt = L.n_qt;
-  out->n_kt = L.n_kt;
-  out->max_qt = L.max_qt;
-  out->max_kt = L.max_kt;
   out->max_row = max_row;
   out->max_col = max_col;
   out->nnz = nnz;
-  out->digest = L.digest;
   size_t off = 0;
   out->off_fwd_row_ptr = off;
   off = align256(off + 4 * ((size_t)p->h_k * L.n_qt + 1));
@@ -443,20 +461,20 @@ cowa_status cowa_schedule_size(const cowa_params* p, cowa_schedule_t* out) {
   off = align256(off + 4 * (size_t)nnz);
   out->off_bwd_ent = off;
   off = align256(off + 4 * (size_t)nnz);
-  out->off_windows = off;
-  off = align256(off + sizeof(cowa::WinDesc) * L.win.size());
-  out->off_seqs = off;
-  if (L.ragged) {
-    off = align256(off + sizeof(cowa::SeqDesc) * L.seq.size());
-    out->off_qt_seq = off;
-    off = align256(off + 4 * (size_t)L.n_qt);
-    out->off_kt_seq = off;
-    off = align256(off + 4 * (size_t)L.n_kt);
-  } else {
-    out->off_qt_seq = out->off_kt_seq = off;
-  }
-  out->bytes = off + cowa::column_order_bytes(*p);  // (off is where column_order_offset puts it)
-  out->buf = nullptr;
+  size_tables(p, L, true, off, out);
+  return COWA_OK;
+}
+
+cowa_status cowa_schedule_size_tables(const cowa_params* p, int32_t backward, cowa_schedule_t* out) {
+  COWA_TRY(check_params(p));
+  if (!out) return fail(COWA_ERR_INVALID_ARG, "out is NULL");
+  Layout L;
+  COWA_TRY(resolve_layout(p, &L));
+  if ((int64_t)p->h_k * L.n_qt >= (int64_t(1) << 31) || (int64_t)p->h_k * L.n_kt >= (int64_t(1) << 31))
+    return fail(COWA_ERR_UNSUPPORTED, "schedule has more than 2^31 rows");
+  std::memset(out, 0, sizeof(*out));
+  out->nnz = -1;
+  size_tables(p, L, backward != 0, 0, out);
   return COWA_OK;
 }
 
@@ -529,7 +547,13 @@ cowa_status cowa_schedule(const cowa_schedule_t* s, void* stream) {
   if (!s) return fail(COWA_ERR_INVALID_ARG, "schedule is NULL");
   COWA_TRY(check_params(&s->p));
   cowa_schedule_t ref;
-  COWA_TRY(cowa_schedule_size(&s->p, &ref));
+  if (s->nnz < 0) {
+    // tables only, with or without the column order that the backward uses
+    COWA_TRY(cowa_schedule_size_tables(&s->p, 1, &ref));
+    if (ref.bytes != s->bytes) COWA_TRY(cowa_schedule_size_tables(&s->p, 0, &ref));
+  } else {
+    COWA_TRY(cowa_schedule_size(&s->p, &ref));
+  }
   if (ref.nnz != s->nnz || ref.bytes != s->bytes || ref.n_qt != s->n_qt || ref.n_kt != s->n_kt ||
       ref.off_fwd_ent != s->off_fwd_ent || ref.off_bwd_ent != s->off_bwd_ent ||
       ref.off_bwd_col_ptr != s->off_bwd_col_ptr || ref.off_windows != s->off_windows ||

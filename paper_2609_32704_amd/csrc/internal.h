@@ -24,11 +24,9 @@ struct WinDesc {
 };
 
 // Device view of a built schedule.
+// (The kernels compute their block lists from the windows; the block lists of
+// the buffer are the schedule's own output.)
 struct SchedView {
-  const int32_t* fwd_row_ptr;
-  const int32_t* bwd_col_ptr;
-  const uint32_t* fwd_ent;
-  const uint32_t* bwd_ent;
   const WinDesc* win;     // [n_win][h_k]: n_win = batch for a ragged batch under the default rule, else 1
   const SeqDesc* seq;     // [batch], ragged batches only
   const int32_t* qt_seq;  // [n_qt]: sequence of each QO block, ragged batches only
@@ -74,10 +72,6 @@ inline SchedView sched_view(const cowa_schedule_t* s) {
   const char* b = static_cast<const char*>(s->buf);
   const bool ragged = s->p.cu_seqlens_q != nullptr;
   SchedView v;
-  v.fwd_row_ptr = reinterpret_cast<const int32_t*>(b + s->off_fwd_row_ptr);
-  v.bwd_col_ptr = reinterpret_cast<const int32_t*>(b + s->off_bwd_col_ptr);
-  v.fwd_ent = reinterpret_cast<const uint32_t*>(b + s->off_fwd_ent);
-  v.bwd_ent = reinterpret_cast<const uint32_t*>(b + s->off_bwd_ent);
   v.win = reinterpret_cast<const WinDesc*>(b + s->off_windows);
   v.seq = ragged ? reinterpret_cast<const SeqDesc*>(b + s->off_seqs) : nullptr;
   v.qt_seq = ragged ? reinterpret_cast<const int32_t*>(b + s->off_qt_seq) : nullptr;

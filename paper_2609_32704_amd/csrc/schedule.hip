@@ -4,8 +4,10 @@
 // flagged FULL or partial (only partial blocks need the element mask).
 //
 // Launches on the caller's stream: the host-resolved window table (and, for a
-// ragged batch, the sequence table) copied in through kernel arguments; for a
-// ragged batch the block-to-sequence maps; then per-row counts, an in-place
+// ragged batch, the sequence table) copied in through kernel arguments, the
+// block-to-sequence maps of a ragged batch and the dK/dV pass's column order,
+// which is all that the attention kernels read (and all that a schedule of
+// tables only holds); then the block lists: per-row counts, an in-place
 // prefix sum of the counts (one workgroup per array), and the entry fill (one
 // wave per row or column, lanes writing consecutive entries).
 #include <algorithm>
@@ -45,8 +47,7 @@ struct SchedArgs {
 // block is at or before the block (binary search over the sequence table;
 // sequences without blocks share their first block index with the next one
 // and are skipped by taking the last match).
-__global__ void sched_tile_map(SchedArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline void tile_map(const SchedArgs& a, int64_t t) {
   const int nq = a.sv.n_qt, nk = a.sv.n_kt, nb = a.p.batch;
   if (t >= (int64_t)nq + nk) return;
   const bool qside = t < nq;
@@ -59,6 +60,7 @@ __global__ void sched_tile_map(SchedArgs a) {
   }
   (qside ? a.qt_seq : a.kt_seq)[tile] = lo;
 }
+__global__ void sched_tile_map(SchedArgs a) { tile_map(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x); }
 
 // Geometry of (local KV head h, block row) on the QO (qside) or KV side.
 __device__ inline HeadGeo row_geo(const SchedArgs& a, int h, int row, bool qside, int* tile) {
@@ -165,8 +167,8 @@ __global__ void sched_fill(SchedArgs a) {
 }
 
 // The dK/dV pass's columns by descending length (query blocks of 64; equal
-// lengths in about ascending order): a counting sort in one workgroup.
-__global__ void __launch_bounds__(1024) sched_order(SchedArgs a, uint32_t* order, int rows) {
+// lengths in about ascending order): a counting sort in one workgroup of 1024.
+__device__ inline void column_order(const SchedArgs& a, uint32_t* order, int rows) {
   __shared__ int32_t bin[1024];
   __shared__ int32_t wsum[16];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -218,21 +220,27 @@ __global__ void __launch_bounds__(1024) sched_order(SchedArgs a, uint32_t* order
   }
 }
 
+// Everything the kernels read, in one launch of one workgroup where it is small
+// (a training or prefill call that builds its own tables is launch-bound here):
+// the tables from the kernel arguments (put.n words), then, from them, the
+// block-to-sequence maps (map) and the column order (order, or null).
+__global__ void __launch_bounds__(1024) sched_tables(SchedArgs a, PutArgs put, int map, uint32_t* order, int rows) {
+  const int tid = threadIdx.x;
+  if (tid < put.n) put.dst[tid] = put.w[tid];
+  __threadfence_block();
+  __syncthreads();
+  if (map) {
+    for (int64_t t = tid; t < (int64_t)a.sv.n_qt + a.sv.n_kt; t += 1024) tile_map(a, t);
+    __threadfence_block();
+    __syncthreads();
+  }
+  if (order != nullptr) column_order(a, order, rows);
+}
+
 }  // namespace
 
 hipError_t launch_schedule(const cowa_schedule_t* s, const void* tables, size_t table_bytes, hipStream_t stream) {
   char* b = static_cast<char*>(s->buf);
-  // the tables: words [off_windows, off_windows + table_bytes) of the buffer
-  const uint32_t* words = static_cast<const uint32_t*>(tables);
-  const size_t n_words = table_bytes / 4;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(b + s->off_windows);
-  for (size_t w0 = 0; w0 < n_words; w0 += kPutWords) {
-    PutArgs pa;
-    pa.dst = dst + w0;
-    pa.n = (int32_t)std::min<size_t>(kPutWords, n_words - w0);
-    std::memcpy(pa.w, words + w0, 4 * (size_t)pa.n);
-    hipLaunchKernelGGL(put_words, dim3(1), dim3(512), 0, stream, pa);
-  }
   SchedArgs a;
   a.p = s->p;
   a.sv = sched_view(s);
@@ -242,22 +250,48 @@ hipError_t launch_schedule(const cowa_schedule_t* s, const void* tables, size_t 
   a.bwd_ent = reinterpret_cast<uint32_t*>(b + s->off_bwd_ent);
   a.qt_seq = reinterpret_cast<int32_t*>(b + s->off_qt_seq);
   a.kt_seq = reinterpret_cast<int32_t*>(b + s->off_kt_seq);
-  if (a.sv.ragged) {
-    const int64_t tiles = (int64_t)s->n_qt + s->n_kt;
-    if (tiles > 0)
-      hipLaunchKernelGGL(sched_tile_map, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, stream, a);
+  // the tables: words [off_windows, off_windows + table_bytes) of the buffer;
+  // all but the last kPutWords of a long table go in launches of their own
+  const uint32_t* words = static_cast<const uint32_t*>(tables);
+  size_t n_words = table_bytes / 4;
+  uint32_t* dst = reinterpret_cast<uint32_t*>(b + s->off_windows);
+  PutArgs pa;
+  auto put = [&]() {
+    pa.dst = dst;
+    pa.n = (int32_t)std::min<size_t>(kPutWords, n_words);
+    std::memcpy(pa.w, words, 4 * (size_t)pa.n);
+    words += pa.n;
+    dst += pa.n;
+    n_words -= (size_t)pa.n;
+  };
+  while (n_words > (size_t)kPutWords) {
+    put();
+    hipLaunchKernelGGL(put_words, dim3(1), dim3(512), 0, stream, pa);
   }
+  put();
+  // maps of more than 8192 blocks take the whole device (one workgroup needs
+  // about 1 us per 1024 blocks)
+  const int64_t tiles = a.sv.ragged ? (int64_t)s->n_qt + s->n_kt : 0;
+  const bool small_map = tiles <= 8192;
+  uint32_t* order = s->n_kt > 0 ? const_cast<uint32_t*>(a.sv.order) : nullptr;
+  const int col_rows = (int)column_rows(s->p, s->n_kt);
+  hipLaunchKernelGGL(sched_tables, dim3(1), dim3(1024), 0, stream, a, pa, tiles > 0 && small_map ? 1 : 0,
+                     small_map ? order : nullptr, col_rows);
+  if (!small_map) {
+    hipLaunchKernelGGL(sched_tile_map, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, stream, a);
+    if (order != nullptr) {
+      pa.n = 0;
+      hipLaunchKernelGGL(sched_tables, dim3(1), dim3(1024), 0, stream, a, pa, 0, order, col_rows);
+    }
+  }
+  if (s->nnz < 0) return hipGetLastError();  // tables only
   const int64_t rows = (int64_t)s->p.h_k * (s->n_qt + s->n_kt);
-  if (a.sv.order != nullptr && s->n_kt > 0)
-    hipLaunchKernelGGL(sched_order, dim3(1), dim3(1024), 0, stream, a, const_cast<uint32_t*>(a.sv.order),
-                       (int)column_rows(s->p, s->n_kt));
   if (rows > 0) {
     hipLaunchKernelGGL(sched_count, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sched_scan, dim3(2), dim3(1024), 0, stream, a);
     hipLaunchKernelGGL(sched_fill, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, a);
   } else {
     // no blocks at all: the two row-pointer arrays are the single word 0
-    PutArgs pa;
     pa.n = 1;
     pa.w[0] = 0;
     pa.dst = reinterpret_cast<uint32_t*>(a.fwd_row_ptr);

@@ -401,3 +401,21 @@ def test_decode_noalloc_rejects_steps_beyond_its_scratch():
     fits = cowa.make_decode_params(64, 32, 8, 128, 131072, 128, 4096)
     assert abi.cowa_decode_workspace_size(fits) <= 32 << 20
     assert lib.cowa_decode_noalloc(ctypes.byref(fits), *[vp(ok)] * 6, vp(0)) == abi.COWA_ERR_NO_DEVICE
+
+
+@pytest.mark.parametrize("cu", [None, [0, 100, 100, 1000]])
+def test_tables_only_schedule_size(cu):
+    """A schedule of tables only has the block counts and digest of the full one and
+    no lists; the backward's column order (128-key columns, 4 bytes each) is
+    optional."""
+    b, n = (2, 1000) if cu is None else (3, 1000)
+    p = cowa.make_params(b, n, n, 4, 2, 64, 3, 50, 64, 64, cu_seqlens_q=cu, cu_seqlens_k=cu)
+    full, with_order, without = abi.cowa_schedule_size(p), abi.cowa_schedule_size_tables(p, True), \
+        abi.cowa_schedule_size_tables(p, False)
+    for t in (with_order, without):
+        assert t.nnz == -1
+        assert (t.n_qt, t.n_kt, t.max_qt, t.max_kt, t.digest) == (full.n_qt, full.n_kt, full.max_qt, full.max_kt,
+                                                                  full.digest)
+        assert t.bytes < full.bytes
+    cols = 2 * 8 if cu is None else 2 * (1 + 0 + 8)
+    assert with_order.bytes - without.bytes == 4 * cols

@@ -240,3 +240,15 @@ def test_bwd_columns_past_the_order_table(ragged):
         ref_g = torch.autograd.grad(p @ vf, (qf, kf, vf), do[hh, :n].double())
         for name, got, want in zip(("dQ", "dK", "dV"), (dq, dk, dv), ref_g):
             compare(name, to_host(got[hh, :n]), want.cpu().numpy())
+
+
+def test_autograd_checks_what_saved_tensor_hooks_return():
+    """A saved-tensor hook that leaves the tensors on the host is refused before
+    anything reaches the GPU."""
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    q, k, v = (torch.randn((1, 2, 200, 64), device=dev).to(torch.bfloat16).requires_grad_(True) for _ in range(3))
+    with torch.autograd.graph.saved_tensors_hooks(lambda x: x.cpu(), lambda x: x):
+        o = cowa.attention(q, k, v, 4, 32)
+    with pytest.raises(ValueError, match="device tensor"):
+        o.sum().backward()

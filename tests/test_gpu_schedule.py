@@ -98,3 +98,39 @@ def test_schedule_tuples(tuples):
     for n_q, n_k, tq, tk in ((333, 1000, 64, 128), (1000, 1000, 128, 32)):
         p = cowa.make_params(1, n_q, n_k, 3, 3, 128, 4, 20, tq, tk, windows=tuples)
         _check_general(p, oracle_schedule.build(n_q, n_k, tq, tk, 4, 20, 3, windows=tuples))
+
+
+@pytest.mark.parametrize("name,lens,tile", [
+    # fixed lengths (None); a ragged batch in one launch; one whose tables need several
+    # launches (480 words each) and, with it, more than 8192 blocks in its maps
+    ("fixed", None, 64), ("ragged", [300, 1, 777, 0, 64], 64), ("many", [40] * 300, 64), ("long_maps", [131] * 2100, 64)])
+def test_tables_only_schedule_serves_like_a_full_one(name, lens, tile):
+    """cowa_schedule_size_tables + cowa_schedule give the kernels the same tables as a
+    full schedule: O, LSE and gradients are bitwise equal."""
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(17)
+    h_q, h_k, d, n = 2, 1, 64, sum(lens) if lens else 1000
+
+    def randn(h):
+        shape = (h, n, d) if lens else (1, h, n, d)
+        return torch.randn(shape, generator=gen, device=dev).to(torch.bfloat16)
+
+    q, k, v, do = randn(h_q), randn(h_k), randn(h_k), randn(h_q)
+    cu = None if lens is None else [sum(lens[:i]) for i in range(len(lens) + 1)]
+    p = cowa.make_params(1 if lens is None else len(lens), n, n, h_q, h_k, d, 3, 50, tile, tile, cu_seqlens_q=cu,
+                         cu_seqlens_k=cu)
+    log(f"tables only: {name} n={n} sequences={1 if lens is None else len(lens)}")
+    out = []
+    for sched in (cowa.Schedule(p, dev), cowa.Schedule._tables(p, dev, None, True)):
+        a = (3, 50, tile, tile)
+        if lens is None:
+            o, lse = cowa.fwd(q, k, v, *a, schedule=sched)
+            out.append((o, lse) + cowa.bwd(q, k, v, o, lse, do, *a, schedule=sched))
+        else:
+            o, lse = cowa.fwd_varlen(q, k, v, cu, cu, *a, schedule=sched)
+            out.append((o, lse) + cowa.bwd_varlen(q, k, v, o, lse, do, cu, cu, *a, schedule=sched))
+    torch.cuda.synchronize()
+    for x, y in zip(*out):
+        assert torch.equal(x, y) and not torch.isnan(x).any().item()
