@@ -124,8 +124,12 @@ def windows(params):
 
 
 def _stream(stream):
+    if stream is not None:
+        return stream
+    # (the raw handle of torch.cuda.current_stream(), without making its Stream
+    # object: 0.5 us instead of 7)
     torch = _torch()
-    return torch.cuda.current_stream().cuda_stream if stream is None else stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class Schedule:
@@ -186,7 +190,7 @@ def _validate(specs):
             raise ValueError(f"{name} must be a torch.Tensor")
         if t.dtype != dtype:
             raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:  # (a torch.Size compares with a tuple)
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
         if not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
@@ -353,28 +357,30 @@ class _Attention:
             torch = _torch()
 
             class CowaAttentionFn(torch.autograd.Function):
+                # The parameters and the kernels' tables are made once in the
+                # forward and serve the backward of the same call.
                 @staticmethod
                 def forward(ctx, q, k, v, cfg):
                     q, k, v = q.contiguous(), k.contiguous(), v.contiguous()
                     w_sink, w_near, tq, tk, scale, h_tot, h_off, wins, cq, ck = cfg
                     if cq is None:
-                        sched_p = make_params(q.shape[0], q.shape[2], k.shape[2], q.shape[1], k.shape[1], q.shape[3],
-                                              w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype), h_tot, h_off, wins)
-                        sched = Schedule._tables(sched_p, q.device, None, True)
-                        o, lse = fwd(q, k, v, w_sink, w_near, tq, tk, scale, h_tot, h_off, schedule=sched,
-                                     windows=wins)
+                        bsz, h_q, n_q, d, h_k, n_k = _dims(q, k)
+                        qs, ks, ls = (bsz, h_q, n_q, d), (bsz, h_k, n_k, d), (bsz, h_q, n_q)
                     else:
-                        sched_p = make_params(len(cq) - 1, q.shape[1], k.shape[1], q.shape[0], k.shape[0],
-                                              q.shape[2], w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype), h_tot,
-                                              h_off, wins, cq, ck)
-                        sched = Schedule._tables(sched_p, q.device, None, True)
-                        o, lse = fwd_varlen(q, k, v, cq, ck, w_sink, w_near, tq, tk, scale, h_tot, h_off,
-                                            schedule=sched, windows=wins)
+                        bsz, h_q, n_q, d, h_k, n_k, cq, ck = _dims_varlen(q, k, cq, ck)
+                        qs, ks, ls = (h_q, n_q, d), (h_k, n_k, d), (h_q, n_q)
+                    p = make_params(bsz, n_q, n_k, h_q, h_k, d, w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype),
+                                    h_tot, h_off, wins, cq, ck)
+                    _validate([(q, "q", q.dtype, qs), (k, "k", q.dtype, ks), (v, "v", q.dtype, ks)])
+                    sched = Schedule._tables(p, q.device, None, True)
+                    o = torch.empty_like(q)
+                    lse = torch.empty(ls, dtype=torch.float32, device=q.device)
+                    _abi.cowa_fwd(p, sched.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
+                                  _stream(None))
                     ctx.save_for_backward(q, k, v, o, lse)
                     ctx.mark_non_differentiable(lse)
                     ctx.set_materialize_grads(False)
-                    ctx.cfg = cfg
-                    ctx.sched = sched
+                    ctx.plan = (p, sched, qs, ks, ls)
                     return o, lse
 
                 @staticmethod
@@ -382,13 +388,17 @@ class _Attention:
                     q, k, v, o, lse = ctx.saved_tensors
                     if d_o is None:
                         return None, None, None, None
-                    w_sink, w_near, tq, tk, scale, h_tot, h_off, wins, cq, ck = ctx.cfg
-                    if cq is None:
-                        dq, dk, dv = bwd(q, k, v, o, lse, d_o.contiguous(), w_sink, w_near, tq, tk, scale, h_tot,
-                                         h_off, schedule=ctx.sched, windows=wins)
-                    else:
-                        dq, dk, dv = bwd_varlen(q, k, v, o, lse, d_o.contiguous(), cq, ck, w_sink, w_near, tq, tk,
-                                                scale, h_tot, h_off, schedule=ctx.sched, windows=wins)
+                    # (saved-tensor hooks may hand back other tensors than the forward saved)
+                    p, sched, qs, ks, ls = ctx.plan
+                    d_o = d_o.contiguous()
+                    _validate([(q, "q", q.dtype, qs), (k, "k", q.dtype, ks), (v, "v", q.dtype, ks),
+                               (o, "o", q.dtype, qs), (d_o, "do", q.dtype, qs), (lse, "lse", torch.float32, ls)])
+                    need = _abi.cowa_bwd_workspace_size(p)
+                    workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+                    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+                    _abi.cowa_bwd(p, sched.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
+                                  d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), workspace.data_ptr(),
+                                  workspace.numel(), _stream(None))
                     return dq, dk, dv, None
 
             cls.fn = CowaAttentionFn
