@@ -147,7 +147,9 @@ typedef struct {
   int32_t w_sink, w_near; /* >= 0 */
   int32_t h_k_total, h_k_offset;
   int32_t split_keys;     /* visible keys per split program (a multiple of 64); 0 = library
-                             default: ~1024 programs in total, each >= 256 keys */
+                             default: ~1024 programs in total, each >= 128 keys at
+                             head_dim 128 (twice that at 64 or for groups of 8), and
+                             each sequence divided evenly over its programs */
   float softmax_scale;    /* > 0 */
   int32_t dtype;          /* COWA_BF16 */
   const cowa_window* windows;  /* NULL: default rule from each sequence's N_k; else h_k host

@@ -3,15 +3,16 @@
 //
 // Split kernel: one workgroup per (split s, local KV head h, sequence b).  The
 // visible keys of (b, h) are the merged key runs of sink, long-range window and
-// near window; split s takes positions [s * SK, (s + 1) * SK) of that ascending
-// list.  Loads are 16-byte and coalesced: a 64-lane wave reads whole K and V
-// rows (d/8 lanes per row), so every wave step streams a contiguous run of
-// cache rows.  Each lane group keeps, for each of the G QO heads of the group,
-// an online-softmax state (m, l, O slice) in registers; the workgroup merges
-// its 4 x (64 / (d/8)) states and writes one partial (m, l, O) per QO head.
+// near window; split s takes an even share of that ascending list (or positions
+// [s * SK, (s + 1) * SK) for a caller's split size SK).  Loads are 16-byte and
+// coalesced: a 64-lane wave reads whole K and V rows (d/8 lanes per row), and
+// the next iteration's rows are in flight while one is computed.  Each lane
+// group keeps, for each of the G QO heads of the group, an online-softmax state
+// (m, l, O slice) in registers; the workgroup merges its 4 x (64 / (d/8)) states
+// and writes one partial (m, l, O) per QO head, or, with one split, the result.
 //
-// Combine kernel: one 64-lane wave per (sequence, QO head) merges the split
-// partials (max of m, rescaled sums) and writes O and the natural-log LSE.
+// Combine kernel: merges the split partials of a (sequence, QO head) (max of m,
+// rescaled sums) and writes O and the natural-log LSE.
 // Everything is fp32 apart from the bf16 loads; scores are kept in base 2.
 #include <map>
 #include <mutex>
@@ -22,12 +23,14 @@
 namespace cowa {
 namespace {
 
-constexpr int kDefaultSplitKeys = 256;   // smallest default split
-constexpr int64_t kTargetPrograms = 1024;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 constexpr int kHeadsPerLaunch = 32;  // explicit windows travel in the kernel arguments, 32 heads at a time
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 struct DecArgs {
   const __bf16* q;
@@ -39,6 +42,7 @@ struct DecArgs {
   float* part_o;   // [B][H_q][S][D]
   float* part_ml;  // [B][H_q][S][2]
   int32_t batch, h_q, h_k, n_max, w_sink, w_near, h_total, h_offset, splits, split_keys;
+  int32_t even;  // split each sequence's visible keys evenly over the splits (else split_keys each)
   float c;  // softmax_scale * log2(e)
   int32_t explicit_win;            // windows below (else the default rule from each sequence's N_k)
   int32_t head_base;               // first local KV head of this launch
@@ -74,12 +78,13 @@ __device__ inline uint4 ld_stream16(const __bf16* ptr) {
   return make_uint4(t.x, t.y, t.z, t.w);
 }
 
-template <int D, int G>
+// ONE: one split, whose workgroup writes O and LSE itself (no combine launch).
+template <int D, int G, bool ONE>
 __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
   constexpr int DC = D / 8;               // lanes per cache row (16-byte chunks)
   constexpr int KG = 64 / DC;             // rows per wave load instruction
   constexpr int STEP = 4 * KG;            // keys per workgroup step (4 waves)
-  constexpr int U = G >= 8 ? 4 : 8;       // steps in flight per iteration
+  constexpr int U = 4;                    // steps per iteration (two iterations' rows in flight)
   __shared__ float sm_m[4][G], sm_l[4][G];
   __shared__ float sm_o[4][G][D];
 
@@ -102,8 +107,10 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
     runs = key_runs3(n_k, min(w.sink, n_k), min(w.near, n_k), min(w.lo, n_k), min(w.hi, n_k));
   }
   const int32_t total = (runs.b0 - runs.a0 + 1) + (runs.b1 - runs.a1 + 1) + (runs.b2 - runs.a2 + 1);
-  const int32_t v0 = s * a.split_keys;
-  const int32_t v1 = min(v0 + a.split_keys, total);
+  // an even share in whole iterations of four waves' rows, or the caller's size
+  const int32_t sk = a.even ? ((total + a.splits - 1) / a.splits + STEP - 1) / STEP * STEP : a.split_keys;
+  const int32_t v0 = s * sk;
+  const int32_t v1 = min(v0 + sk, total);
 
   // query chunk of each QO head as packed bf16 pairs (dot products in fp32)
   uint32_t qp[G][4];
@@ -126,69 +133,72 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
   const __bf16* vbase = a.vc + head_off + dc * 8;
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-  // the split's visible positions [v0, v1) cover at most three contiguous key
-  // runs; each run is streamed as a contiguous key range
-  int32_t off = 0;
+  // The split's visible positions [v0, v1), U steps of STEP keys per iteration;
+  // a position's key follows from the (at most three) runs by selects, so runs
+  // neither cut iterations short nor need loops of their own.  The next
+  // iteration's rows are loaded before the current one is computed.
+  const int32_t n0 = runs.b0 - runs.a0 + 1, n1 = n0 + runs.b1 - runs.a1 + 1;
+  const int32_t d0 = runs.a0, d1 = runs.a1 - n0, d2 = runs.a2 - n1;
+  auto load = [&](int32_t vb, uint4 (&kr)[U], uint4 (&vr)[U]) {
 #pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    const int32_t ra = r == 0 ? runs.a0 : r == 1 ? runs.a1 : runs.a2;
-    const int32_t rb = r == 0 ? runs.b0 : r == 1 ? runs.b1 : runs.b2;
-    if (ra == kNone) break;
-    const int32_t len = rb - ra + 1;
-    const int32_t lo = max(v0, off), hi = min(v1, off + len);
-    off += len;
-    if (lo >= hi) continue;
-    const int32_t k_lo = ra + (lo - off + len), k_hi = ra + (hi - off + len);  // keys [k_lo, k_hi)
-    for (int32_t kb = k_lo; kb < k_hi; kb += STEP * U) {
-      uint4 kr[U], vr[U];
-      bool ok[U];
+    for (int u = 0; u < U; ++u) {
+      const int32_t pv = min(vb + u * STEP + wave * KG + kg, v1 - 1);
+      const int64_t key = pv + (pv < n0 ? d0 : pv < n1 ? d1 : d2);
+      kr[u] = ld_stream16(kbase + key * D);
+      vr[u] = ld_stream16(vbase + key * D);
+    }
+  };
+  auto compute = [&](int32_t vb, const uint4 (&kr)[U], const uint4 (&vr)[U]) {
+    float sc[U][G];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int32_t key = kb + u * STEP + wave * KG + kg;
-        ok[u] = key < k_hi;
-        const int64_t kc = ok[u] ? key : k_hi - 1;
-        kr[u] = ld_stream16(kbase + kc * D);
-        vr[u] = ld_stream16(vbase + kc * D);
-      }
-      float sc[U][G];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t kw[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float part = 0.f;
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qp[g][t]),
-                                                   __builtin_bit_cast(bf16x2, kw[t]), part, false);
-          part = group_sum<DC>(part);
-          sc[u][g] = ok[u] ? part * a.c : -INFINITY;
-        }
-      }
+    for (int u = 0; u < U; ++u) {
+      const bool ok = vb + u * STEP + wave * KG + kg < v1;
+      const uint32_t kw[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        float mx = sc[0][g];
+        float part = 0.f;
 #pragma unroll
-        for (int u = 1; u < U; ++u) mx = fmaxf(mx, sc[u][g]);
-        const float m_new = fmaxf(m[g], mx);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m[g] - m_use);
-        l[g] *= alpha;
+        for (int t = 0; t < 4; ++t)
+          part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qp[g][t]),
+                                                 __builtin_bit_cast(bf16x2, kw[t]), part, false);
+        part = group_sum<DC>(part);
+        sc[u][g] = ok ? part * a.c : -INFINITY;
+      }
+    }
 #pragma unroll
-        for (int t = 0; t < 8; ++t) acc[g][t] *= alpha;
-        m[g] = m_new;
+    for (int g = 0; g < G; ++g) {
+      float mx = sc[0][g];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float p = __builtin_amdgcn_exp2f(sc[u][g] - m_use);
-          l[g] += p;
-          const uint32_t vw[4] = {vr[u].x, vr[u].y, vr[u].z, vr[u].w};
+      for (int u = 1; u < U; ++u) mx = fmaxf(mx, sc[u][g]);
+      const float m_new = fmaxf(m[g], mx);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m[g] - m_use);
+      l[g] *= alpha;
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            acc[g][2 * t] = fmaf(p, __uint_as_float(vw[t] << 16), acc[g][2 * t]);
-            acc[g][2 * t + 1] = fmaf(p, __uint_as_float(vw[t] & 0xffff0000u), acc[g][2 * t + 1]);
-          }
+      for (int t = 0; t < 8; ++t) acc[g][t] *= alpha;
+      m[g] = m_new;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float p = __builtin_amdgcn_exp2f(sc[u][g] - m_use);
+        l[g] += p;
+        const uint32_t vw[4] = {vr[u].x, vr[u].y, vr[u].z, vr[u].w};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          acc[g][2 * t] = fmaf(p, __uint_as_float(vw[t] << 16), acc[g][2 * t]);
+          acc[g][2 * t + 1] = fmaf(p, __uint_as_float(vw[t] & 0xffff0000u), acc[g][2 * t + 1]);
         }
       }
+    }
+  };
+  if (v0 < v1) {
+    uint4 ka[U], va[U], kb[U], vb[U];
+    load(v0, ka, va);
+    for (int32_t x = v0; x < v1; x += 2 * STEP * U) {
+      if (x + STEP * U < v1) load(x + STEP * U, kb, vb);
+      compute(x, ka, va);
+      if (x + STEP * U >= v1) break;
+      if (x + 2 * STEP * U < v1) load(x + 2 * STEP * U, ka, va);
+      compute(x + STEP * U, kb, vb);
     }
   }
 
@@ -236,6 +246,12 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
       ov = fmaf(sm_o[r][g][d], f, ov);
       lv = fmaf(sm_l[r][g], f, lv);
     }
+    if constexpr (ONE) {
+      const int64_t orow = (int64_t)b * a.h_q + hk * G + g;
+      a.o[orow * D + d] = (__bf16)(lv > 0.f ? ov / lv : 0.f);
+      if (d == 0) a.lse[orow] = lv > 0.f ? (mm + __log2f(lv)) * kLn2 : -INFINITY;
+      continue;
+    }
     const int64_t pidx = part_base + (int64_t)g * a.splits;  // [b][hk*G + g][s]
     a.part_o[pidx * D + d] = ov;
     if (d == 0) {
@@ -245,33 +261,79 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
   }
 }
 
-// One wave per (sequence, QO head); lanes own D/64 output elements each.
-template <int D>
-__global__ void __launch_bounds__(256) decode_combine(DecArgs a) {
-  constexpr int PER = D / 64;
-  const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (wave >= a.batch * a.h_q) return;
-  const int64_t base = (int64_t)wave * a.splits;
+// Merge of the split partials of one (sequence, QO head) by W waves: D / 4 lanes
+// hold a 16-byte slice of a partial each, so a wave takes 256 / D partials at a
+// time (four loads in flight), and the lane groups' and waves' sums meet by
+// shuffles and in LDS.  Up to 8 splits one wave is enough (four heads per
+// workgroup), up to 64 four, then sixteen: a serial walk of the splits by one
+// wave is latency-bound (131072 cached tokens of one sequence, 79 splits: the
+// step took 46 us with it, 26 without).
+template <int D, int W>
+__global__ void __launch_bounds__(W > 4 ? 64 * W : 256) decode_combine(DecArgs a) {
+  constexpr int L = D / 4, PER = 64 / L;  // lanes per partial, partials per wave load
+  __shared__ f32x4 sm_o[W][L];
+  __shared__ float sm_l[W];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int row = W == 1 ? (int)(blockIdx.x * 4 + wave) : (int)blockIdx.x;
+  if (row >= a.batch * a.h_q) return;  // (uniform in a workgroup when W > 1)
+  const int w = W == 1 ? 0 : wave;
+  const int64_t base = (int64_t)row * a.splits;
+  const f32x2* ml = reinterpret_cast<const f32x2*>(a.part_ml) + base;
   float mm = -INFINITY;
-  for (int s = lane; s < a.splits; s += 64) mm = fmaxf(mm, a.part_ml[(base + s) * 2]);
+  for (int s = lane; s < a.splits; s += 64) mm = fmaxf(mm, ml[s][0]);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) mm = fmaxf(mm, __shfl_xor(mm, off));
   const float mu = mm == -INFINITY ? 0.f : mm;
-  float ov[PER], lv = 0.f;
+  const int grp = lane / L, ch = lane % L;
+  f32x4 ov = {0.f, 0.f, 0.f, 0.f};
+  float lv = 0.f;
+  const f32x4* po = reinterpret_cast<const f32x4*>(a.part_o) + base * L + ch;
+  for (int s0 = w * PER + grp; s0 < a.splits; s0 += W * PER * 4) {
+    f32x4 x[4];
+    f32x2 y[4];
 #pragma unroll
-  for (int t = 0; t < PER; ++t) ov[t] = 0.f;
-  for (int s = 0; s < a.splits; ++s) {
-    const float ms = a.part_ml[(base + s) * 2];
-    const float f = __builtin_amdgcn_exp2f(ms - mu);
-    lv = fmaf(a.part_ml[(base + s) * 2 + 1], f, lv);
+    for (int u = 0; u < 4; ++u) {
+      const int s = s0 + u * W * PER;
+      const bool ok = s < a.splits;
+      x[u] = po[(int64_t)(ok ? s : s0) * L];
+      y[u] = ml[ok ? s : s0];
+      if (!ok) y[u] = f32x2{-INFINITY, 0.f};
+    }
 #pragma unroll
-    for (int t = 0; t < PER; ++t) ov[t] = fmaf(a.part_o[(base + s) * D + lane * PER + t], f, ov[t]);
+    for (int u = 0; u < 4; ++u) {
+      const float f = __builtin_amdgcn_exp2f(y[u][0] - mu);
+      lv = fmaf(y[u][1], f, lv);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ov[e] = fmaf(x[u][e], f, ov[e]);
+    }
+  }
+#pragma unroll
+  for (int off = L; off < 64; off <<= 1) {
+    lv += __shfl_xor(lv, off);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ov[e] += __shfl_xor(ov[e], off);
+  }
+  if constexpr (W > 1) {
+    if (lane < L) sm_o[wave][ch] = ov;
+    if (lane == 0) sm_l[wave] = lv;
+    __syncthreads();
+    if (wave != 0) return;
+    lv = 0.f;
+    ov = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < W; ++r) {
+      lv += sm_l[r];
+      ov += sm_o[r][ch];
+    }
   }
   const float inv = lv > 0.f ? 1.f / lv : 0.f;
+  if (lane < L) {
+    bf16x4 r;
 #pragma unroll
-  for (int t = 0; t < PER; ++t) a.o[(int64_t)wave * D + lane * PER + t] = (__bf16)(ov[t] * inv);
-  if (lane == 0) a.lse[wave] = lv > 0.f ? (mm + __log2f(lv)) * kLn2 : -INFINITY;
+    for (int e = 0; e < 4; ++e) r[e] = (__bf16)(ov[e] * inv);
+    *reinterpret_cast<bf16x4*>(a.o + (int64_t)row * D + ch * 4) = r;
+  }
+  if (lane == 0) a.lse[row] = lv > 0.f ? (mm + __log2f(lv)) * kLn2 : -INFINITY;
 }
 
 // An upper bound of the visible keys of any (sequence, KV head): sink + near +
@@ -292,12 +354,13 @@ int32_t max_visible(const cowa_decode_params& p) {
   return (int32_t)(v < p.n_max ? v : p.n_max);
 }
 
-template <int D, int G>
-hipError_t launch_dg(DecArgs a, const cowa_window* windows, hipStream_t stream) {
+template <int D, int G, bool ONE>
+hipError_t launch_split(DecArgs a, const cowa_window* windows, hipStream_t stream) {
+  auto kern = decode_split<D, G, ONE>;
   if (!windows) {
     a.explicit_win = 0;
     a.head_base = 0;
-    hipLaunchKernelGGL((decode_split<D, G>), dim3(a.splits, a.h_k, a.batch), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(kern, dim3(a.splits, a.h_k, a.batch), dim3(256), 0, stream, a);
   } else {
     a.explicit_win = 1;
     for (int h0 = 0; h0 < a.h_k; h0 += kHeadsPerLaunch) {
@@ -308,29 +371,48 @@ hipError_t launch_dg(DecArgs a, const cowa_window* windows, hipStream_t stream) 
         const int64_t lo = (int64_t)w.near + w.gap, hi = lo + w.width, cap = int64_t(1) << 30;
         a.win[x] = WinDesc{w.sink, w.near, (int32_t)(lo < cap ? lo : cap), (int32_t)(hi < cap ? hi : cap)};
       }
-      hipLaunchKernelGGL((decode_split<D, G>), dim3(a.splits, nh, a.batch), dim3(256), 0, stream, a);
+      hipLaunchKernelGGL(kern, dim3(a.splits, nh, a.batch), dim3(256), 0, stream, a);
     }
   }
-  const int waves = a.batch * a.h_q;
-  hipLaunchKernelGGL(decode_combine<D>, dim3((waves + 3) / 4), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+template <int D, int G>
+hipError_t launch_dg(const DecArgs& a, const cowa_window* windows, hipStream_t stream) {
+  if (a.splits == 1) return launch_split<D, G, true>(a, windows, stream);
+  const hipError_t err = launch_split<D, G, false>(a, windows, stream);
+  if (err != hipSuccess) return err;
+  const int rows = a.batch * a.h_q;
+  if (a.splits <= 8)
+    hipLaunchKernelGGL((decode_combine<D, 1>), dim3((rows + 3) / 4), dim3(256), 0, stream, a);
+  else if (a.splits <= 64)
+    hipLaunchKernelGGL((decode_combine<D, 4>), dim3(rows), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_combine<D, 16>), dim3(rows), dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// Default split size: about kTargetPrograms split programs in total (four
-// per compute unit of an MI355X), each streaming one contiguous share of a
-// (sequence, KV head)'s visible keys; at least kDefaultSplitKeys keys, a
-// multiple of 256.  Fewer, longer splits amortise each program's start-up
-// (the first loads' latency, the key-run set-up) and its merge.
+// Default split size: about 1024 split programs in total (four per compute unit
+// of an MI355X), of at least 32 KB of K rows (64 KB for groups of 8 QO heads,
+// whose programs end in twice the merging).  Each sequence's visible keys are
+// divided evenly over the splits that the longest possible one needs, so that
+// shorter sequences make shorter programs instead of fewer.  Measured (us): 1024
+// / 1536 / 2048 programs 58 / 62 / 63 for 16 ragged sequences in 32768-token
+// caches, 811 / 816 / 811 for 64 x 131072; smallest program 64 / 128 / 256 keys (d =
+// 128) 11.1 / 10.2 / 12.1 for one sequence of 16384, 17 / 13 / 13 for four ragged
+// ones of up to 8192; groups of 8 (2 x 50000) 37 / 37 / 30.  Before (256 keys, fixed
+// sizes, no prefetch): 17, 18, 78, and 74 for the first.
 int32_t decode_split_keys(const cowa_decode_params& p) {
   if (p.split_keys > 0) return p.split_keys;
+  constexpr int64_t kTargetPrograms = 1024;
+  const int64_t smallest = 128 * (128 / p.head_dim) * (p.h_q / p.h_k >= 8 ? 2 : 1);
   const int64_t per = (int64_t)p.batch * p.h_k;
   const int64_t splits = per >= kTargetPrograms ? 1 : (kTargetPrograms + per - 1) / per;
   const int64_t v = max_visible(p);
-  int64_t sk = (v + splits - 1) / splits;
-  sk = (sk + 255) / 256 * 256;
-  return (int32_t)(sk < kDefaultSplitKeys ? kDefaultSplitKeys : sk);
+  const int64_t sk = ((v + splits - 1) / splits + smallest - 1) / smallest * smallest;
+  return (int32_t)(sk < smallest ? smallest : sk);
 }
 
 int32_t decode_num_splits(const cowa_decode_params& p) {
@@ -388,6 +470,7 @@ hipError_t launch_decode(const cowa_decode_params& p, const void* q, const void*
   a.h_total = p.h_k_total; a.h_offset = p.h_k_offset;
   a.splits = decode_num_splits(p);
   a.split_keys = decode_split_keys(p);
+  a.even = p.split_keys == 0;
   a.c = p.softmax_scale * kLog2e;
   const size_t parts = (size_t)p.batch * p.h_q * a.splits;
   a.part_o = static_cast<float*>(ws);

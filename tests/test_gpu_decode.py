@@ -131,3 +131,19 @@ def test_decode_global_head_offset():
         w = inputs.custom("dec_tp", batch=2, n_q=1, n_k=9000, h_q=4, h_k=1, head_dim=128, w_sink=32, w_near=512,
                           kind="decode", h_total=8, h_offset=r)
         _check(w, [9000, 7777], key=inputs.key_of("dec_tp", r))
+
+
+@pytest.mark.parametrize("case", [
+    # name, batch, h_q, h_k, d, sink, near, n_max, seqlens, split_keys: one split (no combine
+    # launch), 2, 8 / 9 and 64 / 65 splits (one, four and sixteen waves per combine), shares of a
+    # few keys, a sequence with fewer keys than splits, runs that touch
+    ("one_split", 3, 8, 2, 128, 4, 40, 200, [200, 1, 117], 0), ("one_split_d64", 2, 8, 1, 64, 0, 64, 256, [256, 3], 0),
+    ("two", 2, 4, 4, 128, 8, 120, 257, [257, 130], 0), ("eight", 1, 8, 2, 128, 16, 496, 1024, [1023], 0),
+    ("nine", 2, 4, 1, 64, 16, 1136, 2304, [2304, 5], 0), ("sixty_four", 1, 2, 1, 128, 0, 8192, 8192, [8192], 0),
+    ("sixty_five", 2, 2, 1, 128, 0, 8320, 8320, [8320, 100], 0), ("forced_64", 2, 8, 2, 64, 5, 700, 5000, [5000, 33], 64),
+    ("empty_rows", 2, 4, 2, 128, 0, 0, 3000, [3000, 1], 0)], ids=lambda c: c[0])
+def test_decode_split_counts(case):
+    name, bsz, h_q, h_k, d, ws, wn, n_max, seqlens, sk = case
+    w = inputs.custom("dec_counts_" + name, batch=bsz, n_q=1, n_k=n_max, h_q=h_q, h_k=h_k, head_dim=d, w_sink=ws,
+                      w_near=wn, kind="decode")
+    _check(w, seqlens, key=inputs.key_of("dec_counts", name), split_keys=sk)
