@@ -461,14 +461,14 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
     constexpr bool MCUR = decltype(mcurc)::value;
     const int k_first = entry_at(t) * BK;
     // K of block t + 1 goes into the K buffer of block t - 1, which is free
-    // (the last block repeats itself).  With 128-key blocks the
-    // copies of K (from the block start) and of V (from the mid-block barrier)
-    // go out one 1 KB piece per product group: a burst of them would hold the
-    // wave at the vector memory queue.
-    constexpr bool SPREAD = NCH == 4;
-    [[maybe_unused]] const int kf_next = entry_at(t + 1) * BK;
-    if constexpr (!SPREAD) stage(kbase, t + 1, kbuf_off(t + 1));
-    if constexpr (NCH == 2) stage(vbase, t, vbuf_off(t));  // V buffer of block t - 2: free
+    // (the last block repeats itself).  The copies go out one 1 KB piece per
+    // product group: K from the block start; V after K with 64-key blocks (V of
+    // block t, into the free buffer of block t - 2), from the mid-block barrier
+    // with 128-key blocks.  A burst of them holds the wave at the vector memory
+    // queue: issued at once, 64-key blocks took 102 us at 4096 tokens (32/8
+    // heads, d = 128), 149 at 1000 queries of 32000 keys and 139 at 100; spread
+    // over the groups 100, 146 and 135.
+    const int kf_next = entry_at(t + 1) * BK;
     const unsigned char* Kt = smem + kbuf_off(t);
     const unsigned char* Vt = smem + vbuf_off(t);
     const unsigned char* Vp = smem + vbuf_off(t + 1);  // V of block t - 1
@@ -505,8 +505,9 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (SPREAD && GG < PPW) stage_piece(kbase, kf_next, kbuf_off(t + 1), GG);
-      if constexpr (SPREAD && GG >= 2 * NG - PF && GG < 2 * NG - PF + PPW)
+      if constexpr (GG < PPW) stage_piece(kbase, kf_next, kbuf_off(t + 1), GG);
+      if constexpr (NCH == 2 && GG >= PPW && GG < 2 * PPW) stage_piece(vbase, k_first, vbuf_off(t), GG - PPW);
+      if constexpr (NCH == 4 && GG >= 2 * NG - PF && GG < 2 * NG - PF + PPW)
         stage_piece(vbase, kf_next, vbuf_off(t + 1), GG - (2 * NG - PF));
       if constexpr (GG + PF < NGS) load(std::integral_constant<int, GG + PF>{}, fa[(GG + PF) % RING]);
       const bf16x8& a = fa[GG % RING];
