@@ -124,27 +124,6 @@ struct SwzTile {
   __device__ static inline int off_col(int row, int col) { return off(row, col >> 3) + ((col & 7) << 1); }
 };
 
-// Copy rows [first, first + ROWS) of a row-major [n_rows][D] bf16 matrix into
-// a swizzled LDS tile; rows past n_rows repeat row n_rows - 1 (callers mask
-// them).  The NW waves of the workgroup take the 1 KB pieces in turn; wave must
-// be wave-uniform.  Since NW pieces span a multiple of 16 rows, a lane's row
-// modulo 16, and so its swizzled chunk, is the same in every piece it copies.
-template <int D, int ROWS, int NW>
-__device__ inline void load_tile(const __bf16* base, int first, int n_rows, unsigned char* lds, int wave, int lane) {
-  using T = SwzTile<D, ROWS>;
-  constexpr int RPL = 1024 / (D * 2);  // rows per piece
-  static_assert(T::LOADS % NW == 0 && (NW * RPL) % 16 == 0, "piece layout");
-  const int row0 = wave * RPL + lane / T::CH;
-  const int col = (((lane % T::CH) ^ swz<T::CH>(row0)) << 3);
-#pragma unroll
-  for (int n = 0; n < T::LOADS / NW; ++n) {
-    int r = first + n * NW * RPL + row0;
-    r = r < n_rows ? r : n_rows - 1;
-    __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + (int64_t)r * D + col),
-                                     (lds_void*)(lds + (n * NW + wave) * 1024), 16, 0, 0);
-  }
-}
-
 // Global -> LDS copies issued as inline assembly: 16 (dma16) or 4 (dma4) bytes
 // per lane, lane l landing at LDS byte address lds_base + 16 l (or 4 l).  The
 // compiler does not see these as memory operations, so it neither counts them
@@ -186,105 +165,6 @@ __device__ inline void dma16_buf(uint32_t voff, i32x4 rsrc, uint32_t lds_base) {
                :
                : "v"(voff), "s"(rsrc), "s"(lds_base)
                : "memory", "m0");
-}
-
-// load_tile through dma16 (same layout and piece order).
-template <int D, int ROWS, int NW>
-__device__ inline void load_tile_asm(const __bf16* base, int first, int n_rows, uint32_t lds, int wave, int lane) {
-  using T = SwzTile<D, ROWS>;
-  constexpr int RPL = 1024 / (D * 2);
-  static_assert(T::LOADS % NW == 0 && (NW * RPL) % 16 == 0, "piece layout");
-  const int row0 = wave * RPL + lane / T::CH;
-  const int col = (((lane % T::CH) ^ swz<T::CH>(row0)) << 3);
-#pragma unroll
-  for (int n = 0; n < T::LOADS / NW; ++n) {
-    int r = first + n * NW * RPL + row0;
-    r = r < n_rows ? r : n_rows - 1;
-    dma16(base + (int64_t)r * D + col, __builtin_amdgcn_readfirstlane(lds + (n * NW + wave) * 1024));
-  }
-}
-
-// load_tile_asm for a wave-uniform wave count known at run time.
-template <int D, int ROWS>
-__device__ inline void load_tile_asm_nw(const __bf16* base, int first, int n_rows, uint32_t lds, int wave, int nw,
-                                        int lane) {
-  using T = SwzTile<D, ROWS>;
-  constexpr int RPL = 1024 / (D * 2);
-  if constexpr (T::LOADS % 8 == 0 && (8 * RPL) % 16 == 0) {
-    if (nw == 8) return load_tile_asm<D, ROWS, 8>(base, first, n_rows, lds, wave, lane);
-  }
-  if constexpr (T::LOADS % 4 == 0 && (4 * RPL) % 16 == 0) {
-    if (nw == 4) return load_tile_asm<D, ROWS, 4>(base, first, n_rows, lds, wave, lane);
-  }
-  for (int n = wave; n < T::LOADS; n += nw) {
-    const int flat = n * 64 + lane;
-    const int row = flat / T::CH, slot = flat % T::CH;
-    const int chunk = slot ^ swz<T::CH>(row);
-    int r = first + row;
-    r = r < n_rows ? r : n_rows - 1;
-    dma16(base + (int64_t)r * D + chunk * 8, __builtin_amdgcn_readfirstlane(lds + n * 1024));
-  }
-}
-
-// The same for any wave count (a lane's chunk recomputed per piece).
-template <int D, int ROWS>
-__device__ inline void load_tile_any(const __bf16* base, int first, int n_rows, unsigned char* lds, int wave, int nw,
-                                     int lane) {
-  using T = SwzTile<D, ROWS>;
-  for (int n = wave; n < T::LOADS; n += nw) {
-    const int flat = n * 64 + lane;  // 16-byte unit index == LDS position
-    const int row = flat / T::CH, slot = flat % T::CH;
-    const int chunk = slot ^ swz<T::CH>(row);
-    int r = first + row;
-    r = r < n_rows ? r : n_rows - 1;
-    __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(base + (int64_t)r * D + chunk * 8),
-                                     (lds_void*)(lds + n * 1024), 16, 0, 0);
-  }
-}
-
-// Dispatch on a wave-uniform wave count.
-template <int D, int ROWS>
-__device__ inline void load_tile_nw(const __bf16* base, int first, int n_rows, unsigned char* lds, int wave, int nw,
-                                    int lane) {
-  using T = SwzTile<D, ROWS>;
-  constexpr int RPL = 1024 / (D * 2);
-  if constexpr (T::LOADS % 8 == 0 && (8 * RPL) % 16 == 0) {
-    if (nw == 8) return load_tile<D, ROWS, 8>(base, first, n_rows, lds, wave, lane);
-  }
-  if constexpr (T::LOADS % 4 == 0 && (4 * RPL) % 16 == 0) {
-    if (nw == 4) return load_tile<D, ROWS, 4>(base, first, n_rows, lds, wave, lane);
-  }
-  load_tile_any<D, ROWS>(base, first, n_rows, lds, wave, nw, lane);
-}
-
-// 16-byte row fragment: row `row`, columns 8 chunk .. 8 chunk + 7.
-template <int D, int ROWS>
-__device__ inline bf16x8 read_row8(const unsigned char* tile, int row, int chunk) {
-  return *reinterpret_cast<const bf16x8*>(tile + SwzTile<D, ROWS>::off(row, chunk));
-}
-
-// Transposed MFMA operand from a row-major swizzled tile: output lane j of each
-// 16-lane group gets column c0 + j of rows r0 + 4 g + t (t = 0..3) in its
-// first four slots and of rows r0 + 16 + 4 g + t in the last four, g = lane / 16.
-template <int D, int ROWS>
-__device__ inline bf16x8 read_tr8(const unsigned char* tile, int r0, int c0, int lr, int lg) {
-  using T = SwzTile<D, ROWS>;
-  const int row = r0 + 4 * lg + (lr >> 2);
-  const int col = c0 + 4 * (lr & 3);
-  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + T::off_col(row, col)));
-  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + T::off_col(row + 16, col)));
-  const bf16x4 a = __builtin_bit_cast(bf16x4, lo), b = __builtin_bit_cast(bf16x4, hi);
-  return bf16x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-}
-
-// Same from a plain (unswizzled) row-major tile with a row pitch in bytes.
-__device__ inline bf16x8 read_tr8_plain(const unsigned char* tile, int pitch, int r0, int c0, int lr, int lg) {
-  const int row = r0 + 4 * lg + (lr >> 2);
-  const int col = c0 + 4 * (lr & 3);
-  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + row * pitch + col * 2));
-  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(tile + (row + 16) * pitch + col * 2));
-  const bf16x4 a = __builtin_bit_cast(bf16x4, lo), b = __builtin_bit_cast(bf16x4, hi);
-  return bf16x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
 
 // Per-lane byte offsets of the two read patterns, for rows 0..15 of a tile;

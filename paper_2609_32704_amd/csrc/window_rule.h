@@ -326,14 +326,4 @@ __host__ __device__ inline Ranges decode_key_runs(int64_t n_k, int64_t w_sink, i
   return r;
 }
 
-// The key at position v (0-based) of the ascending visible list.
-__host__ __device__ inline int32_t run_key(const Ranges& r, int32_t v) {
-  for (int x = 0; x < r.n; ++x) {
-    const int32_t sz = r.b[x] - r.a[x] + 1;
-    if (v < sz) return r.a[x] + v;
-    v -= sz;
-  }
-  return r.n > 0 ? r.b[r.n - 1] : 0;
-}
-
 }  // namespace cowa
