@@ -655,6 +655,37 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
         cm = fmaxf(cm, __shfl_xor(cm, 32));
         m_fix[nq] = cm * c;  // -inf for a column without a legal key there
       }
+      // Tiles without a full block start at their last keys, which their first
+      // rows do not reach when a tile is taller than a chunk.  Such rows take
+      // the 32 keys from their own 32-row tile's first distance-0 key on, which hold
+      // each row's distance-0 key (K straight from memory: once per row, early
+      // tiles only).
+      bool unset = false;
+#pragma unroll
+      for (int nq = 0; nq < NQT; ++nq) unset |= m_fix[nq] == -INFINITY && q_first + nq * 32 + l32 < n_q;
+      if (__builtin_expect(__ballot(unset) != 0, 0)) {
+#pragma unroll
+        for (int nq = 0; nq < NQT; ++nq) {
+          const int kd = q_first + nq * 32 + g.off, kr = kd + l32 < n_k ? kd + l32 : n_k - 1;
+          const __bf16* krow = kbase + (int64_t)kr * D + 8 * hh;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(krow + ks * 16);
+            sacc[0][nq] = ks == 0 ? mfma32_v0(a, qf[nq][0]) : mfma32_v(a, qf[nq][ks], sacc[0][nq]);
+            mfma_settle(sacc[0]);
+            __builtin_amdgcn_sched_barrier(0);  // (one fragment at a time: no registers to spare here)
+          }
+          float cm = -INFINITY;
+          const uint32_t lm = legal_keys32(g, q_first + nq * 32 + l32, kd + 4 * hh);
+#pragma unroll
+          for (int x = 0; x < 16; ++x) {
+            const bool ok = (lm >> (8 * (x >> 2) + (x & 3))) & 1u;
+            cm = fmaxf(cm, ok ? sacc[0][nq][x] : -INFINITY);
+          }
+          cm = fmaxf(cm, __shfl_xor(cm, 32));
+          m_fix[nq] = m_fix[nq] == -INFINITY ? cm * c : m_fix[nq];
+        }
+      }
     }
 #pragma unroll
     for (int nq = 0; nq < NQT; ++nq) mu[nq] = m_fix[nq] == -INFINITY ? 0.f : m_fix[nq] + kHead;
@@ -673,17 +704,14 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
     } else {
       // a column without an offset at the start (m = 0) keeps its sum only if
       // that sum is comfortably normal (otherwise it met no legal key, or its
-      // P underflowed); an overflow shows in the sum.  The line lies below
-      // 2^-kHead, the sum that a move of the offset leaves: with it above (2^-60)
-      // every such row whose offset moved was run again, which doubled the
-      // forward of short ragged batches (10 sequences of up to 6000 tokens, d =
-      // 64: 126 + 118 us, now 126 + 4).  Terms lost below 2^-126 weigh at most
-      // 2^-56 of the sum each.
+      // P underflowed); an overflow shows in the sum.  A move of the offset
+      // leaves 2^-kHead, below the line: such a row runs again from its exact
+      // maximum.
 #pragma unroll
       for (int nq = 0; nq < NQT; ++nq) {
         const float l = lacc[nq][0];
         hot |= !(l <= 0x1p64f);
-        far |= m_fix[nq] == -INFINITY && q_first + nq * 32 + l32 < n_q && !(l >= 0x1p-70f);
+        far |= m_fix[nq] == -INFINITY && q_first + nq * 32 + l32 < n_q && !(l >= 0x1p-60f);
       }
     }
     if (__ballot(hot) != 0) {
