@@ -218,10 +218,12 @@ cowa_status cowa_fwd(const cowa_params* p, const cowa_schedule_t* s,
  * float32 dK/dV partials of the KV columns (128 keys) that the dK/dV stage walks
  * in several parts and sums in a fixed order: those holding sink keys, whose
  * query lists are much longer than every other column's (every query sees the
- * sink, Eq. fwa_support; at most 16 parts each, 256 MB in total), and, where
- * there are too few columns to fill the device, the others (at most 8 parts,
- * 256 MB in total).  The split depends only on the parameters, so results stay
- * deterministic. */
+ * sink, Eq. fwa_support; at most 16 parts each), and, where a sequence has too few
+ * columns to fill the device, the others (at most 6 parts); at most 256 MB of
+ * them, and none where one workgroup takes all parts of a column.  How a column
+ * is cut follows from one KV head of one sequence and h_k_total alone: dK and dV
+ * of a sequence do not depend on the batch it is in, nor those of a KV head on
+ * which other heads the call holds, bit for bit. */
 cowa_status cowa_bwd_workspace_size(const cowa_params* p, size_t* bytes);
 
 /* Backward (Alg. 2): exact gradients of <dO, O> w.r.t. the unscaled Q, K and

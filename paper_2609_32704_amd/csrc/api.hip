@@ -185,111 +185,69 @@ cowa::HeadGeo geo_of(const cowa_params* p, const Layout& L, int b, int h) {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Split plan of the dK/dV pass (cowa::BwdSplit).  Lengths are in steps of 64
-// query rows of one QO head.
-//
-// Sink columns: parts of about half an ordinary column, and not longer than an
-// ordinary column's parts; at most 16 and 256 MB of partials (with whole other
-// columns and 64-key schedule tiles half as many, so that a schedule's tiles, not
-// the pass's 128-key columns, set the partials' bytes).
-//
-// Other columns, where there are at most two per workgroup slot of the device:
-// the pass takes about
-//   max(mean steps per slot, what the k + 1 longest of k * slots + 1 parts need
-//       on one slot) x time per step
-// plus the start of each workgroup and the partials' way through HBM, which is
-// evaluated for each number of parts from a few length classes per (sequence,
-// KV head): columns with near and whole long-range run, with some of the latter,
-// and with the whole or part of the near run alone.  With more columns than that the partials cost
-// about what the balance gains, and longest-first order does most of it.
-// Measured (us, d = 128, one part / the chosen number): 1000 tokens 32/8 heads
-// 95 / 50 (3), 2048 142 / 101 (2), 65536 of one KV head 2020 / 1910 (2); 8192
-// tokens 32/8 heads stay at one part (469, two would take 534); d = 64, 8192
-// tokens 16/4 heads 214 / 159 (3).
+// Split plan of the dK/dV pass (cowa::BwdSplit).  The parts of each column follow
+// from column_rule; this finds their largest numbers and who takes them:
+//  * a workgroup per part, while the call has at most one column per compute unit
+//    or no more than one sequence of it alone;
+//  * past that a workgroup per column, but for the columns with sink keys, whose
+//    parts would be too long a chain (d = 64, whose walk spills its sums: only
+//    where the partials would pass 256 MB);
+//  * a workgroup for each of those as well once all columns together keep the
+//    device busy for longer than the longest takes, or where their partials would
+//    pass 256 MB.
+// Measured (us, the three of them), 32/8 heads, d = 128: 2 x 2048 tokens 181 / 190 /
+// 262, 4 x 2048 357 / 271 / 270, 4 x 1000 120 / 103 / 159, 8 x 1000 247 / 181 / 160, 16
+// x 1000 - / 335 / 292, 64 x 1000 - / - / 1125 (1484 with whole columns in
+// clusters).  16/4 heads, d = 64: 4 x 4096 198 / 209 / 489, 16 x 1000 114 / 131 / 151.
 cowa::BwdSplit bwd_split_plan(const cowa_params* p, const Layout& L) {
   cowa::BwdSplit sp;
-  if (L.max_kt == 0 || L.max_qt == 0) return sp;
-  const int CK = cowa::kColKeys, G = p->h_q / p->h_k;
-  const int64_t copies = L.ragged ? 1 : p->batch;
-  const int64_t max_cols = ((int64_t)L.max_kt * p->tile_k + CK - 1) / CK;
-  int64_t S = 0;
-  for (const cowa::WinDesc& w : L.win) S = std::max<int64_t>(S, ((int64_t)w.sink + CK - 1) / CK);
-  S = std::min<int64_t>(S, max_cols);
-  struct Level {
-    double len, cnt;
-  };
-  std::vector<Level> lv;
-  double l_sink = 0, l_other = 1, total = 0;
+  const int G = p->h_q / p->h_k;
+  const int64_t seqs = L.ragged ? (int64_t)L.seq.size() : p->batch, copies = L.ragged ? 1 : p->batch;
+  const int64_t columns = cowa::column_count(*p) * copies;
+  int64_t longest = 1, total = 0, most_cols = 0;  // steps of the longest column and of all; columns of a sequence
+  cowa::ColumnRule r{};
+  cowa::Geo32 last{};
+  sp.n_all = (int64_t)p->h_k * copies * cowa::column_rows(*p, L.n_kt);
   for (size_t b = 0; b < L.seq.size(); ++b) {
-    const int64_t nq = L.seq[b].n_q, nk = L.seq[b].n_k, off = nk - nq;
-    if (nq == 0) continue;
-    const double bq = (double)((nq + 63) / 64);
-    const double cols = (double)((nk + CK - 1) / CK);
+    const int32_t n_k = L.seq[b].n_k;
+    if (L.seq[b].n_q == 0) continue;
+    const int64_t cols = (n_k + cowa::kColKeys - 1) / cowa::kColKeys;
+    most_cols = std::max(most_cols, cols * p->h_k_total);
     for (int h = 0; h < p->h_k; ++h) {
       const cowa::Geo32 g = cowa::geo32(geo_of(p, L, (int)b, h));
-      if (S > 0 && g.w_sink > 0) {
-        const double s = G * (double)cowa::runs3_count(cowa::query_block_runs3<64>(g, 0, (int32_t)std::min<int64_t>(CK, nk) - 1));
-        l_sink = std::max(l_sink, s);
-        total += s * (double)std::min<int64_t>(S, (int64_t)cols) * copies;
-      }
-      const int64_t width = g.hi > g.lo ? g.hi - g.lo : 0;
-      const double ln = g.w_near > 0 ? std::min(bq, (double)((CK + g.w_near - 2) / 64 + 2)) : 0;
-      const double ll = width > 0 ? std::min(bq, (double)((CK + width - 2) / 64 + 2)) : 0;
-      const double with = std::max<double>(0, (double)(nk - g.lo) - std::max<int64_t>(0, off - g.hi)) / CK;
-      const double full = width > 0 ? std::max<double>(0, (double)(nk - g.hi) - std::max<int64_t>(0, off - g.lo)) / CK : 0;
-      const double ramp = width > 0 ? std::max(0.0, with - full) : 0;
-      const double near = std::max(0.0, std::min(cols, (double)(nk - std::max<int64_t>(0, off - g.w_near)) / CK) - full - ramp);
-      const double tail = std::min(near, (double)std::min<int64_t>(g.w_near, nk) / CK);  // the last columns' near runs end early
-      const Level add[5] = {{G * std::min(bq, ln + ll), full}, {G * std::min(bq, ln + 0.75 * ll), ramp / 2},
-                            {G * std::min(bq, ln + 0.25 * ll), ramp / 2}, {G * ln, near - tail}, {G * ln / 2, tail}};
-      for (const Level& a : add)
-        if (a.cnt > 0 && a.len > 0) {
-          lv.push_back({a.len, a.cnt * copies});
-          total += a.len * a.cnt * copies;
-          l_other = std::max(l_other, a.len);
+      if (h == 0 || g.w_near != last.w_near || g.w_sink != last.w_sink || g.hi - g.lo != last.hi - last.lo) {
+        r = cowa::column_rule(g, G, p->h_k_total, p->head_dim);
+        sp.PO = std::max(sp.PO, r.ordinary);
+        longest = std::max<int64_t>(longest, r.longest);
+        if (g.w_sink > 0) {
+          // (every query sees the first key, if it is a sink's: no column is longer)
+          const int n = G * ((g.n_q + 63) / 64);
+          sp.P = std::max(sp.P, cowa::column_parts(r, true, n));
+          longest = std::max<int64_t>(longest, n);
+          sp.S = std::max(sp.S, (g.w_sink + cowa::kColKeys - 1) / cowa::kColKeys);
         }
+      }
+      last = g;
+      total += r.longest * cols * copies;
     }
   }
-  const int64_t rows = (int64_t)p->h_k * copies * (L.ragged ? (int64_t)L.n_kt : max_cols);
-  const size_t part_bytes = cowa::bwd_part_floats(*p) * sizeof(float);
-  const double slots = p->head_dim == 128 ? 256 : 512, step_us = p->head_dim == 128 ? 2.0 : 2.6;
-  double n_cols = 0;
-  for (const Level& a : lv) n_cols += a.cnt;
-  const int64_t seqs = L.ragged ? (int64_t)L.seq.size() : p->batch;
-  auto sink_parts = [&](int PO) -> int64_t {
-    if (S == 0) return 1;
-    int64_t P = std::min<int64_t>((int64_t)std::ceil(std::max(2, PO) * l_sink / l_other), 16) ;
-    if (PO == 1) P = P * p->tile_k / CK;
-    while (P > 1 && (size_t)(seqs * p->h_k * S * P) * part_bytes > (size_t(256) << 20)) --P;
-    return std::max<int64_t>(P, 1);
-  };
-  double best = 0;
-  for (int P : {1, 2, 3, 4, 6, 8}) {
-    if (P > 1 && (n_cols > 2 * slots || (size_t)rows * P * part_bytes > (size_t(256) << 20))) break;
-    std::vector<Level> parts;
-    for (const Level& a : lv) parts.push_back({a.len / P, a.cnt * P});
-    if (S > 0) parts.push_back({l_sink / sink_parts(P), (double)(seqs * p->h_k * S * sink_parts(P))});
-    if (parts.empty()) break;
-    std::sort(parts.begin(), parts.end(), [](const Level& a, const Level& b) { return a.len > b.len; });
-    double bound = total / slots, seen = 0;
-    for (const Level& a : parts) {
-      seen += a.cnt;
-      bound = std::max(bound, std::floor((seen - 1) / slots + 1) * a.len);
-    }
-    const double est = bound * step_us + 6.0 * std::ceil(seen / slots) +
-                       (P > 1 ? 5.0 + n_cols * P * 2.0 * part_bytes / 4.5e6 : 0.0);
-    if (P == 1 || est < 0.97 * best) {
-      best = est;
-      sp.PO = P;
-    }
+  if (sp.P > 1) {
+    sp.P = std::max(sp.P, sp.PO);  // (a head of the call may have fewer sink columns)
+    sp.n_cols = seqs * p->h_k * sp.S;
+  } else {
+    sp.S = 0;
   }
-  sp.target = (int32_t)std::ceil(l_other / sp.PO);
-  sp.n_all = rows;
-  const int64_t P = sink_parts(sp.PO);
-  if (P > 1) {
-    sp.S = (int32_t)S;
-    sp.P = (int32_t)P;
-    sp.n_cols = seqs * p->h_k * S;
+  const size_t most = size_t(256) << 20;
+  if (sp.PO > 1 && ((p->head_dim == 128 && columns >= 256 && columns > most_cols) ||
+                    cowa::bwd_split_bytes(*p, sp) > most)) {
+    sp.PO = 1;
+    sp.walk = true;
+  }
+  if ((sp.walk && total >= (p->head_dim == 128 ? 256 : 512) * longest) || cowa::bwd_split_bytes(*p, sp) > most) {
+    sp.S = 0;
+    sp.P = 1;
+    sp.n_cols = 0;
+    sp.walk = true;
   }
   return sp;
 }

@@ -98,14 +98,16 @@ struct BwdCfg {
 // the others take n_items columns x PO parts (part 0 of a sink column).  With an
 // order table the items are its columns, longest first, each with the batch
 // entries and parts side by side (past two workgroups per compute unit in
-// chunks of 8 per XCD, so that neighbours share its L2); without one they are
-// clusters of 32 consecutive columns of one KV head that share an XCD's L2.
+// chunks of 8 per XCD, so that neighbours share its L2); without one, or with more
+// columns than kMaxOrdered unless each is walked whole, they are clusters of 32
+// consecutive columns of one KV head that share an XCD's L2.
 // Measured (us, clusters / longest first): 8192 tokens, 32/8 heads 516 / 469; 4 x
 // 2048 288 / 231; 16384 1199 / 1142; 131072 of one KV head 6930 / 6887; 32768
 // (2048 columns) 3977 / 4056.
 struct SplitArgs {
-  float* part;       // sinks [n_cols][P][2][BK * D] float32 partials (P > 1), then [n_all][PO][...] (PO > 1)
-  int32_t S, P, PO, target;
+  float* part;       // BwdWork::part
+  int32_t S, P, PO;  // BwdSplit
+  int32_t heads;     // KV heads of the whole model (column_rule)
   int32_t n_extra;   // workgroups of parts 1 .. P-1, rounded up to a multiple of 8
   int32_t rows;      // column rows (column_rows)
   int32_t n_items;   // columns of the grid
@@ -119,62 +121,17 @@ __device__ inline bool column_ctx(const cowa_params& p, const SchedView& sv, int
   k_first = sv.ragged ? sc.tile * p.tile_k : row * kColKeys;
   return k_first % kColKeys == 0 && k_first < sc.n_k;
 }
-// Parts of a column of n_steps steps.
-__device__ inline int column_parts(const SplitArgs& sa, int col, int n_steps) {
-  if (sa.P > 1 && col < sa.S) return sa.P;
-  const int n = (n_steps + sa.target - 1) / sa.target;
-  return n < 1 ? 1 : (n < sa.PO ? n : sa.PO);
-}
-
-template <int D>
-__global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, SplitArgs sa,
-                                                const __bf16* __restrict__ q,
-                                                const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-                                                const __bf16* __restrict__ d_o, const float* __restrict__ nl,
-                                                const float* __restrict__ nd, __bf16* __restrict__ dk,
-                                                __bf16* __restrict__ dv) {
+// Part `part` of the column at k_first_ of (sequence sc.b, local KV head hk), or,
+// WALK, all of its parts, in order (BwdSplit::walk).
+template <int D, bool WALK>
+__device__ __forceinline__ void walk_column(const cowa_params& p, const SchedView& sv, const SplitArgs& sa,
+                                            const __bf16* q, const __bf16* k, const __bf16* v, const __bf16* d_o,
+                                            const float* nl, const float* nd, __bf16* dk, __bf16* dv,
+                                            unsigned char* smem, int part, int row, int unit, int hk, const SeqCtx& sc,
+                                            int k_first_) {
   using C = BwdCfg<D>;
   constexpr int NW = C::NW, BK = C::BK;
-  extern __shared__ __align__(1024) unsigned char smem[];
-
-  int part = 0, row, unit;
-  const bool extra = (int)blockIdx.x < sa.n_extra;
-  if (extra) {
-    const int e = blockIdx.x;
-    part = 1 + e % (sa.P - 1);
-    const int rest = e / (sa.P - 1);
-    const int tile = rest % sa.S, us = rest / sa.S;  // us = sequence * h_k + KV head
-    if (us >= p.batch * p.h_k) return;               // padding
-    if (!sv.ragged) {
-      row = tile;
-      unit = us;
-    } else {
-      const SeqDesc sd = sv.seq[us / p.h_k];
-      if (tile * BK >= sd.n_k) return;  // a sequence with fewer columns
-      row = sd.kt_off + tile * (BK / p.tile_k);
-      unit = us % p.h_k;
-    }
-  } else if (sv.order != nullptr) {
-    const int total = sa.n_items * sa.PO, id = blockIdx.x - sa.n_extra, copies = sv.ragged ? 1 : p.batch;
-    const int e = total > 512 ? xcd_remap(id, total) : id;
-    part = e % sa.PO;
-    const int item = e / sa.PO;
-    const int c = (int)sv.order[item / copies];
-    row = c % sa.rows;
-    unit = c / sa.rows + (item % copies) * p.h_k;
-  } else {
-    const int e = blockIdx.x - sa.n_extra;
-    part = e / sa.n_items;
-    const WorkItem wi = cluster_item(e % sa.n_items, sa.rows, 1, grid_units(p, sv),
-                                     cluster_rows(sa.rows, grid_units(p, sv), 32), false);
-    row = wi.row;
-    unit = wi.unit;
-  }
-  int hk, k_first_;
-  SeqCtx sc;
-  if (row >= sa.rows || !column_ctx(p, sv, row, unit, hk, sc, k_first_)) return;
   const int j = k_first_ / BK;  // column within the sequence
-  if (!extra && part > 0 && sa.P > 1 && j < sa.S) return;  // a sink column's parts are the extra workgroups
   const int G = p.h_q / p.h_k;
   const Geo32 g = sc.g;
   const int n_q = sc.n_q, n_k = sc.n_k;
@@ -196,9 +153,8 @@ __global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, Spl
   const Runs3 runs = query_block_runs3<C::BQ>(g, (int)k_first, k_last);
   const int r0 = runs.b0 - runs.a0 + 1, r1 = r0 + runs.b1 - runs.a1 + 1, n_ent = r1 + runs.b2 - runs.a2 + 1;
   const int n_steps = G * n_ent;
-  const int n_parts = column_parts(sa, j, n_steps);
+  const int n_parts = column_parts(column_rule(g, G, sa.heads, D), (int)k_first < g.w_sink, n_steps);
   if (part >= n_parts) return;
-  const bool split = n_parts > 1;
   const int cap = sa.cap;
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + C::MAIN_BYTES);
   int n_full = 0;
@@ -216,9 +172,10 @@ __global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, Spl
   }
   const int n_part = n_ent - n_full;
   const int steps_full = G * n_full;
-  // this workgroup's steps: all of them, or part `part` of n_parts contiguous shares
-  const int s_begin = (int)((int64_t)n_steps * part / n_parts);
-  const int s_end = (int)((int64_t)n_steps * (part + 1) / n_parts);
+  // this workgroup's steps: part `part` of n_parts contiguous shares, or all of them
+  auto part_end = [&](int x) { return (int)((int64_t)n_steps * (x + 1) / n_parts); };
+  const int s_begin = part_end(part - 1);
+  const int s_end = WALK ? n_steps : part_end(part);
   // cursor (phase: 0 full / 1 partial, QO head, list index) of step s_begin
   int c_ph, c_k, c_hh;
   {
@@ -506,15 +463,42 @@ __global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, Spl
     advance(n2_ph, n2_hh, n2_k);
     slot = slot == 2 ? 0 : slot + 1;
   };
+  const float scale = p.softmax_scale;
   int t = s_begin;
-  for (; t < (s_end < steps_full ? s_end : steps_full); ++t) step(false);
-  for (; t < s_end; ++t) step(true);
+  if constexpr (WALK) {
+    // part after part: a part's sums start at zero and are added to those of the
+    // parts before, as where a workgroup per part and the second kernel do it
+    // (the product by the scale is not fused with the sum there either)
+    f32x4 dks[C::MD][C::NTK], dvs[C::MD][C::NTK];
+    for (; part < n_parts; ++part) {
+      const int end = part_end(part);
+      for (; t < (end < steps_full ? end : steps_full); ++t) step(false);
+      for (; t < end; ++t) step(true);
+#pragma unroll
+      for (int md = 0; md < C::MD; ++md)
+#pragma unroll
+        for (int nt = 0; nt < C::NTK; ++nt) {
+          f32x4 a = scale * dka[md][nt];
+          asm volatile("" : "+v"(a));
+          dks[md][nt] = part == 0 ? a : dks[md][nt] + a;
+          dvs[md][nt] = part == 0 ? dva[md][nt] : dvs[md][nt] + dva[md][nt];
+          dka[md][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+          dva[md][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+#pragma unroll
+    for (int md = 0; md < C::MD; ++md)
+#pragma unroll
+      for (int nt = 0; nt < C::NTK; ++nt) dka[md][nt] = dks[md][nt], dva[md][nt] = dvs[md][nt];
+  } else {
+    for (; t < (s_end < steps_full ? s_end : steps_full); ++t) step(false);
+    for (; t < s_end; ++t) step(true);
+  }
 
   // the copies staged past the last step must land before their LDS is reused
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  const float scale = p.softmax_scale;
-  if (split) {
+  if (!WALK && n_parts > 1) {
     // float32 partials in register order: element ((md NTK + nt) NW + wave) 64 + lane
     // holds rows d = 16 md + 4 (lane / 16) + 0..3, key wave NKW + 16 nt + lane % 16
     const int64_t col = sa.P > 1 && j < sa.S ? ((int64_t)(sc.b * p.h_k + hk) * sa.S + j) * sa.P + part
@@ -531,6 +515,7 @@ __global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, Spl
       }
     return;
   }
+  const float out_scale = WALK ? 1.f : scale;  // (the sums of a walk hold the scale)
   // write dK and dV of the block: through LDS as [key][d], then 16-byte rows
   __bf16* tk = reinterpret_cast<__bf16*>(smem);                        // [BK][D + 8]
   __bf16* tv = reinterpret_cast<__bf16*>(smem) + BK * (D + 8);         // [BK][D + 8]
@@ -541,7 +526,7 @@ __global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, Spl
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         const int key = wave * C::NKW + nt * 16 + lr, d = md * 16 + 4 * lg + rr;
-        tk[key * (D + 8) + d] = (__bf16)(scale * dka[md][nt][rr]);
+        tk[key * (D + 8) + d] = (__bf16)(out_scale * dka[md][nt][rr]);
         tv[key * (D + 8) + d] = (__bf16)dva[md][nt][rr];
       }
   __syncthreads();
@@ -555,6 +540,62 @@ __global__ void __launch_bounds__(256) bwd_main(cowa_params p, SchedView sv, Spl
       *reinterpret_cast<uint4*>(dvb + kp * D + ch * 8) = *reinterpret_cast<const uint4*>(tv + key * (D + 8) + ch * 8);
     }
   }
+}
+
+// WALK: BwdSplit::walk, columns with sink keys excepted where they have partials.
+template <int D, bool WALK>
+__global__ void __launch_bounds__(256, D == 64 && WALK ? 2 : 1) bwd_main(cowa_params p, SchedView sv, SplitArgs sa,
+                                                const __bf16* __restrict__ q,
+                                                const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                                                const __bf16* __restrict__ d_o, const float* __restrict__ nl,
+                                                const float* __restrict__ nd, __bf16* __restrict__ dk,
+                                                __bf16* __restrict__ dv) {
+  using C = BwdCfg<D>;
+  constexpr int BK = C::BK;
+  extern __shared__ __align__(1024) unsigned char smem[];
+
+  int part = 0, row, unit;
+  const bool extra = (int)blockIdx.x < sa.n_extra;
+  if (extra) {
+    const int e = blockIdx.x;
+    part = 1 + e % (sa.P - 1);
+    const int rest = e / (sa.P - 1);
+    const int tile = rest % sa.S, us = rest / sa.S;  // us = sequence * h_k + KV head
+    if (us >= p.batch * p.h_k) return;               // padding
+    if (!sv.ragged) {
+      row = tile;
+      unit = us;
+    } else {
+      const SeqDesc sd = sv.seq[us / p.h_k];
+      if (tile * BK >= sd.n_k) return;  // a sequence with fewer columns
+      row = sd.kt_off + tile * (BK / p.tile_k);
+      unit = us % p.h_k;
+    }
+  } else if (sv.order != nullptr) {
+    const int total = sa.n_items * sa.PO, id = blockIdx.x - sa.n_extra, copies = sv.ragged ? 1 : p.batch;
+    const int e = total > 512 ? xcd_remap(id, total) : id;
+    part = e % sa.PO;
+    const int item = e / sa.PO;
+    const int c = (int)sv.order[item / copies];
+    row = c % sa.rows;
+    unit = c / sa.rows + (item % copies) * p.h_k;
+  } else {
+    const int e = blockIdx.x - sa.n_extra;
+    part = e / sa.n_items;
+    const WorkItem wi = cluster_item(e % sa.n_items, sa.rows, 1, grid_units(p, sv),
+                                     cluster_rows(sa.rows, grid_units(p, sv), 32), false);
+    row = wi.row;
+    unit = wi.unit;
+  }
+  int hk, k_first_;
+  SeqCtx sc;
+  if (row >= sa.rows || !column_ctx(p, sv, row, unit, hk, sc, k_first_)) return;
+  const bool sink = sa.P > 1 && k_first_ / BK < sa.S;
+  if (!extra && part > 0 && sink) return;  // a sink column's parts are the extra workgroups
+  if (WALK && !sink)
+    walk_column<D, true>(p, sv, sa, q, k, v, d_o, nl, nd, dk, dv, smem, part, row, unit, hk, sc, k_first_);
+  else
+    walk_column<D, false>(p, sv, sa, q, k, v, d_o, nl, nd, dk, dv, smem, part, row, unit, hk, sc, k_first_);
 }
 
 // Sum of the partials of each split column (in part order) -> bf16 dK, dV; one
@@ -591,13 +632,11 @@ __global__ void __launch_bounds__(256) bwd_split_sum(cowa_params p, SchedView sv
   if (!column_ctx(p, sv, row, unit, hk, sc, k_first)) return;
   j = k_first / BK;
   const int n_k = sc.n_k;
-  int n_parts = sa.P;
-  if ((int)blockIdx.x >= n_sink) {
-    if (sa.P > 1 && j < sa.S) return;
-    const int k_last = k_first + BK < n_k ? k_first + BK - 1 : n_k - 1;
-    n_parts = column_parts(sa, j, p.h_q / p.h_k * runs3_count(query_block_runs3<C::BQ>(sc.g, k_first, k_last)));
-    if (n_parts == 1) return;
-  }
+  if ((int)blockIdx.x >= n_sink && sa.P > 1 && j < sa.S) return;
+  const int k_last = k_first + BK < n_k ? k_first + BK - 1 : n_k - 1, G = p.h_q / p.h_k;
+  const int n_parts = column_parts(column_rule(sc.g, G, sa.heads, D), k_first < sc.g.w_sink,
+                                   G * runs3_count(query_block_runs3<C::BQ>(sc.g, k_first, k_last)));
+  if (n_parts == 1) return;
   const int64_t row0 = sc.k0 + (int64_t)hk * sc.kh;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
   const f32x4* src = reinterpret_cast<const f32x4*>(sa.part + first * 2 * BK * D);
@@ -629,24 +668,24 @@ hipError_t launch_main(const cowa_params& p, SchedView sv, const void* q, const 
                        const void* d_o, const BwdWork& w, void* dk, void* dv, hipStream_t stream) {
   using C = BwdCfg<D>;
   static_assert(C::OUT_BYTES <= C::LDS_MAX && C::MAIN_BYTES < C::LDS_MAX, "LDS budget");
-  auto kern = bwd_main<D>;
+  const BwdSplit& sp = w.split;
+  auto kern = sp.walk ? bwd_main<D, true> : bwd_main<D, false>;
   {
     const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
     if (err != hipSuccess) return err;
   }
-  const BwdSplit& sp = w.split;
   const int copies = sv.ragged ? 1 : p.batch;
-  if (column_count(p) * copies > kMaxOrdered) sv.order = nullptr;  // (many rounds: the L2 matters more)
+  if (!sp.walk && column_count(p) * copies > kMaxOrdered) sv.order = nullptr;  // (many rounds: the L2 matters more)
   SplitArgs sa;
   sa.part = w.part;
   sa.S = sp.S;
   sa.P = sp.P;
   sa.PO = sp.PO;
-  sa.target = sp.target > 0 ? sp.target : 1;
-  sa.n_extra = sp.P > 1 ? (int32_t)(((int64_t)p.batch * p.h_k * sp.S * (sp.P - 1) + 7) / 8 * 8) : 0;
+  sa.heads = p.h_k_total;
+  sa.n_extra = sa.P > 1 ? (int32_t)(((int64_t)p.batch * p.h_k * sa.S * (sa.P - 1) + 7) / 8 * 8) : 0;
   sa.rows = column_rows(p, sv.n_kt);
   sa.n_items = sv.order ? (int32_t)column_count(p) * copies : sa.rows * p.h_k * copies;
-  sa.other = sp.P > 1 ? sp.n_cols * sp.P : 0;
+  sa.other = sa.P > 1 ? sp.n_cols * sa.P : 0;
   // 64-row blocks of the longest sequence
   const int64_t nq = sv.ragged ? (int64_t)sv.max_qt * p.tile_q : p.n_q;
   sa.cap = (int32_t)((nq + C::BQ - 1) / C::BQ);
@@ -656,8 +695,8 @@ hipError_t launch_main(const cowa_params& p, SchedView sv, const void* q, const 
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<const __bf16*>(d_o), w.nl, w.nd, static_cast<__bf16*>(dk),
                      static_cast<__bf16*>(dv));
-  const int n_sink = sp.P > 1 ? (int)sp.n_cols : 0;
-  const unsigned sums = (unsigned)n_sink + (sp.PO > 1 ? (unsigned)sp.n_all : 0u);
+  const int n_sink = sa.P > 1 ? (int)sp.n_cols : 0;
+  const unsigned sums = (unsigned)n_sink + (sa.PO > 1 ? (unsigned)sp.n_all : 0u);
   if (sums > 0)
     hipLaunchKernelGGL((bwd_split_sum<D>), dim3(sums, C::MD), dim3(256), 0, stream, p, sv, sa, n_sink,
                        static_cast<__bf16*>(dk), static_cast<__bf16*>(dv));

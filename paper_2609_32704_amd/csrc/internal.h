@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "cowa.h"
+#include "window_rule.h"
 
 namespace cowa {
 
@@ -37,11 +38,9 @@ struct SchedView {
   const uint32_t* order;  // dK/dV columns, longest first (column_order_bytes), or null
 };
 
-// The dK/dV pass has columns of its own: kColKeys keys of one KV head and sequence.
-// Column rows: ceil(N_k / kColKeys) for fixed lengths; in a ragged batch the
-// schedule's KV blocks, of which every (kColKeys / tile_k)-th of a sequence
-// starts a column and the others hold none.
-constexpr int kColKeys = 128;
+// Column rows of the dK/dV pass: ceil(N_k / kColKeys) for fixed lengths; in a
+// ragged batch the schedule's KV blocks, of which every (kColKeys / tile_k)-th of
+// a sequence starts a column and the others hold none.
 inline int32_t column_rows(const cowa_params& p, int32_t n_kt) {
   return p.cu_seqlens_k ? n_kt : (p.n_k + kColKeys - 1) / kColKeys;
 }
@@ -54,15 +53,17 @@ inline int64_t column_count(const cowa_params& p) {
     rows = (p.n_k + kColKeys - 1) / kColKeys;
   return rows * p.h_k;
 }
-// Up to kMaxOrdered columns are also listed longest first at the end of the
-// schedule buffer: few workgroups of unequal length leave the device idle at
-// the end unless the long ones start first.  Larger grids have enough rounds
-// (and take their columns in clusters that share an L2).
-constexpr int64_t kMaxOrdered = 1024;
+// Up to kMaxOrdered columns of a fixed-length batch entry, or kMaxOrderedRagged of
+// a whole ragged batch, are also listed longest first at the end of the schedule
+// buffer: workgroups of unequal length leave the device idle at the end unless the
+// long ones start first.  Grids of more than kMaxOrdered columns, all batch entries
+// together, have enough rounds and take their columns in clusters that share an L2,
+// but for a walk (BwdSplit), whose sink columns are as long as many others.
+constexpr int64_t kMaxOrdered = 1024, kMaxOrderedRagged = 16384;
 inline size_t column_order_bytes(const cowa_params& p) {
   if (p.dtype != COWA_BF16) return 0;  // (no backward)
   const int64_t n = column_count(p);
-  return n <= kMaxOrdered ? 4 * (size_t)n : 0;
+  return n <= (p.cu_seqlens_k ? kMaxOrderedRagged : kMaxOrdered) ? 4 * (size_t)n : 0;
 }
 inline size_t column_order_offset(const cowa_schedule_t* s) {
   return (s->off_kt_seq + (s->p.cu_seqlens_k ? 4 * (size_t)s->n_kt : 0) + 255) & ~size_t(255);
@@ -117,20 +118,20 @@ int bwd_dq_max_kblocks(int head_dim, int tile_k);
 hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const void* q, const void* k,
                            const void* v, void* o, float* lse, hipStream_t stream);
 
-// Split of the dK/dV pass's columns into parts.  Every query that reaches a sink
-// key sees it, so the sink columns have query lists as long as the sequence
-// while every other column holds only its near and long-range runs; and where
-// there are few columns, even those leave compute units idle or finish far
-// apart.  A column of several parts is walked by as many workgroups, each
-// taking a contiguous share of its steps and writing float32 partial dK and dV;
-// a second kernel sums the partials in a fixed order (deterministic) and writes
-// bf16.  The first S columns of every (sequence, KV head) have P parts; the
-// others up to PO, of about `target` steps each.  The plan depends on the
-// parameters alone.
+// Split of the dK/dV pass's columns into parts (column_rule).  Every query that
+// reaches a sink key sees it, so the sink columns have query lists as long as the
+// sequence while every other column holds only its near and long-range runs;
+// and where a sequence has few columns, even those leave compute units idle or
+// finish far apart.  The parts of a column are walked either by as many
+// workgroups, which write float32 partial dK and dV that a second kernel sums in
+// part order and writes as bf16, or (`walk`) by one workgroup, part after part,
+// which adds each part's sums to those before in its registers.  Both give the
+// same bits, so that choice may look at the whole call: many columns fill the
+// device by themselves.
 struct BwdSplit {
-  int32_t S = 0, P = 1;   // leading (sink) columns per (sequence, KV head), and their parts
-  int32_t PO = 1;         // most parts of any other column
-  int32_t target = 0;     // steps per part of the others
+  int32_t S = 0, P = 1;   // leading columns per (sequence, KV head) that hold sink keys, and their most parts
+  int32_t PO = 1;         // most parts of any other column (a walk: 1)
+  bool walk = false;      // a workgroup per column, but for the first S if P > 1
   int64_t n_cols = 0;     // sink columns: sequences x KV heads x S
   int64_t n_all = 0;      // column slots: sequences x KV heads x column rows
 };
@@ -139,11 +140,12 @@ inline size_t bwd_part_floats(const cowa_params& p) { return (size_t)2 * kColKey
 
 // Backward workspace: per query row (layout of LSE), nd = -D with
 // D = rowsum(O * dO) (the term of Alg. 2), then nl = -LSE log2(e); then the
-// float32 partials of the split dK/dV columns; each array 256-byte aligned.
+// float32 partials of the dK/dV columns of several parts; each array 256-byte
+// aligned.
 struct BwdWork {
   float* nd;
   float* nl;
-  float* part;  // sinks [n_cols][P][2][kColKeys * head_dim] if P > 1, then [n_all][PO][...] if PO > 1
+  float* part;  // sinks [n_cols][P][2][kColKeys * head_dim] if P > 1, then [n_all][PO][...] if PO > 1; or null
   BwdSplit split;
 };
 inline size_t bwd_array_bytes(const cowa_params& p) { return ((size_t)q_rows(p) * sizeof(float) + 255) & ~size_t(255); }

@@ -209,6 +209,72 @@ __host__ __device__ inline int32_t runs3_count(const Runs3& r) {
   return (r.b0 - r.a0 + 1) + (r.b1 - r.a1 + 1) + (r.b2 - r.a2 + 1);
 }
 
+// The dK/dV pass has columns of its own, kColKeys keys of one KV head and sequence,
+// and walks a column in steps: one block of 64 queries of one QO head each.
+constexpr int kColKeys = 128;
+
+// How a column's steps are cut into parts, whose float32 sums are added in order.
+// The cut decides how dK and dV are rounded, so it follows from one KV head of
+// one sequence and from the number of heads of the whole model (`heads`)
+// alone: a sequence gives the same bits in any batch, and a KV head on any rank.
+//   longest   steps of a column past the sink, at most: the near and the
+//             long-range run, each spanning up to one block more than its length
+//   ordinary  most parts of such a column.  Where the sequence's columns of all
+//             heads are few, a workgroup per part fills the device: at most
+//             what 0.8 of it takes beyond the first parts (d = 64, two workgroups per
+//             compute unit: 448), columns with sink keys, which are cut further,
+//             counted as three, and as long as one more part shortens the
+//             longest column by more than it costs.
+//   sink      most parts of a column with sink keys, which every later query
+//             sees: 16, and at most 256 MB of sums over all heads.  Its parts are as
+//             long as an ordinary column's, or, where those are whole, half of
+//             `longest`, but 128 steps if `longest` has them (8192 tokens, 32/8 heads:
+//             parts of 128 steps 441 us, of 72 460)
+// Measured (us, 1 / 2 / 3 / 4 / 6 ordinary parts), 32/8 heads, d = 128: 500
+// tokens 66 / 52 / 40 / 35 / 32; 1000 95 / 64 / 48 / 65 / 65 (past 256 parts a second
+// round); 2048 185 / 116 / 127; 4096 230 / 240.  8/2 heads: 16384 925 / 775.  16/4,
+// d = 64: 1000 74 / 48 / 38 / 34 / 30; 4096 146 / 98 / 80 / 86 / 82; 8192 237 / 182 / 193.
+struct ColumnRule {
+  int32_t longest, ordinary, sink;
+};
+__host__ __device__ inline ColumnRule column_rule(const Geo32& g, int32_t group, int32_t heads, int32_t head_dim) {
+  ColumnRule r;
+  const bool wide = head_dim == 128;
+  const int32_t width = g.hi - g.lo, bq = (g.n_q + 63) / 64;
+  const int32_t near = g.w_near > 0 ? imin32(bq, (kColKeys + g.w_near - 2) / 64 + 2) : 0;
+  const int32_t lng = width > 0 ? imin32(bq, (kColKeys + width - 2) / 64 + 2) : 0;
+  r.longest = imax32(1, group * imin32(bq, near + lng));
+  // (32-bit: capped far above where a column has one part)
+  constexpr int32_t kMany = 1 << 20;
+  const int32_t h = imin32(heads, kMany);
+  const int32_t cols = (int32_t)imin64(kMany, imax64(1, (int64_t)((g.n_k + kColKeys - 1) / kColKeys) * h));
+  const int32_t load = cols + (g.w_sink > 0 ? 2 * h : 0), slots = wide ? 256 : 448;
+  const int32_t fill = imin32(wide ? 6 : 3, 1 + (8 * slots + 3 * load) / (10 * load));
+  // in ns: a step, the launch that sums, a part's start and way through memory
+  const int32_t step = (wide ? 2000 : 2600) * imin32(r.longest, 1 << 19), sum = 10000;
+  const int32_t part = 1000 + (wide ? 57 : 28) * cols;
+  int32_t n = 1;
+  // (two parts halve the longest column; with a column per slot they only even out the end)
+  if (fill > 1 && step > (cols < slots ? 2 : 8) * (sum + 2 * part)) ++n;
+  while (n > 1 && n < fill && step > part * n * (n + 1)) ++n;
+  r.ordinary = n;
+  const int32_t sinks = (int32_t)imin64(kMany, imax64(1, (int64_t)((g.w_sink + kColKeys - 1) / kColKeys) * h));
+  r.sink = imax32(1, imin32(16, 2048 * (128 / head_dim) / sinks));
+  return r;
+}
+// Parts of a column of n_steps steps.
+__host__ __device__ inline int32_t column_parts(const ColumnRule& r, bool sink, int32_t n_steps) {
+  int32_t len = r.longest, per = r.ordinary;
+  if (sink && per == 1) {
+    if (len >= 256)
+      per = 2;
+    else
+      len = imin32(len, 128);
+  }
+  const int32_t most = sink ? r.sink : r.ordinary;
+  return n_steps >= 1 << 28 ? most : imax32(1, imin32((n_steps * per + len - 1) / len, most));
+}
+
 // Every pair of queries q0 .. q1 and keys k0 .. k1 lies inside the sequence and
 // is legal (tile_full for any query and key range, in 32-bit scalars; bounds
 // clamped to n_k).

@@ -222,6 +222,19 @@ def test_bwd_workspace_without_sink_has_no_parts():
     assert abi.cowa_bwd_workspace_size(p) == _split_ws(32 * 8192, 8, 8, 64, 128)
 
 
+@pytest.mark.parametrize("n,near,batch", [(1000, 128, 3), (4096, 1024, 4), (8192, 1024, 4), (65536, 4096, 2)])
+def test_bwd_column_parts_follow_from_one_head_of_one_sequence(n, near, batch):
+    """The workspace's partials (beside the two per-row arrays) of all 8 KV heads are 8
+    times those of one rank, and of a batch as many times those of one sequence
+    as it has: the same parts of every column, whatever the schedule's tiles."""
+    def parts(bsz, h_q, h_k, offset, tile=128):
+        p = cowa.make_params(bsz, n, n, h_q, h_k, 128, 64, near, tile, tile, h_k_total=8, h_k_offset=offset)
+        return (abi.cowa_bwd_workspace_size(p) - _split_ws(bsz * h_q * n, 0, 1, 128, 128)) / (2 * 128 * 128 * 4)
+    whole = parts(1, 32, 8, 0)
+    assert whole > 0 and parts(batch, 32, 8, 0) == batch * whole and parts(1, 32, 8, 0, 64) == whole
+    assert all(8 * parts(1, 4, 1, r) == whole for r in (0, 3, 7))
+
+
 def test_decode_argument_errors_on_host():
     lib = _lib()
     d = cowa.make_decode_params(4, 8, 2, 128, 1000, 16, 64)

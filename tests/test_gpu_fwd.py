@@ -157,14 +157,16 @@ def test_fwd_wide_score_range(lift, lse_min, d, tile):
     compare("LSE", to_host(lse), l_r)
 
 
+@pytest.mark.parametrize("window", [(0, 20, 0, 0), (0, 0, 33, 20)])
 @pytest.mark.parametrize("level", [-62.0, -67.0, -73.0, 40.0])
 @pytest.mark.parametrize("d", [64, 128])
-def test_fwd_rows_without_a_starting_offset(level, d):
-    """A near window of 20 keys: most rows meet no legal key among the first 32
-    of their first block, so the untracked launch starts them at offset 0.  Their
-    scores lie near `level` (base 2), on both sides of the sum below which such
-    rows go to the tracked launch (2^-70) and, at 40, high enough that the offset
-    moves at once."""
+def test_fwd_rows_without_a_starting_offset(level, d, window):
+    """Rows that meet no legal key among the first 32 of their tile's first block: a
+    near window of 20 keys, whose rows take their offset from their own diagonal,
+    and a window of the 20 keys at distance 33 to 52, whose rows see no key there
+    either and start at offset 0.  Their scores lie near `level` (base 2), on both
+    sides of the sum below which rows without an offset go to the tracked launch
+    (2^-60) and, at 40, high enough that the offset moves at once."""
     dev = need_gpu()
     import paper_2609_32704_amd as cowa
     n, h_q, h_k = 400, 4, 1
@@ -178,9 +180,9 @@ def test_fwd_rows_without_a_starting_offset(level, d):
     q, k, v = (to_dev(b, dev) for b in bits)
     o = torch.full_like(q, float("nan"))
     lse = torch.full((1, h_q, n), float("nan"), dtype=torch.float32, device=dev)
-    cowa.fwd(q, k, v, 0, 20, 128, 128, d ** -0.5, out=o, lse=lse)
+    cowa.fwd(q, k, v, 0, 0, 128, 128, d ** -0.5, out=o, lse=lse, windows=[window])
     torch.cuda.synchronize()
-    o_r, l_r = ref.forward(vals[0], vals[1], vals[2], 0, 20, d ** -0.5)
+    o_r, l_r = ref.forward(vals[0], vals[1], vals[2], 0, 0, d ** -0.5, windows=[window])
     compare("O", to_host(o), o_r)
     compare("LSE", to_host(lse), l_r)
 

@@ -1,5 +1,5 @@
-"""One rank's share of the 8-way KV-head split at 131072 tokens equals the
-corresponding slice of the all-heads run, bit for bit.
+"""One rank's share of a KV-head split, and one sequence of a batch, equal the
+corresponding slice of the whole, bit for bit.
 
 Sec. 2.3 (global KV-head assignment): rank r of a tensor-parallel group owns KV
 head r and the QO heads of its group, builds its windows from the global head
@@ -8,9 +8,12 @@ library takes the global index through h_k_offset / h_k_total, so the call
 with h_k = 1, h_q = 4, h_k_offset = r, h_k_total = 8 on the slices of the
 tensors must reproduce the all-heads call's O, LSE, dQ, dK and dV for those
 heads exactly: every row and column is computed by the same steps in the same
-order (the dK/dV split plan depends only on the column lengths, which are the
-same).  This checks the full-size launch configuration of the benchmark at
-every output element, without an oracle.
+order.  In the dK/dV pass that order includes the parts into which a column is
+cut, which follow from one KV head of one sequence and the number of all heads,
+whoever walks them (a workgroup per part, or per column where a batch has many).
+The 131072-token case is the benchmark's full-size launch configuration at every
+output element, without an oracle; the shorter ones are the sizes at which
+columns are cut, taken one by one and, in a batch, one after the other.
 """
 
 import pytest
@@ -60,3 +63,34 @@ def test_rank_share_equals_all_heads_slice():
                 log(f"  {name}: max |diff| {diff:.3e}")
             assert same, f"rank {r}: {name} differs from the all-heads run"
         log(f"  rank {r}: O, LSE, dQ, dK, dV bitwise equal")
+
+
+@pytest.mark.parametrize("n,batch,h_q,h_k,d,near", [
+    # columns in parts: by a workgroup each alone, in a batch by a workgroup each (1000) or
+    # by one per column (the next two); sink columns only (4096, 65536); d = 64
+    (1000, 4, 32, 8, 128, 128), (1000, 10, 32, 8, 128, 128), (2048, 4, 32, 8, 128, 1024), (4096, 4, 32, 8, 128, 1024),
+    (65536, 2, 32, 8, 128, 4096), (1500, 3, 16, 4, 64, 128), (1500, 104, 8, 2, 64, 128)])
+def test_rank_and_batch_entry_equal_the_whole(n, batch, h_q, h_k, d, near):
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(7)
+    q, k, v, do = (torch.randn((batch, h, n, d), generator=gen, device=dev).to(torch.bfloat16)
+                   for h in (h_q, h_k, h_k, h_q))
+
+    def run(x, h_k_offset):
+        o, lse = cowa.fwd(*x[:3], 64, near, 128, 128, h_k_total=h_k, h_k_offset=h_k_offset)
+        return (o, lse) + cowa.bwd(*x[:3], o, lse, x[3], 64, near, 128, 128, h_k_total=h_k, h_k_offset=h_k_offset)
+
+    log(f"{batch} x {n} tokens, {h_q}/{h_k} heads, d={d}")
+    names, g = ("O", "LSE", "dQ", "dK", "dV"), h_q // h_k
+    whole = run((q, k, v, do), 0)
+    for b in (0, batch - 1):
+        alone = run([x[b:b + 1].contiguous() for x in (q, k, v, do)], 0)
+        for name, x, y in zip(names, alone, whole):
+            assert torch.equal(x, y[b:b + 1]), f"entry {b} of {batch}: {name} differs from the batch's"
+        for r in (0, h_k - 1):
+            part = run([x[b:b + 1, m * r:m * r + m].contiguous() for x, m in ((q, g), (k, 1), (v, 1), (do, g))], r)
+            for name, x, y in zip(names, part, alone):
+                m = 1 if name in ("dK", "dV") else g
+                assert torch.equal(x, y[:, m * r:m * r + m]), f"rank {r}: {name} differs from all heads'"
