@@ -252,6 +252,27 @@ cowa::BwdSplit bwd_split_plan(const cowa_params* p, const Layout& L) {
   return sp;
 }
 
+// The shapes of a row pass that the call's heads take (fwd_shape or dq_shape).
+template <class Shape>
+cowa::RowPlan row_plan(const cowa_params* p, const Layout& L, Shape shape) {
+  cowa::RowPlan plan;
+  const int G = p->h_q / p->h_k;
+  for (size_t b = 0; b < L.seq.size(); ++b) {
+    if (L.seq[b].n_q == 0) continue;
+    cowa::Geo32 last{};
+    for (int h = 0; h < p->h_k; ++h) {
+      const cowa::Geo32 g = cowa::geo32(geo_of(p, L, (int)b, h));
+      const bool same = h > 0 && g.w_near == last.w_near && g.w_sink == last.w_sink && g.hi - g.lo == last.hi - last.lo;
+      last = g;
+      if (same) continue;
+      const int s = shape(g, G, p->head_dim);
+      plan.list64[s] = std::max(plan.list64[s], cowa::row_list_blocks(g, 256, 64));
+      plan.list128[s] = std::max(plan.list128[s], cowa::row_list_blocks(g, 256, 128));
+    }
+  }
+  return plan;
+}
+
 // Every schedule-relevant field must match (the digest covers windows and lengths).
 bool same_schedule(const cowa_params* a, const cowa_params* b) {
   return a->n_q == b->n_q && a->n_k == b->n_k && a->h_k == b->h_k && a->w_sink == b->w_sink &&
@@ -562,7 +583,8 @@ cowa_status cowa_fwd(const cowa_params* p, const cowa_schedule_t* s, const void*
     return hip_status(cowa::launch_fwd_fp32(*p, sv, static_cast<const float*>(q), static_cast<const float*>(k),
                                             static_cast<const float*>(v), static_cast<float*>(o), lse, st),
                       "fp32 forward launch");
-  return hip_status(cowa::launch_fwd_bf16(*p, sv, q, k, v, o, lse, st), "bf16 forward launch");
+  return hip_status(cowa::launch_fwd_bf16(*p, sv, row_plan(p, L, cowa::fwd_shape), q, k, v, o, lse, st),
+                    "bf16 forward launch");
 }
 
 cowa_status cowa_bwd_workspace_size(const cowa_params* p, size_t* bytes) {
@@ -675,8 +697,8 @@ cowa_status cowa_bwd_dq(const cowa_params* p, const cowa_schedule_t* s, const vo
   COWA_TRY(check_dq_ptrs(q, k, v, d_o, dq));
   COWA_TRY(check_device());
   if (s->n_qt == 0) return COWA_OK;
-  return hip_status(cowa::launch_bwd_dq(*p, cowa::sched_view(s), q, k, v, d_o, dq, w,
-                                        static_cast<hipStream_t>(stream)),
+  return hip_status(cowa::launch_bwd_dq(*p, cowa::sched_view(s), row_plan(p, L, cowa::dq_shape), q, k, v, d_o, dq,
+                                        w, static_cast<hipStream_t>(stream)),
                     "backward dQ launch");
 }
 
@@ -702,7 +724,8 @@ cowa_status cowa_bwd(const cowa_params* p, const cowa_schedule_t* s, const void*
   if (s->n_kt > 0)
     COWA_TRY(hip_status(cowa::launch_bwd_main(*p, sv, q, k, v, d_o, dk, dv, w, st), "backward dK/dV launch"));
   if (s->n_qt == 0) return COWA_OK;
-  return hip_status(cowa::launch_bwd_dq(*p, sv, q, k, v, d_o, dq, w, st), "backward dQ launch");
+  return hip_status(cowa::launch_bwd_dq(*p, sv, row_plan(p, L, cowa::dq_shape), q, k, v, d_o, dq, w, st),
+                    "backward dQ launch");
 }
 
 cowa_status cowa_decode_workspace_size(const cowa_decode_params* p, size_t* bytes) {

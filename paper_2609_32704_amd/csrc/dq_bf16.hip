@@ -116,6 +116,7 @@ __global__ void __launch_bounds__(256, dq_occupancy(NQT))
   const SeqCtx sc = row_ctx(p, sv, rt, row, unit, hk, q0);
   const int n_q = sc.n_q, n_k = sc.n_k;
   if (q0 >= n_q) return;
+  if (rt.shape >= 0 && dq_shape(sc.g, G, D) != rt.shape) return;  // (another launch's)
   const int h0 = (hk * (G / hpw) + group) * hpw;  // first QO head (all in KV group hk)
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -434,7 +435,7 @@ __global__ void __launch_bounds__(256, dq_occupancy(NQT))
   }
 
   // dQ = scale dQ^T, written once per row through LDS: once every wave's last
-  // reads are done, each wave stages its 64 rows and stores whole rows, 16
+  // reads are done, each wave stages its rows and stores whole rows, 16
   // bytes per lane, instead of 16-byte pieces of 32 rows per store in the
   // accumulator layout
   const float scale = p.softmax_scale;
@@ -463,17 +464,17 @@ __global__ void __launch_bounds__(256, dq_occupancy(NQT))
 }
 
 template <int D, int NQT, int BK>
-hipError_t launch(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                  const void* d_o, const float* nl, const float* nd, void* dq, hipStream_t stream) {
+hipError_t launch(const cowa_params& p, const SchedView& sv, int64_t list, int shape, const void* q, const void* k,
+                  const void* v, const void* d_o, const float* nl, const float* nd, void* dq, hipStream_t stream) {
   using C = Dq32Cfg<D, NQT, BK>;
   auto kern = bwd_dq32<D, NQT, BK>;
   const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
   if (err != hipSuccess) return err;
   // as many heads of the group per workgroup as it has, up to one per wave
   const int G = p.h_q / p.h_k, hpw = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
-  const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw);
-  const int cap = list_capacity(p, sv, rt.R, BK);
-  if (cap > C::max_kblocks()) return hipErrorInvalidValue;
+  const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw, shape);
+  const int cap = (int)list;  // (of 256 rows, at least as many as a tile has)
+  if (list > C::max_kblocks()) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3((unsigned)rt.blocks), dim3(256), C::lds_bytes(cap), stream, p, sv, rt, cap,
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<const __bf16*>(d_o), nl, nd, static_cast<__bf16*>(dq));
@@ -486,25 +487,26 @@ hipError_t launch(const cowa_params& p, const SchedView& sv, const void* q, cons
 // schedule tile, as the entry point documents them.
 int bwd_dq_max_kblocks(int d, int tk) { return (160 * 1024 - 4 * tk * d * 2) / 4; }
 
-hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                         const void* d_o, void* dq, const BwdWork& w, hipStream_t stream) {
-  // Which shape: V the visible keys of a row, W the 256-row tiles of one KV head's
-  // group in one sequence (see the measurements at the top of this file; neither
-  // batch nor the other heads enter, so a sequence's or a rank's result does not
-  // depend on them).  The 64-row shape with 128-key
-  // blocks needs its row's list beside 128 KB of buffers (up to 1M keys).
-  if (p.head_dim == 128) {
-    const int64_t V = visible_bound(p, sv);
-    const int64_t W = (int64_t)(p.h_q / p.h_k) * p.n_q / 256;
-    if (V >= 8192 && W >= 32 && list_capacity(p, sv, 256, 128) <= Dq32Cfg<128, 2, 128>::max_kblocks())
-      return launch<128, 2, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-    if (V >= 4096 && V < 8192 && W >= 256) return launch<128, 2, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-    return launch<128, 1, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const RowPlan& plan, const void* q,
+                         const void* k, const void* v, const void* d_o, void* dq, const BwdWork& w,
+                         hipStream_t stream) {
+  // the shapes of the call's heads (dq_shape; measurements at the top of this file)
+  static_assert(Dq32Cfg<128, 2, 128>::max_kblocks() == kDqList128 && Dq32Cfg<64, 1, 64>::max_kblocks() == kDqList64,
+                "dq_shape");
+  hipError_t err = hipSuccess;
+  for (int s = kRowShapes - 1; s >= 0 && err == hipSuccess; --s) {
+    if (!plan.used(s)) continue;
+    const int only = plan.one_shape() ? -1 : s;
+    const int64_t l64 = plan.list64[s], l128 = plan.list128[s];
+    if (p.head_dim == 128)
+      err = s == 2   ? launch<128, 2, 128>(p, sv, l128, only, q, k, v, d_o, w.nl, w.nd, dq, stream)
+            : s == 1 ? launch<128, 2, 64>(p, sv, l64, only, q, k, v, d_o, w.nl, w.nd, dq, stream)
+                     : launch<128, 1, 64>(p, sv, l64, only, q, k, v, d_o, w.nl, w.nd, dq, stream);
+    else
+      err = s == 1 ? launch<64, 1, 128>(p, sv, l128, only, q, k, v, d_o, w.nl, w.nd, dq, stream)
+                   : launch<64, 1, 64>(p, sv, l64, only, q, k, v, d_o, w.nl, w.nd, dq, stream);
   }
-  // (128-key blocks halve the list where a row of more than 2M keys needs it)
-  if (list_capacity(p, sv, 128, 64) > Dq32Cfg<64, 1, 64>::max_kblocks())
-    return launch<64, 1, 128>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
-  return launch<64, 1, 64>(p, sv, q, k, v, d_o, w.nl, w.nd, dq, stream);
+  return err;
 }
 
 }  // namespace cowa

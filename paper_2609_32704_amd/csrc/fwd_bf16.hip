@@ -119,25 +119,35 @@ struct FwdCfg {
   static_assert(NCH == 2 || NCH == 4, "64- or 128-key blocks");
 };
 
+// A workgroup's row tile: its rows (rt.R from query q0 on of each of hpw QO heads,
+// group `group` of KV head hk) in sequence sc.
+struct RowItem {
+  SeqCtx sc;
+  int hk, group, q0;
+};
+__device__ inline bool row_work(const cowa_params& p, const SchedView& sv, const RowTiles& rt, RowItem& it) {
+  int row, unit;
+  if (!row_item(rt, grid_units(p, sv), p.h_q / p.h_k / rt.hpw, blockIdx.x, row, unit, it.group)) return false;
+  it.sc = row_ctx(p, sv, rt, row, unit, it.hk, it.q0);
+  return it.q0 < it.sc.n_q;
+}
+
 // rt: the launch's rows; R = rows per (workgroup, head)
 template <int D, int NQT, int BK, bool TRACK>
-__global__ void __launch_bounds__(256, fwd_occupancy(NQT))
-    fwd_bf16_kernel(cowa_params p, SchedView sv, RowTiles rt, int cap, const __bf16* __restrict__ q,
-                    const __bf16* __restrict__ k, const __bf16* __restrict__ v, __bf16* __restrict__ o,
-                    float* __restrict__ lse) {
+__device__ __forceinline__ void fwd_rows(const cowa_params& p, const RowTiles& rt, const RowItem& it, int cap,
+                                         unsigned char* smem, const __bf16* __restrict__ q,
+                                         const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                                         __bf16* __restrict__ o, float* __restrict__ lse) {
   using C = FwdCfg<D, NQT, BK>;
   using T = typename C::T;
   constexpr int KS = C::KS, MD = C::MD, NCH = C::NCH, NG = C::NG;
-  extern __shared__ __align__(1024) unsigned char smem[];
 
   const int hpw = rt.hpw, wph = C::NW / hpw;  // heads per workgroup, waves per head
   const int G = p.h_q / p.h_k;
-  int row, unit, group, hk, q0;
-  if (!row_item(rt, grid_units(p, sv), G / hpw, blockIdx.x, row, unit, group)) return;
-  const SeqCtx sc = row_ctx(p, sv, rt, row, unit, hk, q0);
+  const SeqCtx& sc = it.sc;
+  const int hk = it.hk, q0 = it.q0;
   const int n_q = sc.n_q, n_k = sc.n_k;
-  if (q0 >= n_q) return;
-  const int h0 = (hk * (G / hpw) + group) * hpw;  // first QO head of this workgroup (all in KV group hk)
+  const int h0 = (hk * (G / hpw) + it.group) * hpw;  // first QO head of this workgroup (all in KV group hk)
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31, hh = lane >> 5;  // MFMA column and half
@@ -772,31 +782,62 @@ __global__ void __launch_bounds__(256, fwd_occupancy(NQT))
 }
 
 template <int D, int NQT, int BK, bool TRACK>
-hipError_t launch_one(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v, void* o,
-                      float* lse, hipStream_t stream) {
-  using C = FwdCfg<D, NQT, BK>;
-  auto kern = fwd_bf16_kernel<D, NQT, BK, TRACK>;
+__global__ void __launch_bounds__(256, fwd_occupancy(NQT))
+    fwd_bf16_kernel(cowa_params p, SchedView sv, RowTiles rt, int cap, const __bf16* __restrict__ q,
+                    const __bf16* __restrict__ k, const __bf16* __restrict__ v, __bf16* __restrict__ o,
+                    float* __restrict__ lse) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  RowItem it;
+  if (!row_work(p, sv, rt, it)) return;
+  if (rt.shape >= 0 && fwd_shape(it.sc.g, p.h_q / p.h_k, D) != rt.shape) return;  // (another launch's)
+  fwd_rows<D, NQT, BK, TRACK>(p, rt, it, cap, smem, q, k, v, o, lse);
+}
+
+// Both shapes of d = 64, for calls whose sequences and heads differ: they have the
+// same row tiles, so each workgroup takes its head's (10 ragged sequences of up to
+// 6000 tokens, 16/4 heads: a launch per shape made the
+// training pass 422 us instead of 410, this kernel 389 instead of 391).
+__global__ void __launch_bounds__(256, fwd_occupancy(1))
+    fwd_bf16_d64(cowa_params p, SchedView sv, RowTiles rt, int cap, const __bf16* __restrict__ q,
+                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, __bf16* __restrict__ o,
+                 float* __restrict__ lse) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  RowItem it;
+  if (!row_work(p, sv, rt, it)) return;
+  if (fwd_shape(it.sc.g, p.h_q / p.h_k, 64) == 1)
+    fwd_rows<64, 1, 128, false>(p, rt, it, cap, smem, q, k, v, o, lse);
+  else
+    fwd_rows<64, 1, 64, false>(p, rt, it, cap, smem, q, k, v, o, lse);
+}
+
+// C: the shape (the larger one's LDS of a kernel that has two); list: capacity
+template <class C, class Kernel>
+hipError_t launch_one(Kernel kern, const cowa_params& p, const SchedView& sv, int64_t list, int shape, const void* q,
+                      const void* k, const void* v, void* o, float* lse, hipStream_t stream) {
   const hipError_t err = allow_lds(reinterpret_cast<const void*>(kern), C::LDS_MAX);
   if (err != hipSuccess) return err;
   // as many heads of the group per workgroup as it has, up to one per wave: the
   // fewest query rows per head, and so the fewest masked or unneeded pairs
   const int G = p.h_q / p.h_k, hpw = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
-  const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw);
-  const int cap = list_capacity(p, sv, rt.R, BK);
-  if (cap > C::max_kblocks()) return hipErrorInvalidValue;
+  const RowTiles rt = row_tiles(p, sv, hpw, C::NQW * C::NW / hpw, shape);
+  const int cap = (int)list;  // (of 256 rows, at least as many as a tile has)
+  if (list > C::max_kblocks()) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3((unsigned)rt.blocks), dim3(256), C::lds_bytes(cap), stream, p, sv, rt, cap,
                      static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v),
                      static_cast<__bf16*>(o), lse);
   return hipGetLastError();
 }
+template <int D, int NQT, int BK, bool TRACK>
+hipError_t launch_shape(const cowa_params& p, const SchedView& sv, int64_t list, int shape, const void* q,
+                        const void* k, const void* v, void* o, float* lse, hipStream_t stream) {
+  return launch_one<FwdCfg<D, NQT, BK>>(fwd_bf16_kernel<D, NQT, BK, TRACK>, p, sv, list, shape, q, k, v, o, lse, stream);
+}
 
-// Which shape runs the untracked launch.  32 rows per wave leave room for two
+// The shapes of the untracked launch (fwd_shape).  32 rows per wave leave room for two
 // waves per SIMD (at d = 128 with 64-key blocks), which hide each other's row
 // starts, copies and exponentials, and make twice as many workgroups; 64 rows
 // per wave read each K/V fragment from LDS once for two products, which wins
-// only where rows are long and many.  The rule looks at one KV head of one
-// sequence (so that a sequence's result does not depend on its batch, nor a
-// rank's on the heads of the others): V the visible keys of a row, W the
+// only where rows are long and many.  V: the visible keys of a row, W: the
 // 256-row tiles of the head's group.  Measured at d = 128 (us, 32 rows and 64-key
 // blocks / 64 rows and 128-key blocks):
 //   1000 tokens, 32/8 heads (V 250, W 15)                23 /   37
@@ -812,24 +853,25 @@ hipError_t launch_one(const cowa_params& p, const SchedView& sv, const void* q, 
 // (3237 against 3472 us there; 27 against 25 at 2048 tokens, V 900).
 // (Past 1M keys in a row the list of 128-key blocks does not fit beside its buffers.)
 template <int D>
-hipError_t launch_d(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v, void* o,
-                    float* lse, hipStream_t stream) {
-  const int64_t V = visible_bound(p, sv);
-  const int64_t W = (int64_t)(p.h_q / p.h_k) * p.n_q / 256;
-  hipError_t err;
+hipError_t launch_d(const cowa_params& p, const SchedView& sv, const RowPlan& plan, const void* q, const void* k,
+                    const void* v, void* o, float* lse, hipStream_t stream) {
+  const bool one = plan.one_shape();
+  hipError_t err = hipSuccess;
   if constexpr (D == 128) {
-    if (((V >= 8192 && W >= 32) || (V >= 4096 && W >= 512)) &&
-        list_capacity(p, sv, 256, 128) <= FwdCfg<128, 2, 128>::max_kblocks())
-      err = launch_one<128, 2, 128, false>(p, sv, q, k, v, o, lse, stream);
-    else
-      err = launch_one<128, 1, 64, false>(p, sv, q, k, v, o, lse, stream);
-    if (err == hipSuccess) err = launch_one<128, 2, 64, true>(p, sv, q, k, v, o, lse, stream);
+    static_assert(FwdCfg<128, 2, 128>::max_kblocks() == kFwdList128, "fwd_shape");
+    if (plan.used(1)) err = launch_shape<128, 2, 128, false>(p, sv, plan.list128[1], one ? -1 : 1, q, k, v, o, lse, stream);
+    if (err == hipSuccess && plan.used(0))
+      err = launch_shape<128, 1, 64, false>(p, sv, plan.list64[0], one ? -1 : 0, q, k, v, o, lse, stream);
+    if (err == hipSuccess) err = launch_shape<128, 2, 64, true>(p, sv, plan.most64(), -1, q, k, v, o, lse, stream);
   } else {
-    if (V >= 1024)
-      err = launch_one<64, 1, 128, false>(p, sv, q, k, v, o, lse, stream);
+    if (!one)
+      err = launch_one<FwdCfg<64, 1, 128>>(fwd_bf16_d64, p, sv, imax64(plan.list128[1], plan.list64[0]), -1, q, k, v, o,
+                                           lse, stream);
+    else if (plan.used(1))
+      err = launch_shape<64, 1, 128, false>(p, sv, plan.list128[1], -1, q, k, v, o, lse, stream);
     else
-      err = launch_one<64, 1, 64, false>(p, sv, q, k, v, o, lse, stream);
-    if (err == hipSuccess) err = launch_one<64, 1, 128, true>(p, sv, q, k, v, o, lse, stream);
+      err = launch_shape<64, 1, 64, false>(p, sv, plan.list64[0], -1, q, k, v, o, lse, stream);
+    if (err == hipSuccess) err = launch_shape<64, 1, 128, true>(p, sv, plan.most128(), -1, q, k, v, o, lse, stream);
   }
   return err;
 }
@@ -846,10 +888,10 @@ bool fwd_bf16_supported(int d, int tq, int tk) {
   return (d == 64 || d == 128) && (tq == 64 || tq == 128) && (tk == 64 || tk == 128);
 }
 
-hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                           void* o, float* lse, hipStream_t stream) {
-  return p.head_dim == 128 ? launch_d<128>(p, sv, q, k, v, o, lse, stream)
-                           : launch_d<64>(p, sv, q, k, v, o, lse, stream);
+hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const RowPlan& plan, const void* q,
+                           const void* k, const void* v, void* o, float* lse, hipStream_t stream) {
+  return p.head_dim == 128 ? launch_d<128>(p, sv, plan, q, k, v, o, lse, stream)
+                           : launch_d<64>(p, sv, plan, q, k, v, o, lse, stream);
 }
 
 }  // namespace cowa

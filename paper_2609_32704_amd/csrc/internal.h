@@ -115,8 +115,19 @@ int bwd_main_max_qblocks(int head_dim);
 // the dQ pass keeps one row's block list in LDS: at most this many key blocks
 int bwd_dq_max_kblocks(int head_dim, int tile_k);
 
-hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const void* q, const void* k,
-                           const void* v, void* o, float* lse, hipStream_t stream);
+// What a call's KV heads and sequences need of a row pass: the longest block
+// list (row_list_blocks of 256 rows) per shape (fwd_shape, dq_shape) and block
+// size; zero where no head takes the shape.
+struct RowPlan {
+  int64_t list64[kRowShapes] = {0, 0, 0}, list128[kRowShapes] = {0, 0, 0};
+  bool used(int shape) const { return list64[shape] > 0; }
+  bool one_shape() const { return used(0) + used(1) + used(2) == 1; }
+  int64_t most64() const { return imax64(list64[0], imax64(list64[1], list64[2])); }
+  int64_t most128() const { return imax64(list128[0], imax64(list128[1], list128[2])); }
+};
+
+hipError_t launch_fwd_bf16(const cowa_params& p, const SchedView& sv, const RowPlan& plan, const void* q,
+                           const void* k, const void* v, void* o, float* lse, hipStream_t stream);
 
 // Split of the dK/dV pass's columns into parts (column_rule).  Every query that
 // reaches a sink key sees it, so the sink columns have query lists as long as the
@@ -170,8 +181,9 @@ hipError_t launch_bwd_prepare(const cowa_params& p, const void* o, const void* d
                               const BwdWork& w, hipStream_t stream);
 hipError_t launch_bwd_main(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
                            const void* d_o, void* dk, void* dv, const BwdWork& w, hipStream_t stream);
-hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const void* q, const void* k, const void* v,
-                         const void* d_o, void* dq, const BwdWork& w, hipStream_t stream);
+hipError_t launch_bwd_dq(const cowa_params& p, const SchedView& sv, const RowPlan& plan, const void* q,
+                         const void* k, const void* v, const void* d_o, void* dq, const BwdWork& w,
+                         hipStream_t stream);
 bool decode_supported(int head_dim, int group);
 size_t decode_workspace_bytes(const cowa_decode_params& p);
 int32_t decode_num_splits(const cowa_decode_params& p);

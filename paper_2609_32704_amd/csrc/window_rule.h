@@ -275,6 +275,46 @@ __host__ __device__ inline int32_t column_parts(const ColumnRule& r, bool sink, 
   return n_steps >= 1 << 28 ? most : imax32(1, imin32((n_steps * per + len - 1) / len, most));
 }
 
+// Blocks of bk keys that hold a key some query of R consecutive ones sees, at most.
+__host__ __device__ inline int64_t row_list_blocks(const Geo32& g, int32_t R, int32_t bk) {
+  const int64_t runs = ((int64_t)R + g.w_near) / bk + 2 + ((int64_t)R + g.hi - g.lo) / bk + 2 + (g.w_sink + bk - 1) / bk;
+  return imin64(runs, ((int64_t)g.n_k + bk - 1) / bk);
+}
+
+// Which shape of the forward and of the dQ pass takes a KV head of a sequence.
+// A shape has row tiles and key blocks of its own, which fix how O, LSE and dQ
+// are rounded, so the choice follows from that head and that sequence alone (V:
+// the visible keys of a row; W: the 256-row tiles of the head's group): a
+// sequence gives the same bits in any batch, packed or not, and a head on any
+// rank.  Where a call's heads and sequences differ, each shape has a launch that
+// takes its own.  The measurements are beside the kernels' launches.
+struct RowLoad {
+  int64_t v, w;
+};
+__host__ __device__ inline RowLoad row_load(const Geo32& g, int32_t group) {
+  return RowLoad{imin64((int64_t)g.w_near + g.w_sink + (g.hi > g.lo ? g.hi - g.lo : 0), g.n_k), (int64_t)group * g.n_q / 256};
+}
+// longest block lists that fit beside the buffers of the 64-row shapes (128-key
+// blocks, d = 128) and of the dQ pass's 64-key blocks at d = 64
+constexpr int32_t kFwdList128 = 8188, kDqList128 = 8192, kDqList64 = 32768;
+constexpr int kRowShapes = 3;
+// d = 128: 32 rows per wave and 64-key blocks (0) or 64 and 128 (1); d = 64: 32
+// rows and 64-key (0) or 128-key blocks (1)
+__host__ __device__ inline int32_t fwd_shape(const Geo32& g, int32_t group, int32_t head_dim) {
+  const RowLoad r = row_load(g, group);
+  if (head_dim == 64) return r.v >= 1024 ? 1 : 0;
+  return ((r.v >= 8192 && r.w >= 32) || (r.v >= 4096 && r.w >= 512)) && row_list_blocks(g, 256, 128) <= kFwdList128 ? 1 : 0;
+}
+// d = 128: 32 rows per wave and 64-key blocks (0), 64 rows and 64-key (1) or 128-key
+// blocks (2); d = 64: 32 rows and 64-key blocks (0), or 128-key blocks, which halve
+// the list, where a row of more than 2M keys needs it (1)
+__host__ __device__ inline int32_t dq_shape(const Geo32& g, int32_t group, int32_t head_dim) {
+  const RowLoad r = row_load(g, group);
+  if (head_dim == 64) return row_list_blocks(g, 256, 64) > kDqList64 ? 1 : 0;
+  if (r.v >= 8192) return r.w >= 32 && row_list_blocks(g, 256, 128) <= kDqList128 ? 2 : 0;
+  return r.v >= 4096 && r.w >= 256 ? 1 : 0;
+}
+
 // Every pair of queries q0 .. q1 and keys k0 .. k1 lies inside the sequence and
 // is legal (tile_full for any query and key range, in 32-bit scalars; bounds
 // clamped to n_k).

@@ -88,9 +88,11 @@ __device__ inline SeqCtx seq_ctx(const cowa_params& p, const SchedView& sv, int 
 // Rows and clusters are rounded up; the padding's workgroups end at once.
 struct RowTiles {
   int32_t n_rows, R, hpw, cq, blocks;
+  int32_t shape;  // take only the heads of this shape (fwd_shape, dq_shape), or all of them (-1)
 };
-inline RowTiles row_tiles(const cowa_params& p, const SchedView& sv, int hpw, int R) {
+inline RowTiles row_tiles(const cowa_params& p, const SchedView& sv, int hpw, int R, int shape) {
   RowTiles t;
+  t.shape = shape;
   t.R = R;
   t.hpw = hpw;
   if (!sv.ragged)
@@ -113,41 +115,6 @@ __device__ inline bool row_item(const RowTiles& t, int units, int groups, int id
   row = t.n_rows - 1 - (r * t.cq + item / groups);
   return row >= 0;
 }
-// Widest near, sink and long-range windows of any KV head (keys), for the
-// longest sequence.
-struct WindowBound {
-  int64_t n_k, near, sink, width;
-};
-inline WindowBound window_bound(const cowa_params& p, const SchedView& sv) {
-  WindowBound b{sv.ragged ? (int64_t)sv.max_kt * p.tile_k : p.n_k, 0, 0, 0};
-  if (p.windows) {
-    for (int h = 0; h < p.h_k; ++h) {
-      b.near = imax64(b.near, p.windows[h].near);
-      b.sink = imax64(b.sink, p.windows[h].sink);
-      b.width = imax64(b.width, p.windows[h].width);
-    }
-  } else {
-    b.near = p.w_near;
-    b.sink = p.w_sink;
-    b.width = (imax64(b.n_k - p.w_near - p.w_sink, 0) + p.h_k_total - 1) / p.h_k_total;
-  }
-  b.near = imin64(b.near, b.n_k);
-  b.sink = imin64(b.sink, b.n_k);
-  b.width = imin64(b.width, b.n_k);
-  return b;
-}
-// visible keys of any query, at most
-inline int64_t visible_bound(const cowa_params& p, const SchedView& sv) {
-  const WindowBound b = window_bound(p, sv);
-  return imin64(b.near + b.sink + b.width, b.n_k);
-}
-// blocks of bk keys that hold a key some query of R consecutive ones sees, at most
-inline int list_capacity(const cowa_params& p, const SchedView& sv, int R, int bk) {
-  const WindowBound b = window_bound(p, sv);
-  const int64_t runs = (R + b.near) / bk + 2 + (R + b.width) / bk + 2 + (b.sink + bk - 1) / bk;
-  return (int)imin64(runs, (b.n_k + bk - 1) / bk);
-}
-
 // Context of row tile `row`; q0: its first query (>= n_q: the tile is empty).
 __device__ inline SeqCtx row_ctx(const cowa_params& p, const SchedView& sv, const RowTiles& rt, int row, int unit, int& hk,
                                  int& q0) {

@@ -94,3 +94,46 @@ def test_rank_and_batch_entry_equal_the_whole(n, batch, h_q, h_k, d, near):
             for name, x, y in zip(names, part, alone):
                 m = 1 if name in ("dK", "dV") else g
                 assert torch.equal(x, y[:, m * r:m * r + m]), f"rank {r}: {name} differs from all heads'"
+
+
+@pytest.mark.parametrize("lens,h_q,h_k,d,near,tile,windows", [
+    # sequences and heads that take different shapes of the forward and the dQ pass:
+    # d = 128, rows of 8192 visible keys beside short ones; 4096 and many rows; one
+    # head dense and the others narrow; d = 64 around 1024 visible keys
+    ([(8200, 8200), (900, 900), (1, 70)], 8, 2, 128, 8192, 128, None),
+    ([(300, 300), (32800, 32800), (0, 40)], 8, 2, 128, 4000, 64, None),
+    ([(8300, 8300), (600, 1000)], 8, 4, 128, 512,
+     128, [(16, 512, 0, 40), (16, 9000, 0, 0), (16, 512, 100, 300), (0, 64, 0, 0)]),
+    ([(500, 500), (3000, 3000), (77, 2500), (64, 64)], 16, 4, 64, 512, 64, None)])
+def test_packed_sequence_and_window_head_equal_alone(lens, h_q, h_k, d, near, tile, windows):
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    cq = [sum(a for a, _ in lens[:x]) for x in range(len(lens) + 1)]
+    ck = [sum(b for _, b in lens[:x]) for x in range(len(lens) + 1)]
+    q, k, v, do = (torch.randn((h, n, d), generator=gen, device=dev).to(torch.bfloat16)
+                   for h, n in ((h_q, cq[-1]), (h_k, ck[-1]), (h_k, ck[-1]), (h_q, cq[-1])))
+
+    def run(x, cq, ck, wins, h_k_offset):
+        kw = dict(h_k_total=h_k, h_k_offset=h_k_offset, windows=wins)
+        o, lse = cowa.fwd_varlen(*x[:3], cq, ck, 16, near, tile, tile, **kw)
+        return (o, lse) + cowa.bwd_varlen(*x[:3], o, lse, x[3], cq, ck, 16, near, tile, tile, **kw)
+
+    log(f"{lens}, {h_q}/{h_k} heads, d={d}, windows {windows}")
+    names, g = ("O", "LSE", "dQ", "dK", "dV"), h_q // h_k
+    whole = run((q, k, v, do), cq, ck, windows, 0)
+    for b, (n_q, n_k) in enumerate(lens):
+        if n_q == 0:
+            continue
+        sl = [slice(cq[b], cq[b + 1]), slice(ck[b], ck[b + 1])]
+        alone = run([x[:, s].contiguous() for x, s in ((q, sl[0]), (k, sl[1]), (v, sl[1]), (do, sl[0]))],
+                    [0, n_q], [0, n_k], windows, 0)
+        for name, x, y in zip(names, alone, whole):
+            assert torch.equal(x, y[:, sl[1 if name in ("dK", "dV") else 0]]), f"sequence {b}: {name} differs from the batch's"
+    for r in range(h_k):
+        part = run([x[m * r:m * r + m].contiguous() for x, m in ((q, g), (k, 1), (v, 1), (do, g))], cq, ck,
+                   None if windows is None else windows[r:r + 1], r)
+        for name, x, y in zip(names, part, whole):
+            m = 1 if name in ("dK", "dV") else g
+            assert torch.equal(x, y[m * r:m * r + m]), f"rank {r}: {name} differs from all heads'"
