@@ -36,10 +36,25 @@ __device__ inline f32x4 mfma4(float a, float b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Shape of a sequence's forward: 16 rows and eight waves (0) up to 256 workgroups
+// (one per compute unit), so that every SIMD has work; else four waves (1); at
+// d = 128 many tiles take 32 rows per workgroup (2), which halves the K and V reads
+// per product (at d = 64 it only costs occupancy).  Waves and rows fix the order of
+// the sums, so the tiles of one sequence and the heads of the whole model count,
+// not the batch or the heads of this device.  Measured: 512 tokens, 4 heads, d = 64:
+// 8.8 us with eight waves, 9.2 with four; 4096 tokens, d = 64, 16 heads: 136 us at 16
+// rows, 145 at 32; d = 128, 32 heads: 879 us at 16 rows, 821 at 32 (88 TFLOP/s).  The
+// vector-ALU kernel before took 180 us, 3.9 ms and 4.7 ms.
+__host__ __device__ inline int fp32_shape(int32_t n_q, int32_t heads, int32_t head_dim) {
+  const int64_t wgs = ((int64_t)n_q + 15) / 16 * heads;
+  return wgs <= 256 ? 0 : head_dim == 128 && wgs > 4096 ? 2 : 1;
+}
+
+// pick: the heads of the whole model if other launches take other sequences, else 0
 template <int D, int NQ, int NW>
-__global__ void __launch_bounds__(64 * NW, 2) fwd_fp32_kernel(cowa_params p, SchedView sv, const float* __restrict__ q,
-                                                              const float* __restrict__ k, const float* __restrict__ v,
-                                                              float* __restrict__ o, float* __restrict__ lse) {
+__global__ void __launch_bounds__(64 * NW, 2)
+    fwd_fp32_kernel(cowa_params p, SchedView sv, int pick, const float* __restrict__ q, const float* __restrict__ k,
+                    const float* __restrict__ v, float* __restrict__ o, float* __restrict__ lse) {
   constexpr int R = 16 * NQ;     // query rows of the workgroup
   constexpr int CK = 16;         // keys per chunk
   constexpr int GD = D / 16;     // groups of four products over d in S^T; 16-byte loads per row and lane
@@ -59,6 +74,7 @@ __global__ void __launch_bounds__(64 * NW, 2) fwd_fp32_kernel(cowa_params p, Sch
   const int n_q = sc.n_q, n_k = sc.n_k;
   const int q0 = i * R;
   if (q0 >= n_q) return;
+  if (pick > 0 && fp32_shape(n_q, pick, D) != (NQ == 2 ? 2 : NW == 4 ? 1 : 0)) return;
   const Geo32 g = sc.g;
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -213,29 +229,35 @@ __global__ void __launch_bounds__(64 * NW, 2) fwd_fp32_kernel(cowa_params p, Sch
 }
 
 template <int D, int NQ, int NW>
-hipError_t launch(const cowa_params& p, const SchedView& sv, const float* q, const float* k, const float* v, float* o,
-                  float* lse, hipStream_t stream) {
+hipError_t launch(const cowa_params& p, const SchedView& sv, int pick, const float* q, const float* k, const float* v,
+                  float* o, float* lse, hipStream_t stream) {
   const dim3 grid((unsigned)sv.n_qt * (p.tile_q / (16 * NQ)), p.h_q, sv.ragged ? 1 : p.batch);
-  hipLaunchKernelGGL((fwd_fp32_kernel<D, NQ, NW>), grid, dim3(64 * NW), 0, stream, p, sv, q, k, v, o, lse);
+  hipLaunchKernelGGL((fwd_fp32_kernel<D, NQ, NW>), grid, dim3(64 * NW), 0, stream, p, sv, pick, q, k, v, o, lse);
   return hipGetLastError();
 }
 
-// Shapes.  Up to 256 workgroups of 16 rows (one per compute unit): eight waves
-// each, so that every SIMD has work; else four.  At d = 128 a large grid takes
-// 32 rows per workgroup, which halves the K and V reads per product (at d = 64
-// it only costs occupancy).  Measured: 512 tokens, 4 heads, d = 64: 8.8 us with
-// eight waves, 9.2 with four; 4096 tokens, d = 64, 16 heads: 136 us at 16 rows,
-// 145 at 32; d = 128, 32 heads: 879 us at 16 rows, 821 at 32 (88 TFLOP/s).  The
-// vector-ALU kernel before took 180 us, 3.9 ms and 4.7 ms.  Past 2^23 row tiles
-// the 32-row shape keeps the grid within the launch limit.
+// A launch takes the sequences of its shape, or (pick 0) all of them.
 template <int D>
 hipError_t launch_d(const cowa_params& p, const SchedView& sv, const float* q, const float* k, const float* v, float* o,
                     float* lse, hipStream_t stream) {
+  const int heads = p.h_q / p.h_k * p.h_k_total;
   const int64_t tiles = (int64_t)sv.n_qt * (p.tile_q / 16);
-  const int64_t wgs = tiles * p.h_q * (sv.ragged ? 1 : p.batch);
-  if (wgs <= 256) return launch<D, 1, 8>(p, sv, q, k, v, o, lse, stream);
-  if ((D == 128 && wgs > 4096) || tiles > (1 << 23)) return launch<D, 2, 4>(p, sv, q, k, v, o, lse, stream);
-  return launch<D, 1, 4>(p, sv, q, k, v, o, lse, stream);
+  bool used[3] = {false, false, false};
+  if (tiles > (1 << 23))  // (32 rows keep the grid within the launch limit)
+    used[2] = true;
+  else if (sv.ragged)
+    for (int b = 0; b < p.batch; ++b) {
+      const int n_q = p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b];
+      if (n_q > 0) used[fp32_shape(n_q, heads, D)] = true;
+    }
+  else
+    used[fp32_shape(p.n_q, heads, D)] = true;
+  const int pick = used[0] + used[1] + used[2] > 1 ? heads : 0;
+  hipError_t err = hipSuccess;
+  if (used[2]) err = launch<D, 2, 4>(p, sv, pick, q, k, v, o, lse, stream);
+  if (err == hipSuccess && used[1]) err = launch<D, 1, 4>(p, sv, pick, q, k, v, o, lse, stream);
+  if (err == hipSuccess && used[0]) err = launch<D, 1, 8>(p, sv, pick, q, k, v, o, lse, stream);
+  return err;
 }
 
 }  // namespace

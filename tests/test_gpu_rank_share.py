@@ -137,3 +137,33 @@ def test_packed_sequence_and_window_head_equal_alone(lens, h_q, h_k, d, near, ti
         for name, x, y in zip(names, part, whole):
             m = 1 if name in ("dK", "dV") else g
             assert torch.equal(x, y[m * r:m * r + m]), f"rank {r}: {name} differs from all heads'"
+
+
+@pytest.mark.parametrize("lens,h_q,h_k,d,tile", [
+    # float32: sequences and ranks on both sides of 256 and of 4096 (d = 128) row tiles
+    # of all heads together; a batch of equal lengths
+    ([512, 4000, 100, 1025], 4, 2, 64, 32), ([600, 2100, 17], 32, 8, 128, 64), ([500, 500, 500], 4, 2, 64, 32)])
+def test_fp32_sequence_and_rank_equal_the_whole(lens, h_q, h_k, d, tile):
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(13)
+    cu = [sum(lens[:x]) for x in range(len(lens) + 1)]
+    q, k, v = (torch.randn((h, cu[-1], d), generator=gen, device=dev) for h in (h_q, h_k, h_k))
+    g = h_q // h_k
+    log(f"{lens} tokens, {h_q}/{h_k} heads, d={d}, float32")
+    whole = cowa.fwd_varlen(q, k, v, cu, cu, 16, 64, tile, tile)
+    for b, n in enumerate(lens):
+        x = [t[:, cu[b]:cu[b + 1]].contiguous() for t in (q, k, v)]
+        alone = cowa.fwd(*(t[None] for t in x), 16, 64, tile, tile)
+        for name, a, w in zip(("O", "LSE"), alone, whole):
+            assert torch.equal(a[0], w[:, cu[b]:cu[b + 1]]), f"sequence {b}: {name} differs from the batch's"
+    if len(set(lens)) == 1:
+        x = [t.reshape(t.shape[0], len(lens), lens[0], d).transpose(0, 1).contiguous() for t in (q, k, v)]
+        for name, a, w in zip(("O", "LSE"), cowa.fwd(*x, 16, 64, tile, tile), whole):
+            assert torch.equal(a.transpose(0, 1).reshape(w.shape), w), f"{name} of the fixed-length batch differs"
+    for r in (0, h_k - 1):
+        x = [t[m * r:m * r + m].contiguous() for t, m in ((q, g), (k, 1), (v, 1))]
+        part = cowa.fwd_varlen(*x, cu, cu, 16, 64, tile, tile, h_k_total=h_k, h_k_offset=r)
+        for name, a, w in zip(("O", "LSE"), part, whole):
+            assert torch.equal(a, w[g * r:g * r + g]), f"rank {r}: {name} differs from all heads'"
