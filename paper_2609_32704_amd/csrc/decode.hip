@@ -16,6 +16,7 @@
 // Everything is fp32 apart from the bf16 loads; scores are kept in base 2.
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 #include "window_rule.h"
@@ -139,20 +140,25 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
   // iteration's rows are loaded before the current one is computed.
   const int32_t n0 = runs.b0 - runs.a0 + 1, n1 = n0 + runs.b1 - runs.a1 + 1;
   const int32_t d0 = runs.a0, d1 = runs.a1 - n0, d2 = runs.a2 - n1;
-  auto load = [&](int32_t vb, uint4 (&kr)[U], uint4 (&vr)[U]) {
+  auto load = [&](int32_t vb, int32_t end, uint4 (&kr)[U], uint4 (&vr)[U]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int32_t pv = min(vb + u * STEP + wave * KG + kg, v1 - 1);
+      const int32_t pv = min(vb + u * STEP + wave * KG + kg, end - 1);
       const int64_t key = pv + (pv < n0 ? d0 : pv < n1 ? d1 : d2);
       kr[u] = ld_stream16(kbase + key * D);
       vr[u] = ld_stream16(vbase + key * D);
     }
   };
-  auto compute = [&](int32_t vb, const uint4 (&kr)[U], const uint4 (&vr)[U]) {
+  // PART: an iteration of fewer positions, of which those past its end repeat the last
+  // row with weight 0
+  auto compute = [&](int32_t vb, int32_t end, const uint4 (&kr)[U], uint4 (&vr)[U],
+                     auto partc) __attribute__((always_inline)) {
+    constexpr bool PART = decltype(partc)::value;
     float sc[U][G];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool ok = vb + u * STEP + wave * KG + kg < v1;
+      // (without the selects the compiler takes more than 256 registers at G = 8)
+      const bool ok = (!PART && G < 8) || vb + u * STEP + wave * KG + kg < end;
       const uint32_t kw[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -164,6 +170,11 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
         part = group_sum<DC>(part);
         sc[u][g] = ok ? part * a.c : -INFINITY;
       }
+    }
+    if constexpr (PART) {  // V as well as the weight, or an infinity there would count as 0 x inf
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (vb + u * STEP + wave * KG + kg >= end) vr[u] = make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -191,14 +202,19 @@ __global__ void __launch_bounds__(256) decode_split(DecArgs a) {
     }
   };
   if (v0 < v1) {
+    // a part of an iteration comes first, so that the loop needs no masks
+    constexpr int32_t IT = STEP * U;
     uint4 ka[U], va[U], kb[U], vb[U];
-    load(v0, ka, va);
-    for (int32_t x = v0; x < v1; x += 2 * STEP * U) {
-      if (x + STEP * U < v1) load(x + STEP * U, kb, vb);
-      compute(x, ka, va);
-      if (x + STEP * U >= v1) break;
-      if (x + 2 * STEP * U < v1) load(x + 2 * STEP * U, ka, va);
-      compute(x + STEP * U, kb, vb);
+    int32_t x = v0 + (v1 - v0) % IT;
+    if (x > v0) load(v0, x, ka, va);
+    if (x < v1) load(x, v1, kb, vb);
+    if (x > v0) compute(v0, x, ka, va, std::true_type{});
+    for (; x < v1; x += 2 * IT) {
+      if (x + IT < v1) load(x + IT, v1, ka, va);
+      compute(x, v1, kb, vb, std::false_type{});
+      if (x + IT >= v1) break;
+      if (x + 2 * IT < v1) load(x + 2 * IT, v1, kb, vb);
+      compute(x + IT, v1, ka, va, std::false_type{});
     }
   }
 
@@ -297,7 +313,10 @@ __global__ void __launch_bounds__(W > 4 ? 64 * W : 256) decode_combine(DecArgs a
       const bool ok = s < a.splits;
       x[u] = po[(int64_t)(ok ? s : s0) * L];
       y[u] = ml[ok ? s : s0];
-      if (!ok) y[u] = f32x2{-INFINITY, 0.f};
+      if (!ok) {  // (the values too: an infinity times weight 0 is none)
+        y[u] = f32x2{-INFINITY, 0.f};
+        x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {

@@ -147,3 +147,27 @@ def test_decode_split_counts(case):
     w = inputs.custom("dec_counts_" + name, batch=bsz, n_q=1, n_k=n_max, h_q=h_q, h_k=h_k, head_dim=d, w_sink=ws,
                       w_near=wn, kind="decode")
     _check(w, seqlens, key=inputs.key_of("dec_counts", name), split_keys=sk)
+
+
+@pytest.mark.parametrize("h_q,h_k,d,n,split_keys", [(8, 2, 128, 1000, 64), (4, 4, 64, 330, 64), (8, 1, 64, 90, 0),
+                                                    (2, 1, 128, 5000, 64), (4, 2, 128, 3001, 0)])
+def test_decode_infinite_value_stays_in_its_column(h_q, h_k, d, n, split_keys):
+    """An infinite V element makes that element of O infinite (every visible key
+    has a positive weight) and changes nothing else: no padding of a split or of the
+    combine may multiply it by zero."""
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    q = torch.randn((1, h_q, d), generator=gen, device=dev).to(torch.bfloat16)
+    kc, vc = (torch.randn((1, h_k, n, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(2))
+    sl = torch.tensor([n], dtype=torch.int32, device=dev)
+    log(f"decode {h_q}/{h_k} d={d} n={n} split_keys={split_keys}")
+    o, lse = cowa.decode(q, kc, vc, sl, 0, n, split_keys=split_keys)
+    for key in sorted({0, 1, 63, 64, 127, n // 2, n - 65, n - 2, n - 1} & set(range(n))):
+        v2 = vc.clone()
+        v2[:, :, key, 5] = float("inf")
+        o2, lse2 = cowa.decode(q, kc, v2, sl, 0, n, split_keys=split_keys)
+        want = o.clone()
+        want[..., 5] = float("inf")
+        assert torch.equal(o2, want) and torch.equal(lse2, lse), f"key {key}"
