@@ -129,6 +129,15 @@ __global__ void __launch_bounds__(64 * NW, 2)
 #pragma unroll
       for (int x = 0; x < VD; ++x) vf[r][x] = *reinterpret_cast<const f32x4*>(vrow + 64 * x);
     }
+    // keys past the end have weight 0, and V 0 as well: an infinity of the last key
+    // would otherwise count as 0 x inf
+    if (key0 + CK > n_k) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int x = 0; x < VD; ++x)
+          if (key0 + 4 * lg + r >= n_k) vf[r][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     // S^T in two chains per query tile (even and odd groups): shorter sums, and
     // independent products to issue
     f32x4 s[NQ];

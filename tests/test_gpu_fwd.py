@@ -232,3 +232,23 @@ def test_fwd_first_rows_keep_an_offset_of_their_own(h_q, h_k, d):
 
 def _round_bf16(x):
     return torch.from_numpy(np.ascontiguousarray(x)).to(torch.bfloat16).double().numpy()
+
+
+@pytest.mark.parametrize("d,n_q,n_k,tile", [(64, 1, 1, 32), (64, 33, 70, 32), (128, 100, 100, 64), (128, 5, 1003, 128)])
+def test_fwd_fp32_infinite_last_value(d, n_q, n_k, tile):
+    """An infinite V element of the last key makes that element of the last row's O
+    infinite and changes nothing else of it: key positions past the end must not
+    count it with weight 0.  (Earlier rows may share a chunk with the key.)"""
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(17)
+    q, k, v = (torch.randn((1, h, n, d), generator=gen, device=dev) for h, n in ((4, n_q), (2, n_k), (2, n_k)))
+    log(f"fp32 d={d} {n_q} x {n_k}")
+    o, lse = cowa.fwd(q, k, v, 0, n_k, tile, tile)
+    v[:, :, -1, 7] = float("-inf")
+    o2, lse2 = cowa.fwd(q, k, v, 0, n_k, tile, tile)
+    o[:, :, -1, 7] = float("-inf")
+    assert torch.equal(o2[:, :, -1], o[:, :, -1]) and torch.equal(lse2, lse)
+    keep = [x for x in range(d) if x != 7]
+    assert torch.equal(o2[..., keep], o[..., keep])
