@@ -437,7 +437,7 @@ int32_t decode_split_keys(const cowa_decode_params& p) {
 int32_t decode_num_splits(const cowa_decode_params& p) {
   const int32_t sk = decode_split_keys(p);
   const int32_t v = max_visible(p);
-  return v > 0 ? (v + sk - 1) / sk : 1;
+  return v > 0 ? (int32_t)(((int64_t)v + sk - 1) / sk) : 1;
 }
 
 size_t decode_workspace_bytes(const cowa_decode_params& p) {

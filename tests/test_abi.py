@@ -253,6 +253,13 @@ def test_decode_argument_errors_on_host():
     assert lib.cowa_decode_workspace_size(ctypes.byref(bad), ctypes.byref(n)) == abi.COWA_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("split_keys", [131072, 1 << 30, (1 << 31) - 64])
+def test_decode_split_keys_beyond_the_sequence_make_one_split(split_keys):
+    d = cowa.make_decode_params(2, 8, 2, 128, 131072, 16, 131072, split_keys=split_keys)
+    parts = 2 * 8  # (m, l, O) of one split per QO head, each array in 256-byte steps
+    assert abi.cowa_decode_workspace_size(d) == parts * 128 * 4 + 256
+
+
 @pytest.mark.parametrize("case", [(1, 512, 512, 4, 2, 16, 64, 2, 0), (1, 8192, 8192, 32, 8, 64, 1024, 8, 0),
                                   (2, 300, 1000, 6, 3, 5, 77, 8, 4), (1, 50, 50, 2, 2, 0, 0, 2, 0)])
 def test_legal_pairs_match_oracle(case):
