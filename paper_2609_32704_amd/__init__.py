@@ -123,13 +123,46 @@ def windows(params):
     return cowa_windows(params)
 
 
-def _stream(stream):
-    if stream is not None:
-        return stream
+def _stream():
     # (the raw handle of torch.cuda.current_stream(), without making its Stream
     # object: 0.5 us instead of 7)
     torch = _torch()
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _other(stream):
+    """A caller's stream handle that is not the current stream's."""
+    return stream is not None and stream != _stream()
+
+
+class _owned_by:
+    """What a call allocates belongs to the stream that uses it: with the caller's
+    stream handle current, torch's allocator hands out memory that this stream has
+    finished with, and gives what the call drops to work behind it on the same
+    stream.  ``keep`` also ties a tensor that outlives the call to the stream that
+    was current before."""
+
+    def __init__(self, stream, device):
+        cuda = _torch().cuda
+        self.before = cuda.current_stream(device)
+        # (1 names the default stream in HIP, as 0 does in torch)
+        self.stream = cuda.ExternalStream(0 if stream == 1 else int(stream), device=device)
+        self.ctx = cuda.stream(self.stream)
+
+    def __enter__(self):
+        self.ctx.__enter__()
+        return self
+
+    def __exit__(self, *exc):
+        return self.ctx.__exit__(*exc)
+
+    def keep(self, *tensors):
+        for t in tensors:
+            t.record_stream(self.before)
+
+    def use(self, schedule):
+        if schedule is not None:
+            schedule.buf.record_stream(self.stream)
 
 
 class Schedule:
@@ -138,16 +171,21 @@ class Schedule:
     device (cowa_schedule)."""
 
     def __init__(self, params, device="cuda", stream=None, build=True):
+        if _other(stream):
+            with _owned_by(stream, device) as own:
+                self.__init__(params, device, None, build)
+                own.keep(self.buf)
+            return
         torch = _torch()
         self.params = params  # its host arrays back the pointer fields of self.s.p
         self.s = cowa_schedule_size(params)
         self.buf = torch.empty(max(int(self.s.bytes), 256), dtype=torch.uint8, device=device)
         self.s.buf = self.buf.data_ptr()
         if build:
-            _abi.cowa_schedule(self.s, _stream(stream))
+            _abi.cowa_schedule(self.s, _stream())
 
     @classmethod
-    def _tables(cls, params, device, stream, backward):
+    def _tables(cls, params, device, backward):
         """A schedule of the kernels' tables only (no block lists), for calls
         that build their own and hand it to nobody."""
         torch = _torch()
@@ -156,7 +194,7 @@ class Schedule:
         self.s = _abi.cowa_schedule_size_tables(params, backward)
         self.buf = torch.empty(max(int(self.s.bytes), 256), dtype=torch.uint8, device=device)
         self.s.buf = self.buf.data_ptr()
-        _abi.cowa_schedule(self.s, _stream(stream))
+        _abi.cowa_schedule(self.s, _stream())
         return self
 
     @property
@@ -237,14 +275,20 @@ def _fwd(p, q, k, v, qs, ks, ls, schedule, out, lse, stream):
     torch = _torch()
     _validate([(q, "q", q.dtype, qs), (k, "k", q.dtype, ks), (v, "v", q.dtype, ks), (out, "out", q.dtype, qs),
                (lse, "lse", torch.float32, ls)])
+    if _other(stream):
+        with _owned_by(stream, q.device) as own:
+            own.use(schedule)
+            res = _fwd(p, q, k, v, qs, ks, ls, schedule, out, lse, None)
+            own.keep(*(t for t, given in zip(res, (out, lse)) if given is None))
+        return res
     if schedule is None:
-        schedule = Schedule._tables(p, q.device, stream, False)
+        schedule = Schedule._tables(p, q.device, False)
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty(ls, dtype=torch.float32, device=q.device)
     _abi.cowa_fwd(p, schedule.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
-                  _stream(stream))
+                  _stream())
     return out, lse
 
 
@@ -277,8 +321,14 @@ def _bwd(p, q, k, v, o, lse, do, qs, ks, ls, schedule, workspace, dq, dk, dv, st
     need = _abi.cowa_bwd_workspace_size(p)
     if workspace is not None and workspace.numel() < need:
         raise ValueError(f"workspace has {workspace.numel()} bytes, the backward needs {need}")
+    if _other(stream):
+        with _owned_by(stream, q.device) as own:
+            own.use(schedule)
+            res = _bwd(p, q, k, v, o, lse, do, qs, ks, ls, schedule, workspace, dq, dk, dv, None)
+            own.keep(*(t for t, given in zip(res, (dq, dk, dv)) if given is None))
+        return res
     if schedule is None:
-        schedule = Schedule._tables(p, q.device, stream, True)
+        schedule = Schedule._tables(p, q.device, True)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     dq = torch.empty_like(q) if dq is None else dq
@@ -286,7 +336,7 @@ def _bwd(p, q, k, v, o, lse, do, qs, ks, ls, schedule, workspace, dq, dk, dv, st
     dv = torch.empty_like(v) if dv is None else dv
     _abi.cowa_bwd(p, schedule.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                   do.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), workspace.data_ptr(),
-                  workspace.numel(), _stream(stream))
+                  workspace.numel(), _stream())
     return dq, dk, dv
 
 
@@ -332,6 +382,12 @@ def decode(q, k_cache, v_cache, seqlens_k, w_sink, w_near, softmax_scale=None, h
     need = _abi.cowa_decode_workspace_size(p)
     if workspace is not None and workspace.numel() < need:
         raise ValueError(f"workspace has {workspace.numel()} bytes, decoding needs {need}")
+    if _other(stream):
+        with _owned_by(stream, q.device) as own:
+            res = decode(q, k_cache, v_cache, seqlens_k, w_sink, w_near, softmax_scale, h_k_total, h_k_offset, split_keys,
+                         workspace, out, lse, None, windows)
+            own.keep(*(t for t, given in zip(res, (out, lse)) if given is None))
+        return res
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     if out is None:
@@ -339,7 +395,7 @@ def decode(q, k_cache, v_cache, seqlens_k, w_sink, w_near, softmax_scale=None, h
     if lse is None:
         lse = torch.empty((bsz, h_q), dtype=torch.float32, device=q.device)
     _abi.cowa_decode(p, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), seqlens_k.data_ptr(), out.data_ptr(),
-                     lse.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream(stream))
+                     lse.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream())
     return out, lse
 
 
@@ -372,11 +428,11 @@ class _Attention:
                     p = make_params(bsz, n_q, n_k, h_q, h_k, d, w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype),
                                     h_tot, h_off, wins, cq, ck)
                     _validate([(q, "q", q.dtype, qs), (k, "k", q.dtype, ks), (v, "v", q.dtype, ks)])
-                    sched = Schedule._tables(p, q.device, None, True)
+                    sched = Schedule._tables(p, q.device, True)
                     o = torch.empty_like(q)
                     lse = torch.empty(ls, dtype=torch.float32, device=q.device)
                     _abi.cowa_fwd(p, sched.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
-                                  _stream(None))
+                                  _stream())
                     ctx.save_for_backward(q, k, v, o, lse)
                     ctx.mark_non_differentiable(lse)
                     ctx.set_materialize_grads(False)
@@ -398,7 +454,7 @@ class _Attention:
                     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
                     _abi.cowa_bwd(p, sched.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                                   d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), workspace.data_ptr(),
-                                  workspace.numel(), _stream(None))
+                                  workspace.numel(), _stream())
                     return dq, dk, dv, None
 
             cls.fn = CowaAttentionFn

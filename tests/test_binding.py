@@ -88,3 +88,72 @@ def test_noncontiguous_rejected(no_library):
     k = bf(B, HK, D, NK).transpose(2, 3)
     with pytest.raises(ValueError, match="contiguous"):
         cowa.fwd(a["q"], k, a["v"], 4, 16, 64, 64)
+
+
+class _FakeStream:
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+
+@pytest.fixture
+def fake_gpu(monkeypatch):
+    """CPU tensors and a stand-in for torch's streams: logs the stream that is current
+    at each allocation, the handle of each library call and each record_stream."""
+    import contextlib
+    log = {"now": 0, "alloc": [], "calls": [], "recorded": []}
+
+    @contextlib.contextmanager
+    def stream_ctx(st):
+        before, log["now"] = log["now"], st.cuda_stream
+        yield
+        log["now"] = before
+
+    def logged(fn):
+        def make(*a, **kw):
+            t = fn(*a, **{k: v for k, v in kw.items() if k != "device"})
+            log["alloc"].append((t.data_ptr(), log["now"]))
+            return t
+        return make
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: _FakeStream(log["now"]))
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device=None: _FakeStream(handle))
+    monkeypatch.setattr(torch.cuda, "stream", stream_ctx)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: log["now"], raising=False)
+    monkeypatch.setattr(torch, "empty", logged(torch.empty))
+    monkeypatch.setattr(torch, "empty_like", logged(torch.empty_like))
+    monkeypatch.setattr(torch.Tensor, "record_stream",
+                        lambda t, st: log["recorded"].append((t.data_ptr(), st.cuda_stream)))
+    monkeypatch.setattr(cowa, "_validate", lambda specs: None)
+    for name in ("cowa_schedule", "cowa_fwd", "cowa_bwd", "cowa_decode"):
+        monkeypatch.setattr(cowa._abi, name, lambda *a, n=name: log["calls"].append((n, a[-1])))
+    return log
+
+
+def test_temporaries_belong_to_the_callers_stream(fake_gpu):
+    """With a stream handle that is not the current one, everything a call allocates
+    (tables, workspace, outputs) belongs to that stream, outputs are also kept for the
+    current one, and a schedule handed in is kept for that stream."""
+    lib_calls = fake_gpu["calls"]
+    a, d = bwd_args(), dec_args()
+    S = 4096
+    sched = cowa.Schedule(cowa.make_params(B, N, NK, HQ, HK, D, 4, 16, 64, 64), "cpu")
+    assert [s for _, s in fake_gpu["alloc"]] == [0] and lib_calls == [("cowa_schedule", 0)]
+    runs = [lambda **kw: cowa.fwd(a["q"], a["k"], a["v"], 4, 16, 64, 64, **kw),
+            lambda **kw: cowa.bwd(a["q"], a["k"], a["v"], a["o"], a["lse"], a["do"], 4, 16, 64, 64, **kw)]
+    for run in runs + [lambda **kw: cowa.decode(d["q"], d["k_cache"], d["v_cache"], d["seqlens_k"], 4, 16, **kw)]:
+        for kw in [{}] + ([{"schedule": sched}] if run in runs else []):
+            for v in ("alloc", "calls", "recorded"):
+                fake_gpu[v].clear()
+            outs = run(stream=S, **kw)
+            assert {s for _, s in fake_gpu["alloc"]} == {S}
+            assert lib_calls and {h for _, h in lib_calls} == {S}
+            for t in outs:
+                assert (t.data_ptr(), 0) in fake_gpu["recorded"]
+            assert not kw or (sched.buf.data_ptr(), S) in fake_gpu["recorded"]
+            for v in ("alloc", "calls", "recorded"):
+                fake_gpu[v].clear()
+            run(stream=0, **kw)  # the current stream's own handle
+            assert {s for _, s in fake_gpu["alloc"]} == {0} and not fake_gpu["recorded"]
+    fake_gpu["alloc"].clear()
+    cowa.Schedule(sched.params, "cpu", stream=S)
+    assert [s for _, s in fake_gpu["alloc"]] == [S] and lib_calls[-1] == ("cowa_schedule", S)

@@ -252,3 +252,32 @@ def test_autograd_checks_what_saved_tensor_hooks_return():
         o = cowa.attention(q, k, v, 4, 32)
     with pytest.raises(ValueError, match="device tensor"):
         o.sum().backward()
+
+
+def test_callers_stream_handle():
+    """Every entry point on a stream handle other than the current stream's (a side
+    stream, or the default stream while a side stream is current) gives the same bits."""
+    import paper_2609_32704_amd as cowa
+    dev = need_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(23)
+    q, k, v, do = (torch.randn((1, h, 700, 128), generator=gen, device=dev).to(torch.bfloat16) for h in (8, 2, 2, 8))
+    sl, q1 = torch.tensor([700], dtype=torch.int32, device=dev), q[:, :, -1].contiguous()
+    p = cowa.make_params(1, 700, 700, 8, 2, 128, 16, 128, 64, 64)
+
+    def run(stream):
+        o, lse = cowa.fwd(q, k, v, 16, 128, 64, 64, stream=stream)
+        sched = cowa.Schedule(p, dev, stream=stream)
+        o2, _ = cowa.fwd(q, k, v, 16, 128, 64, 64, schedule=sched, stream=stream)
+        del sched
+        grads = cowa.bwd(q, k, v, o, lse, do, 16, 128, 64, 64, stream=stream)
+        return (o, lse, o2) + grads + cowa.decode(q1, k, v, sl, 16, 128, stream=stream)
+    want = run(None)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    got = run(side.cuda_stream)
+    with torch.cuda.stream(side):
+        got0 = run(0)
+    torch.cuda.synchronize()
+    for x in (got, got0):
+        assert all(torch.equal(a, b) for a, b in zip(x, want))
