@@ -30,8 +30,6 @@
 namespace cowa {
 namespace {
 
-
-
 // Per query row: nd = -D with D = sum_d O[row, d] dO[row, d] (D/8 lanes per
 // row), and nl = -LSE log2(e), the row's exponent offset in base 2; the dK/dV
 // pass folds nd into the accumulator input of dP = dO V^T (dP - D comes out of
@@ -204,7 +202,7 @@ __device__ __forceinline__ void walk_column(const cowa_params& p, const SchedVie
   };
 
   // Every operand of a step goes global -> LDS directly, through copies the
-  // compiler does not track (dma16/dma4): the Q and dO tiles, and the LSE and
+  // compiler does not track (dma16_buf/dma4): the Q and dO tiles, and the LSE and
   // D values of its 64 rows (waves 0 and 2 copy the LSE, 1 and 3 the D values,
   // the same data twice).  Each wave issues LOADS_PER_STEP copies per step and
   // waits for them two steps later.  Rows past n_q (partial blocks only, where
@@ -582,8 +580,8 @@ __global__ void __launch_bounds__(256, D == 64 && WALK ? 2 : 1) bwd_main(cowa_pa
   } else {
     const int e = blockIdx.x - sa.n_extra;
     part = e / sa.n_items;
-    const WorkItem wi = cluster_item(e % sa.n_items, sa.rows, 1, grid_units(p, sv),
-                                     cluster_rows(sa.rows, grid_units(p, sv), 32), false);
+    const WorkItem wi = cluster_item(e % sa.n_items, sa.rows, grid_units(p, sv),
+                                     cluster_rows(sa.rows, grid_units(p, sv), 32));
     row = wi.row;
     unit = wi.unit;
   }

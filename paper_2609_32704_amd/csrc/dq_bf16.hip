@@ -51,8 +51,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // while dQ^T accumulates in AGPRs through the builtin: written as assembly
 // because the compiler gives all products of a kernel one accumulator register
 // file.  The compiler inserts no wait states for these, so the schedule keeps
-// every reader of a result at least three products behind it, and a block
-// ends with explicit wait states (settle) before its last results are read.
+// vector readers of a result behind the dQ^T products that follow its last k-step, and
+// a block ends with explicit wait states (settle) before its last results are
+// read; tests/test_mfma_distances.py checks every path of the built assembly.
 __device__ inline f32x16 mfma32_v0(const bf16x8& a, const bf16x8& b) {
   f32x16 d;
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));

@@ -10,7 +10,7 @@
 // reading the schedule's.  Every group size gets four waves: with one or two
 // waves for groups that 256 / tile_q does not divide, multi-head attention left
 // half or three quarters of the SIMDs idle.  Workgroups are grouped per XCD so
-// that rows sharing K/V blocks run together on one L2 (cluster_item).
+// that rows sharing K/V blocks run together on one L2 (row_item).
 //
 // Per KV block j of J_{h_k}(i), full blocks first, then partial ones:
 //   * K_j and V_j are copied global -> LDS with direct 16-byte buffer loads,
@@ -57,13 +57,16 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // vector ALUs) while O^T accumulates in AGPRs: written as assembly because the
 // compiler gives all products of a kernel one accumulator register file.  The
 // compiler does not see these as matrix instructions and inserts no wait states
-// for them, so the schedule keeps every reader of a result at least three
-// products behind it (the softmax of a chunk runs one chunk after its S^T; the
-// k-steps of one tile are three products apart, or separated by explicit wait
-// states), and a block ends with explicit wait states before its last S^T can
-// be read.  (A k-step chain accumulates in place; the schedule gives the
-// register allocator no reason to copy a result that may still be in flight,
-// which the kernel's assembly is checked for.)
+// for them, so the schedule keeps vector readers of a result away from it: the
+// softmax of a chunk runs one chunk after its S^T, with at least one whole product
+// (8 passes) and its own issue between the last k-step and the first reader, and a
+// block, or a chunk step without O^T products, ends with explicit wait states.  The
+// k-steps of one tile accumulate in place, on the very same registers and with the same
+// instruction, for which the matrix core forwards the accumulator: they may
+// follow each other directly (32-row waves in a row's first block do) or with an O^T
+// product between.  The register allocator could still copy, spill or write an
+// operand too close to such a product; tests/test_mfma_distances.py checks every path of
+// the built assembly for that.
 __device__ inline f32x16 mfma32_v0(const bf16x8& a, const bf16x8& b) {
   f32x16 d;
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
@@ -750,7 +753,7 @@ __device__ __forceinline__ void fwd_rows(const cowa_params& p, const RowTiles& r
 
   // O = O / l; LSE = (m + log2 l) ln 2 with the offset m of the last pass (base 2).
   // O goes out through LDS (free here: every wave is past the vote's barriers,
-  // its reads are done and its copies have landed): each wave stages its 64
+  // its reads are done and its copies have landed): each wave stages its
   // rows and stores whole rows, 16 bytes per lane, instead of 16-byte pieces of
   // 32 rows per store in the accumulator layout.
   constexpr int OP = C::OUT_PITCH;

@@ -43,37 +43,30 @@ __device__ inline int xcd_remap(int id, int total) {
   return chunk * 8 + (slot & 7);
 }
 
-// Workgroup id -> (row, group, unit) for a grid of n_rows x units x groups
-// workgroups, where the groups of one unit (one sequence and KV head) and
-// neighbouring rows read nearly the same K/V (or Q/dO) blocks.  Work is cut into
-// clusters of cq consecutive rows x the groups of one unit; cluster c runs on
-// XCD c % 8, so the workgroups an XCD runs together (one cluster) share its L2.
-// Rows go out first to last, or last to first (descending), whole cluster rows
-// at a time; the unit of an XCD's cluster rotates from one row range to the
-// next, so every XCD gets the same mix of units.  Shapes that do not tile this
-// way use the row order with chunks of 8 consecutive items per XCD.
+// Workgroup id -> (row, unit) for a grid of n_rows x units workgroups, where
+// neighbouring rows of one unit (one sequence and KV head) read nearly the same Q and
+// dO blocks.  Work is cut into clusters of cq consecutive rows of one unit;
+// cluster c runs on XCD c % 8, so the workgroups an XCD runs together (one
+// cluster) share its L2.  Rows go out first to last, whole cluster rows at a
+// time; the unit of an XCD's cluster rotates from one row range to the next, so
+// every XCD gets the same mix of units.  Shapes that do not tile this way use the
+// row order with chunks of 8 consecutive items per XCD.
 struct WorkItem {
-  int row, group, unit;
+  int row, unit;
 };
-__device__ inline WorkItem cluster_item(int id, int n_rows, int groups, int units, int cq, bool descending) {
+__device__ inline WorkItem cluster_item(int id, int n_rows, int units, int cq) {
   WorkItem w;
   const int n_clusters = units * (n_rows / cq);
   if (n_rows % cq == 0 && n_clusters % 8 == 0) {
-    const int cs = cq * groups;  // workgroups per cluster
-    const int xcd = id & 7, n = id >> 3;
-    const int c = (n / cs) * 8 + xcd, item = n % cs;
+    const int n = id >> 3, c = (n / cq) * 8 + (id & 7);
     const int r = c / units;
     w.unit = (c % units + r) % units;
-    w.group = item % groups;
-    w.row = r * cq + item / groups;
+    w.row = r * cq + n % cq;
   } else {
-    const int per_row = groups * units;
-    const int work = xcd_remap(id, n_rows * per_row);
-    w.row = work / per_row;
-    w.unit = (work % per_row) / groups;
-    w.group = work % groups;
+    const int work = xcd_remap(id, n_rows * units);
+    w.row = work / units;
+    w.unit = work % units;
   }
-  if (descending) w.row = n_rows - 1 - w.row;
   return w;
 }
 
@@ -124,7 +117,7 @@ struct SwzTile {
   __device__ static inline int off_col(int row, int col) { return off(row, col >> 3) + ((col & 7) << 1); }
 };
 
-// Global -> LDS copies issued as inline assembly: 16 (dma16) or 4 (dma4) bytes
+// Global -> LDS copies issued as inline assembly: 16 (dma16_buf) or 4 (dma4) bytes
 // per lane, lane l landing at LDS byte address lds_base + 16 l (or 4 l).  The
 // compiler does not see these as memory operations, so it neither counts them
 // in its own s_waitcnt arithmetic nor makes unrelated LDS reads wait for them;
@@ -136,12 +129,6 @@ struct SwzTile {
 // assembly comes from these statements), so nothing live is overwritten.
 __device__ inline uint32_t lds_addr(const unsigned char* p) {
   return (uint32_t)(uintptr_t)(lds_void*)p;
-}
-__device__ inline void dma16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(gptr), "s"(lds_base)
-               : "memory", "m0");
 }
 __device__ inline void dma4(const void* gptr, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
@@ -159,7 +146,7 @@ __device__ inline i32x4 buffer_rsrc(const void* base, uint32_t bytes) {
   return i32x4{(int)(uint32_t)a, (int)((a >> 32) & 0xffffu), (int)bytes, 0x00020000};
 }
 // 16 bytes per lane from a buffer straight into LDS: lane l lands at
-// lds_base + 16 l.  Issued as assembly and waited for explicitly, like dma16.
+// lds_base + 16 l.  Issued as assembly and waited for explicitly, like dma4.
 __device__ inline void dma16_buf(uint32_t voff, i32x4 rsrc, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
                :

@@ -46,14 +46,6 @@ __host__ __device__ inline HeadGeo make_geo_bounds(int32_t n_q, int32_t n_k, int
   return g;
 }
 
-__host__ __device__ inline HeadGeo make_geo(int32_t n_q, int32_t n_k, int32_t w_sink, int32_t w_near,
-                                            int32_t tile_q, int32_t tile_k, int32_t hg, int32_t ht) {
-  HeadGeo g;
-  g.n_q = n_q; g.n_k = n_k; g.w_sink = w_sink; g.w_near = w_near; g.tile_q = tile_q; g.tile_k = tile_k;
-  long_bounds(n_k, w_sink, w_near, hg, ht, &g.lo, &g.hi);
-  return g;
-}
-
 // Element predicate of Eq. fwa_support (set union of the three windows).
 __host__ __device__ inline bool legal_pair(const HeadGeo& g, int64_t q, int64_t k) {
   if (q >= g.n_q || k >= g.n_k) return false;

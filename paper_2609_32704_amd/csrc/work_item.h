@@ -20,7 +20,6 @@ struct SeqCtx {
   int32_t n_q, n_k;  // its lengths
   int64_t q0, qh;    // row (of d elements) of query 0 of QO head 0; + qh per QO head (Q, O, dO, dQ, LSE, D)
   int64_t k0, kh;    // row of key 0 of KV head 0; + kh per KV head (K, V, dK, dV)
-  int32_t sched;     // schedule row (QO side) or column (KV side) of (h_k, block)
   Geo32 g;           // window of (b, h_k), bounds clamped to n_k
 };
 
@@ -58,7 +57,6 @@ __device__ inline SeqCtx seq_ctx(const cowa_params& p, const SchedView& sv, int 
     c.kh = p.n_k;
     wd = sv.win + (sv.per_seq_win ? c.b * p.h_k : 0) + hk;
   }
-  c.sched = hk * (qside ? sv.n_qt : sv.n_kt) + row;
   const WinDesc w = *wd;
   c.g.off = c.n_k - c.n_q;
   c.g.w_near = w.near < c.n_k ? w.near : c.n_k;
