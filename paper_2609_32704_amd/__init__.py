@@ -185,9 +185,12 @@ class Schedule:
             _abi.cowa_schedule(self.s, _stream())
 
     @classmethod
-    def _tables(cls, params, device, backward):
+    def _tables(cls, params, device, stream, backward):
         """A schedule of the kernels' tables only (no block lists), for calls
         that build their own and hand it to nobody."""
+        if _other(stream):
+            with _owned_by(stream, device):
+                return cls._tables(params, device, None, backward)
         torch = _torch()
         self = cls.__new__(cls)
         self.params = params
@@ -282,7 +285,7 @@ def _fwd(p, q, k, v, qs, ks, ls, schedule, out, lse, stream):
             own.keep(*(t for t, given in zip(res, (out, lse)) if given is None))
         return res
     if schedule is None:
-        schedule = Schedule._tables(p, q.device, False)
+        schedule = Schedule._tables(p, q.device, None, False)
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
@@ -328,7 +331,7 @@ def _bwd(p, q, k, v, o, lse, do, qs, ks, ls, schedule, workspace, dq, dk, dv, st
             own.keep(*(t for t, given in zip(res, (dq, dk, dv)) if given is None))
         return res
     if schedule is None:
-        schedule = Schedule._tables(p, q.device, True)
+        schedule = Schedule._tables(p, q.device, None, True)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     dq = torch.empty_like(q) if dq is None else dq
@@ -428,7 +431,7 @@ class _Attention:
                     p = make_params(bsz, n_q, n_k, h_q, h_k, d, w_sink, w_near, tq, tk, scale, _dtype_code(q.dtype),
                                     h_tot, h_off, wins, cq, ck)
                     _validate([(q, "q", q.dtype, qs), (k, "k", q.dtype, ks), (v, "v", q.dtype, ks)])
-                    sched = Schedule._tables(p, q.device, True)
+                    sched = Schedule._tables(p, q.device, None, True)
                     o = torch.empty_like(q)
                     lse = torch.empty(ls, dtype=torch.float32, device=q.device)
                     _abi.cowa_fwd(p, sched.s, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
