@@ -43,30 +43,11 @@
 namespace cowa {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// S^T and dP^T products with the accumulator in VGPRs (read by the vector ALUs)
-// while dQ^T accumulates in AGPRs through the builtin: written as assembly
-// because the compiler gives all products of a kernel one accumulator register
-// file.  The compiler inserts no wait states for these, so the schedule keeps
-// vector readers of a result behind the dQ^T products that follow its last k-step, and
-// a block ends with explicit wait states (settle) before its last results are
-// read; tests/test_mfma_distances.py checks every path of the built assembly.
-__device__ inline f32x16 mfma32_v0(const bf16x8& a, const bf16x8& b) {
-  f32x16 d;
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
-  return d;
-}
-__device__ inline f32x16 mfma32_v(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  f32x16 d = c;
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
-  return d;
-}
-__device__ inline f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
+// S^T and dP^T accumulate in VGPRs (mfma32_v), dQ^T in AGPRs (mfma32), whose products lie
+// between the last k-step and the exponentials; block ends have wait states.
 __device__ inline void settle(f32x16 (&s)[1], f32x16 (&d)[1]) {
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(s[0]), "+v"(d[0]));
 }

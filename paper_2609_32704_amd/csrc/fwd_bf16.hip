@@ -49,38 +49,12 @@
 namespace cowa {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// S^T = K Q^T products with the accumulator in VGPRs (read by the softmax on the
-// vector ALUs) while O^T accumulates in AGPRs: written as assembly because the
-// compiler gives all products of a kernel one accumulator register file.  The
-// compiler does not see these as matrix instructions and inserts no wait states
-// for them, so the schedule keeps vector readers of a result away from it: the
-// softmax of a chunk runs one chunk after its S^T, with at least one whole product
-// (8 passes) and its own issue between the last k-step and the first reader, and a
-// block, or a chunk step without O^T products, ends with explicit wait states.  The
-// k-steps of one tile accumulate in place, on the very same registers and with the same
-// instruction, for which the matrix core forwards the accumulator: they may
-// follow each other directly (32-row waves in a row's first block do) or with an O^T
-// product between.  The register allocator could still copy, spill or write an
-// operand too close to such a product; tests/test_mfma_distances.py checks every path of
-// the built assembly for that.
-__device__ inline f32x16 mfma32_v0(const bf16x8& a, const bf16x8& b) {
-  f32x16 d;
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
-  return d;
-}
-__device__ inline f32x16 mfma32_v(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  f32x16 d = c;
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
-  return d;
-}
-__device__ inline f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-// wait states after the products above before their results are read; the
+// S^T = K Q^T accumulates in VGPRs (mfma32_v), O^T in AGPRs (mfma32).  An O^T product lies
+// between the last k-step of a chunk and its softmax; chunk steps without those and
+// block ends have these wait states before the results are read.  The
 // accumulators pass through the statement, so no reader is moved above it
 __device__ inline void mfma_settle(f32x16& a, f32x16& b) {
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(a), "+v"(b));

@@ -26,6 +26,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
@@ -196,6 +197,33 @@ __device__ inline void static_for(F&& f) {
 
 __device__ inline f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// 32x32x16 products with the accumulator in VGPRs (read by the vector ALUs), for
+// kernels whose other products accumulate in AGPRs through mfma32: written as
+// assembly because the compiler gives all products of a kernel one accumulator register
+// file.  B comes from AGPRs.  The compiler does not see these as matrix
+// instructions and inserts no wait states for them, so a kernel's schedule keeps
+// vector readers of a result away from it (a whole product of 8 passes and its own issue
+// between the last k-step and the first reader, or explicit wait states).  The
+// k-steps of one tile accumulate in place, on the very same registers and with the
+// same instruction, for which the matrix core forwards the accumulator: they may
+// follow each other directly (32-row waves in a row's first block do) or with another
+// product between.  The register allocator could still copy, spill or write an
+// operand too close to such a product; tests/test_mfma_distances.py checks every
+// path of the built assembly for that.
+__device__ inline f32x16 mfma32_v0(const bf16x8& a, const bf16x8& b) {
+  f32x16 d;
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+  return d;
+}
+__device__ inline f32x16 mfma32_v(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+  f32x16 d = c;
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+  return d;
+}
+__device__ inline f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
 }  // namespace cowa
