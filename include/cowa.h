@@ -207,7 +207,9 @@ cowa_status cowa_schedule(const cowa_schedule_t* s, void* stream);
  * keeps one schedule row in LDS: COWA_ERR_UNSUPPORTED (before any launch)
  * when ceil(N_k / tile_k) exceeds 8188 (head_dim 128, tile_k 128; 24572 for
  * tile_k 64 or head_dim 64 with tile_k 128; 32764 for head_dim 64, tile_k
- * 64), i.e. 1M key tokens at 128. */
+ * 64), i.e. 1M key tokens at 128.  O and LSE of a sequence do not depend on the
+ * batch or pack it is in, nor those of a head on which other heads the call holds,
+ * bit for bit (float32: given h_k_total). */
 cowa_status cowa_fwd(const cowa_params* p, const cowa_schedule_t* s,
                      const void* q, const void* k, const void* v,
                      void* o, float* lse, void* stream);
