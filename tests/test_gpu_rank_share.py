@@ -69,7 +69,8 @@ def test_rank_share_equals_all_heads_slice():
     # columns in parts: by a workgroup each alone, in a batch by a workgroup each (1000) or
     # by one per column (the next two); sink columns only (4096, 65536); d = 64
     (1000, 4, 32, 8, 128, 128), (1000, 10, 32, 8, 128, 128), (2048, 4, 32, 8, 128, 1024), (4096, 4, 32, 8, 128, 1024),
-    (65536, 2, 32, 8, 128, 4096), (1500, 3, 16, 4, 64, 128), (1500, 104, 8, 2, 64, 128)])
+    (8192, 1, 32, 8, 128, 1024), (8192, 3, 8, 2, 128, 1024),
+    (16384, 2, 32, 8, 128, 2048), (65536, 2, 32, 8, 128, 4096), (1500, 3, 16, 4, 64, 128), (1500, 104, 8, 2, 64, 128)])
 def test_rank_and_batch_entry_equal_the_whole(n, batch, h_q, h_k, d, near):
     import paper_2609_32704_amd as cowa
     dev = need_gpu()
